@@ -46,6 +46,9 @@ static const Cfg kCfgs[] = {
     {128, 160, 32, 4, 1, 1.75f, 2, 3, 12, true},
 };
 static constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
+// 32 x 32 tiles: the direct kernel (gemm_direct.hip) where it takes the
+// problem, else one wave a tile with run-time gathers
+static constexpr int kCfg32 = 7;
 
 int gemm_num_cfgs() { return kNumCfgs; }
 
@@ -119,7 +122,7 @@ static GemmFn pick_fn(const GemmDesc& d, int prec, int cfg, bool lean) {
     if (lean) return split_fn(g.split, d.b_mode == LOAD_KVEC ? LOAD_KVEC : LOAD_MNVEC);
     cfg = g.fallback;
   }
-  return gemm_fn_prec(prec, cfg, gemm_variant(d));
+  return gemm_fn_prec(prec, cfg, cfg == kCfg32 ? 0 : gemm_variant(d));
 }
 
 // grouped configurations: 0 -> 128x128, 1 -> 64x64, 2 -> 32x32, 3 -> 64x64 in two k-slices
@@ -256,8 +259,19 @@ static int heuristic_cfg(const GemmDesc& d, int prec) {
   // one workgroup per compute unit for the large tiles; a GEMM that shares
   // the chip with a concurrent stream counts on half of them
   const int kSlots = g_shared ? 128 : 256;
+  // Few tiles: a call lasts as long as one tile's chain of loads and
+  // products, which the direct kernel cuts over eight waves.  Measured
+  // against the best staged tile (M x N x K, graph replay): 256 x 512 x 256
+  // FP32 11.6 -> 4.3 us, 512 x 512 x 1024 30.8 -> 11.0; at 640 tiles (1280 x
+  // 512 x 256) FP32 11.2 -> 9.3, at 672 13.0 -> 15.5.  The split precisions
+  // issue less matrix-core time per product and win up to about 1024 tiles
+  // (1024 x 1024 x 128 8.8 -> 7.0; 1536 x 1024 x 512 21.5 -> 25.4).
+  if (direct_ok(d)) {
+    const int64_t tiles = (int64_t)((d.M + 31) / 32) * ((d.N + 31) / 32) * d.batch;
+    if (tiles <= (prec == TN_PREC_FP32 ? 640 : 1024)) return kCfg32;
+  }
   double best = 1e300;
-  int best_c = 7;   // 32 x 32 tiles fit every problem
+  int best_c = kCfg32;   // 32 x 32 tiles fit every problem
   for (int c = 0; c < kNumCfgs; ++c) {
     if (!cfg_allowed(d, prec, c)) continue;
     const Cfg& g = kCfgs[c];
@@ -383,6 +397,12 @@ void grouped_tune_put(uint64_t sig, int prec, int cfg, bool timed) {
 
 int32_t launch_gemm_cfg(GemmDesc& d, int32_t prec, int cfg, hipStream_t st) {
   if (cfg < 0 || cfg >= kNumCfgs) return fail(TN_ERR_INVALID_ARGUMENT, "bad tile config %d", cfg);
+  if (cfg == kCfg32 && direct_ok(d)) {
+    // the lanes of a store run along n: exchange the operands where C is
+    // contiguous along m
+    auto unit = [](const Group& r) { return r.n > 0 && r.s[1][r.n - 1] == 1; };
+    return launch_gemm_direct(unit(d.gm) && !unit(d.gn) ? exchanged(d) : d, prec, st);
+  }
   const Cfg& g = kCfgs[cfg];
   // the problem the kernel runs on (exchanged operands for the swap kinds)
   // and whether the lean kind applies; otherwise the general tile of the
@@ -436,8 +456,14 @@ static int heuristic_choice(const GemmDesc& d, int prec) {
   const int c = heuristic_cfg(d, prec);
   if (!g_splitk || g_forced_cfg.load() >= 0) return c;
   const int64_t slots = g_shared ? 128 : 256, tiles = cfg_tiles(d, c);
+  // the direct kernel cuts K over its own waves: a slice of 256 keeps a wave
+  // one set of loads (4.5 us), and below 1024 the slices' sum costs more than
+  // they save (K = 512 whole: 5.5 us)
+  const bool direct = c == kCfg32 && direct_ok(d);
+  if (direct && d.K < 1024) return c;
+  const int64_t most = direct ? 2 * slots : slots, least_k = direct ? 256 : 128;
   for (int lg = max_slice_lg(); lg >= 1; --lg)
-    if (slices_ok(d, lg) && tiles << lg <= slots && d.K >> lg >= 128) return c + 100 * lg;
+    if (slices_ok(d, lg) && tiles << lg <= most && d.K >> lg >= least_k) return c + 100 * lg;
   return c;
 }
 
@@ -481,7 +507,7 @@ static int tune_cfg(GemmDesc& d, int32_t prec, int level, hipStream_t st) {
   for (int v = 0; v < kNumCfgs * (max_slice_lg() + 1); ++v) {
     const int c = v % kNumCfgs, lg = v / kNumCfgs;
     const Cfg& g = kCfgs[c];
-    if ((int64_t)g.bm * g.bn > 4ll * d.M * d.N && c != 7) continue;  // mostly padding (32 x 32 always runs)
+    if ((int64_t)g.bm * g.bn > 4ll * d.M * d.N && c != kCfg32) continue;  // mostly padding (32 x 32 always runs)
     if (!cfg_allowed(d, prec, c)) continue;
     // k-slices only where the whole GEMM leaves most compute units idle
     if (lg > 0 && (!slices_ok(d, lg) || cfg_tiles(d, c) << lg > 512 || cfg_tiles(d, c) >= 256)) continue;

@@ -88,6 +88,9 @@ int32_t householder_apply_q(const double* xc, int m, int n, const double* tf, do
 // K <= 32 with N or M <= 16 (and no batch, scale or max-abs): the HBM-bound path
 bool gemm_small_fits(const GemmDesc& d);
 int32_t launch_gemm_small(const GemmDesc& d, int32_t prec, hipStream_t st);
+// direct kernels (gemm_direct.hip): 32 x 32 tiles, eight waves cutting K
+bool direct_ok(const GemmDesc& d);
+int32_t launch_gemm_direct(const GemmDesc& d, int32_t prec, hipStream_t st);
 int32_t launch_gemm_cfg(GemmDesc& d, int32_t prec, int cfg, hipStream_t st);
 int gemm_num_cfgs();
 

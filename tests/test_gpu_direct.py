@@ -1,0 +1,105 @@
+"""The direct contraction kernel (32 x 32 tiles, K cut over eight waves)
+against the FP64 oracle where it can go wrong: tile remainders, every
+remainder of the chunk of K, fewer chunks than waves, one more than a wave
+keeps in flight, all pairs of layouts, several axes a group, permuted
+outputs, and the problems it does not take.
+
+Tolerances as in test_gpu_contract.py: the stated accuracy of each precision.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1905_01330_amd as tn
+
+pytestmark = pytest.mark.gpu
+
+DEV = torch.device("cuda:0")
+TOL = {"fp32": 1e-5, "split_bf16": 1e-6, "split_bf16_3p": 1e-4, "bf16": 2e-2}
+TILE = 7   # the 32 x 32 configuration
+
+
+def gpu(x):
+    return torch.tensor(np.asarray(x, dtype=np.float32), device=DEV)
+
+
+def check(got, a, b, pa, pb, tol, what):
+    torch.cuda.synchronize()
+    got = got.cpu().double().numpy()
+    ref = oracle.tensordot(a, b, pa, pb)
+    scale = oracle.tensordot(np.abs(a), np.abs(b), pa, pb)
+    rel = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    assert rel <= tol, f"{what}: relative error {rel:.3e} > {tol:.1e}"
+    assert (np.abs(got - ref) <= 4 * tol * scale + 1e-30).all(), what
+
+
+def stored(x, inner):
+    """x [rows, k] on the device with k unit-stride ("k"), the rows ("m"), or neither ("g")."""
+    if inner == "k":
+        return gpu(x)
+    if inner == "m":
+        return gpu(x.T.copy()).t()
+    wide = gpu(np.zeros((x.shape[0], 2 * x.shape[1])))
+    wide[:, ::2] = gpu(x)
+    return wide[:, ::2]
+
+
+@pytest.mark.parametrize("prec", list(TOL))
+@pytest.mark.parametrize("layout", ["kk", "km", "mk", "mm", "gk", "mg", "gg"])
+def test_edges_of_the_tile_and_of_k(prec, layout):
+    rng = np.random.default_rng(91)
+    ks = [2, 3, 7, 8, 9, 15, 16, 17, 31, 33, 64, 127, 130, 391, 513, 1030]
+    shapes = [(32, 32), (2, 33), (31, 5), (65, 32), (33, 70)]
+    for i, k in enumerate(ks):
+        m, n = shapes[i % len(shapes)]
+        a = rng.standard_normal((m, k)).astype(np.float32)
+        b = rng.standard_normal((n, k)).astype(np.float32)
+        got = tn.contract_between(stored(a, layout[0]), stored(b, layout[1]), [1], [1], prec=prec)
+        if k > 1 and m * n > 256:
+            assert tn.tune_last_choice() == TILE
+        check(got, a, b, [1], [1], TOL[prec], f"{m}x{n}x{k}")
+
+
+@pytest.mark.parametrize("prec", ["fp32", "split_bf16"])
+@pytest.mark.parametrize("inner", [3, 4, 20])
+def test_groups_of_several_axes(prec, inner):
+    """Two contracted axes that do not merge (inner extents off and on the
+    multiples of four), three free axes a side, the result written through
+    permuted strides with either side contiguous; then three contracted
+    axes, and four free ones, which the kernel does not take."""
+    rng = np.random.default_rng(92)
+    a = rng.standard_normal((5, 3, 6, 7, inner)).astype(np.float32)      # m m k m k
+    b = rng.standard_normal((inner, 4, 6, 3, 5)).astype(np.float32)      # k n k n n
+    out = torch.empty((5, 3, 7, 4, 3, 5), device=DEV)
+    tn.contract_between(gpu(a), gpu(b), [2, 4], [2, 0], out=out, prec=prec)
+    check(out, a, b, [2, 4], [2, 0], TOL[prec], "n contiguous")
+    back = torch.empty(5 * 3 * 7 * 4 * 3 * 5, device=DEV)
+    view = torch.as_strided(back, (5, 3, 7, 4, 3, 5), (1, 35, 5, 105 * 15, 105 * 5, 105))   # m axis 0 contiguous
+    tn.contract_between(gpu(a), gpu(b), [2, 4], [2, 0], out=view, prec=prec)
+    check(view, a, b, [2, 4], [2, 0], TOL[prec], "m contiguous")
+    a = rng.standard_normal((9, 2, 5, 3, 4, inner)).astype(np.float32)
+    b = rng.standard_normal((inner, 11, 2, 3, 4)).astype(np.float32)
+    got = tn.contract_between(gpu(a), gpu(b), [1, 3, 5], [2, 3, 0], prec=prec)
+    check(got, a, b, [1, 3, 5], [2, 3, 0], TOL[prec], "three contracted axes")
+    a = rng.standard_normal((2, 3, 2, 5, 2, inner)).astype(np.float32)
+    ga = gpu(a.transpose(3, 5, 0, 2, 4, 1).copy()).permute(2, 5, 3, 0, 4, 1)
+    b = rng.standard_normal((40, inner)).astype(np.float32)
+    check(tn.contract_between(ga, gpu(b), [5], [1], prec=prec), a, b, [5], [1], TOL[prec], "five free axes")
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+def test_infinities_stay_in_their_rows(bad):
+    """A row past the end of a tile repeats the last one, and k past the end
+    reads as zero: neither may carry an infinity or NaN elsewhere."""
+    rng = np.random.default_rng(93)
+    a = rng.standard_normal((34, 37)).astype(np.float32)
+    b = rng.standard_normal((35, 37)).astype(np.float32)
+    a[33, 36] = bad
+    got = tn.contract_between(gpu(a), gpu(b), [1], [1]).cpu().double().numpy()
+    with np.errstate(invalid="ignore"):
+        ref = a.astype(np.float64) @ b.T.astype(np.float64)
+    assert np.isfinite(got[:33]).all()
+    assert np.array_equal(np.isnan(got[33]), np.isnan(ref[33]))
+    assert np.array_equal(np.isposinf(got[33]), np.isposinf(ref[33]))
+    assert np.allclose(got[:33], ref[:33], rtol=0, atol=1e-4)
