@@ -253,6 +253,12 @@ __global__ void __launch_bounds__(256) slice_sum_kernel(const float* __restrict_
   }
 }
 
+// tiles of configuration c on the caller's problem
+static int64_t cfg_tiles(const GemmDesc& d, int c) {
+  const Cfg& g = kCfgs[c];
+  return (int64_t)((d.M + g.bm - 1) / g.bm) * ((d.N + g.bn - 1) / g.bn) * d.batch;
+}
+
 static int heuristic_cfg(const GemmDesc& d, int prec) {
   const int forced = g_forced_cfg.load();
   if (forced >= 0) return forced;
@@ -262,14 +268,14 @@ static int heuristic_cfg(const GemmDesc& d, int prec) {
   // Few tiles: a call lasts as long as one tile's chain of loads and
   // products, which the direct kernel cuts over eight waves.  Measured
   // against the best staged tile (M x N x K, graph replay): 256 x 512 x 256
-  // FP32 11.6 -> 4.3 us, 512 x 512 x 1024 30.8 -> 11.0; at 640 tiles (1280 x
-  // 512 x 256) FP32 11.2 -> 9.3, at 672 13.0 -> 15.5.  The split precisions
-  // issue less matrix-core time per product and win up to about 1024 tiles
-  // (1024 x 1024 x 128 8.8 -> 7.0; 1536 x 1024 x 512 21.5 -> 25.4).
-  if (direct_ok(d)) {
-    const int64_t tiles = (int64_t)((d.M + 31) / 32) * ((d.N + 31) / 32) * d.batch;
-    if (tiles <= (prec == TN_PREC_FP32 ? 640 : 1024)) return kCfg32;
-  }
+  // FP32 11.6 -> 4.5 us, 512 x 512 x 1024 30.8 -> 8.6; at 2560 tiles (2560 x
+  // 1024 x 512) FP32 54.4 -> 35.1, split-BF16 37.7 -> 30.9, past which the
+  // larger tiles fill the chip.  With K below 128 the sums and stores weigh
+  // more: 1024 x 1024 x 64 6.4 either way, 2048 x 1024 x 32 8.1 -> 10.3.  Two
+  // problems at once (a shared chip, or both in one launch) count on less
+  // than half: 1024 tiles each.
+  const int64_t most = d.K >= 128 ? (g_shared ? 1024 : 2560) : (g_shared ? 320 : 640);
+  if (direct_ok(d) && cfg_tiles(d, kCfg32) <= most) return kCfg32;
   double best = 1e300;
   int best_c = kCfg32;   // 32 x 32 tiles fit every problem
   for (int c = 0; c < kNumCfgs; ++c) {
@@ -443,12 +449,6 @@ static int32_t launch_choice(GemmDesc& d, int32_t prec, int v, hipStream_t st) {
   return hip_check(hipGetLastError(), "k-slice sum");
 }
 
-// tiles of configuration c on the caller's problem
-static int64_t cfg_tiles(const GemmDesc& d, int c) {
-  const Cfg& g = kCfgs[c];
-  return (int64_t)((d.M + g.bm - 1) / g.bm) * ((d.N + g.bn - 1) / g.bn) * d.batch;
-}
-
 // the heuristic choice: the estimated tile, cut into k-slices when its tiles
 // fill at most half the compute units it can count on (a quarter for four
 // slices) and every slice keeps at least 128 of k
@@ -465,6 +465,16 @@ static int heuristic_choice(const GemmDesc& d, int prec) {
   for (int lg = max_slice_lg(); lg >= 1; --lg)
     if (slices_ok(d, lg) && tiles << lg <= most && d.K >> lg >= least_k) return c + 100 * lg;
   return c;
+}
+
+bool direct_chosen(const GemmDesc& d, int32_t prec) {
+  log_enabled();
+  {
+    std::lock_guard<std::mutex> lk(g_tune_mu);
+    if (g_tune_level > 0 || !g_tune_path.empty()) return false;
+  }
+  SharedChipScope shared;
+  return g_forced_cfg.load() < 0 && direct_ok(d) && heuristic_choice(d, prec) == kCfg32;
 }
 
 // the stream on which the tuner runs the second copy of a GEMM that shares

@@ -91,6 +91,27 @@ int32_t launch_gemm_small(const GemmDesc& d, int32_t prec, hipStream_t st);
 // direct kernels (gemm_direct.hip): 32 x 32 tiles, eight waves cutting K
 bool direct_ok(const GemmDesc& d);
 int32_t launch_gemm_direct(const GemmDesc& d, int32_t prec, hipStream_t st);
+// whether a GEMM issued now beside another of its size runs whole on the
+// direct kernel: few tiles, no tile forced, no tuning and no tile cache file
+// that could say otherwise
+bool direct_chosen(const GemmDesc& d, int32_t prec);
+// two independent GEMMs (either may be null) in one launch of the direct
+// kernel, where direct_pair_ok
+bool direct_pair_ok(const GemmDesc* l, const GemmDesc* r);
+int32_t launch_direct_pair(const GemmDesc* l, const GemmDesc* r, int32_t prec, hipStream_t st);
+// a site of the operator sweeps: its environment (L_k or R_k+1), tensors and
+// the intermediate it leaves for the second contraction (dense T2[a', t, v, b]
+// on the left, T2'[u, a, t, b'] on the right)
+struct WstepSite {
+  const tn_tensor* env;
+  const tn_tensor* site;
+  const tn_tensor* mpo;
+  float* out;
+};
+// the first contraction and the operator step of a left and a right site
+// (either may be null) in one launch, where direct_wstep_ok
+bool direct_wstep_ok(const WstepSite* l, const WstepSite* r);
+int32_t launch_direct_wstep(const WstepSite* l, const WstepSite* r, int32_t prec, hipStream_t st);
 int32_t launch_gemm_cfg(GemmDesc& d, int32_t prec, int cfg, hipStream_t st);
 int gemm_num_cfgs();
 

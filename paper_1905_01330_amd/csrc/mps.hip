@@ -25,10 +25,15 @@ __device__ inline int scale_exponent(uint32_t bits) {
   return e - 127;
 }
 
-__global__ void mps_init_kernel(float* e0, uint32_t* slots, int n_slots) {
-  for (int i = threadIdx.x + blockIdx.x * blockDim.x; i < n_slots; i += blockDim.x * gridDim.x)
-    slots[i] = i == 0 ? 0x3f800000u : 0u;
-  if (threadIdx.x == 0 && blockIdx.x == 0) e0[0] = 1.0f;
+// the environments before the first site (one, or one per end of the chain:
+// grid y) and their |E| slots
+__global__ void mps_init_kernel(float* e0, uint32_t* slots, int n_slots, float* er0, uint32_t* rslots, int n_rslots) {
+  float* e = blockIdx.y ? er0 : e0;
+  uint32_t* sl = blockIdx.y ? rslots : slots;
+  const int n = blockIdx.y ? n_rslots : n_slots;
+  for (int i = threadIdx.x + blockIdx.x * blockDim.x; i < n; i += blockDim.x * gridDim.x)
+    sl[i] = i == 0 ? 0x3f800000u : 0u;
+  if (threadIdx.x == 0 && blockIdx.x == 0) e[0] = 1.0f;
 }
 
 __global__ void mps_finish_kernel(const float* e_final, const uint32_t* slots, int n_used, double* out2) {
@@ -120,52 +125,85 @@ static int32_t check_chain(int32_t n_sites, const tn_tensor* sites, const char* 
   return TN_OK;
 }
 
-// GEMM views of one inner-product site (shared by the single and batched paths)
+// GEMM views of one inner-product site
 //   T[a', s, b] = sum_a E[a', a] phi[a, s, b]        (E scaled by 2^-e of slot k)
 //   E'[b', b]  = sum_{a', s} psi[a', s, b'] T[a', s, b]
-static int32_t inner_site(const tn_tensor& psi, const tn_tensor& phi, float* e_in, float* e_out, float* t,
-                          uint32_t* slots, int k, int32_t prec, hipStream_t st, float* sk = nullptr,
-                          size_t sk_floats = 0) {
-  SplitKScope slices(sk, sk_floats);
+static int32_t inner_plan(const tn_tensor& psi, const tn_tensor& phi, float* e_in, float* e_out, float* t,
+                          uint32_t* in_slot, uint32_t* out_slot, GemmDesc& g1, GemmDesc& g2) {
   const int64_t da = psi.shape[0], db = phi.shape[0], d = psi.shape[1];
   const int64_t da2 = psi.shape[2], db2 = phi.shape[2];
   tn_tensor e = make_view(e_in, TN_F32, {da, db});
   tn_tensor tv = make_view(t, TN_F32, {da, d, db2});
   tn_tensor eo = make_view(e_out, TN_F32, {da2, db2});
   const int32_t a1[1] = {1}, b1[1] = {0};
-  GemmDesc g;
-  TN_TRY(plan_gemm(e, phi, 1, a1, b1, tv, g));
-  g.a_scale_bits = slots + k;
-  TN_TRY(launch_gemm(g, prec, st));
+  TN_TRY(plan_gemm(e, phi, 1, a1, b1, tv, g1));
+  g1.a_scale_bits = in_slot;
   const int32_t a2[2] = {0, 1}, b2[2] = {0, 1};
-  TN_TRY(plan_gemm(psi, tv, 2, a2, b2, eo, g));
-  g.c_absmax = slots + k + 1;
-  return launch_gemm(g, prec, st);
+  TN_TRY(plan_gemm(psi, tv, 2, a2, b2, eo, g2));
+  g2.c_absmax = out_slot;
+  return TN_OK;
 }
 
 // right-to-left site of the two-sided inner product
 //   T[a', s, b] = sum_b' psi[a', s, b'] E_R[b', b]   (scaled by 2^-e of in_slot:
 //                                                      exact, so which factor carries it is immaterial)
 //   E_R'[a', a] = sum_{s, b} T[a', s, b] phi[a, s, b]
-static int32_t inner_site_right(const tn_tensor& psi, const tn_tensor& phi, float* e_in, float* e_out, float* t,
-                                uint32_t* in_slot, uint32_t* out_slot, int32_t prec, hipStream_t st,
-                                float* sk = nullptr, size_t sk_floats = 0) {
-  SplitKScope slices(sk, sk_floats);
+static int32_t inner_plan_right(const tn_tensor& psi, const tn_tensor& phi, float* e_in, float* e_out, float* t,
+                                uint32_t* in_slot, uint32_t* out_slot, GemmDesc& g1, GemmDesc& g2) {
   const int64_t da = psi.shape[0], db = phi.shape[0], d = psi.shape[1];
   const int64_t da2 = psi.shape[2], db2 = phi.shape[2];
   tn_tensor e = make_view(e_in, TN_F32, {da2, db2});
   tn_tensor tv = make_view(t, TN_F32, {da, d, db2});
   tn_tensor eo = make_view(e_out, TN_F32, {da, db});
   const int32_t a1[1] = {2}, b1[1] = {0};
-  GemmDesc g;
-  TN_TRY(plan_gemm(psi, e, 1, a1, b1, tv, g));
-  g.a_scale_bits = in_slot;
-  TN_TRY(launch_gemm(g, prec, st));
+  TN_TRY(plan_gemm(psi, e, 1, a1, b1, tv, g1));
+  g1.a_scale_bits = in_slot;
   const int32_t a2[2] = {1, 2}, b2[2] = {1, 2};
-  TN_TRY(plan_gemm(tv, phi, 2, a2, b2, eo, g));
-  g.c_absmax = out_slot;
-  return launch_gemm(g, prec, st);
+  TN_TRY(plan_gemm(tv, phi, 2, a2, b2, eo, g2));
+  g2.c_absmax = out_slot;
+  return TN_OK;
 }
+
+static int32_t inner_launch(GemmDesc& g1, GemmDesc& g2, int32_t prec, hipStream_t st, float* sk, size_t sk_floats) {
+  SplitKScope slices(sk, sk_floats);
+  TN_TRY(launch_gemm(g1, prec, st));
+  return launch_gemm(g2, prec, st);
+}
+
+// The caller's stream and a side stream for the second end (direction) of a
+// chain.  Work of both alternates between two forms: joined, where the two
+// ends' steps share launches on the caller's stream, and forked, where each
+// end has its own stream; events order the changes.  join() before the call
+// returns puts everything on the caller's stream (capturable).
+struct TwoStreams {
+  hipStream_t st, side;
+  bool forked = false;
+  hipEvent_t ev = nullptr;
+  explicit TwoStreams(hipStream_t s) : st(s), side(s) {}
+  ~TwoStreams() {
+    if (ev) hipEventDestroy(ev);
+  }
+  int32_t order(hipStream_t before, hipStream_t after) {
+    if (!ev && hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
+      ev = nullptr;
+      return fail(TN_ERR_DEVICE, "create event failed");
+    }
+    TN_TRY(hip_check(hipEventRecord(ev, before), "record event"));
+    return hip_check(hipStreamWaitEvent(after, ev, 0), "wait event");
+  }
+  int32_t fork() {
+    if (forked) return TN_OK;
+    if (side == st) TN_TRY(side_stream(side));
+    TN_TRY(order(st, side));
+    forked = true;
+    return TN_OK;
+  }
+  int32_t join() {
+    if (!forked) return TN_OK;
+    forked = false;
+    return order(side, st);
+  }
+};
 
 // chains of at least this many sites are contracted from both ends at once
 constexpr int kInnerTwoSided = 4;
@@ -474,7 +512,11 @@ static WstepRightFn wstep_right_fn(int wl, int wr, int d, int64_t db, const void
   }
 }
 
-__global__ void fill_one_kernel(float* p) { p[0] = 1.0f; }
+// the environments outside the chain's ends (either may be null)
+__global__ void fill_one_kernel(float* l, float* r) {
+  if (threadIdx.x == 0 && l) l[0] = 1.0f;
+  if (threadIdx.x == 1 && r) r[0] = 1.0f;
+}
 
 __global__ void energy_kernel(const float* l_last, const float* r_first, double* e2) {
   if (threadIdx.x == 0) {
@@ -629,52 +671,58 @@ int32_t tn_mps_inner(int32_t n_sites, const tn_tensor* psi, const tn_tensor* phi
   float* sk = reinterpret_cast<float*>(ws + L.sk);
   float* skr = reinterpret_cast<float*>(ws + L.skr);
   if (n_sites < kInnerTwoSided) {
-    hipLaunchKernelGGL(mps_init_kernel, dim3(grid_for(n_sites + 1)), dim3(256), 0, st, e[0], slots, n_sites + 1);
+    hipLaunchKernelGGL(mps_init_kernel, dim3(grid_for(n_sites + 1)), dim3(256), 0, st, e[0], slots, n_sites + 1,
+                       nullptr, nullptr, 0);
     TN_TRY(hip_check(hipGetLastError(), "mps init"));
-    for (int k = 0; k < n_sites; ++k)
-      TN_TRY(inner_site(psi[k], phi[k], e[k & 1], e[(k + 1) & 1], t, slots, k, prec, st, sk, L.sk_floats));
+    for (int k = 0; k < n_sites; ++k) {
+      GemmDesc g1, g2;
+      TN_TRY(inner_plan(psi[k], phi[k], e[k & 1], e[(k + 1) & 1], t, slots + k, slots + k + 1, g1, g2));
+      TN_TRY(inner_launch(g1, g2, prec, st, sk, L.sk_floats));
+    }
     hipLaunchKernelGGL(mps_finish_kernel, dim3(1), dim3(256), 0, st, e[n_sites & 1], slots, n_sites, out2);
     return hip_check(hipGetLastError(), "mps finish");
   }
-  // Two-sided: sites 0 .. c-1 from the left on the caller's stream, sites
-  // n-1 .. c from the right on a side stream forked from it and joined back
-  // (capturable), issued site by site so both streams always have work.
+  // Two-sided: sites 0 .. c-1 from the left, sites n-1 .. c from the right.
   // Each half is a chain of dependent GEMMs that alone leaves most of the
-  // chip idle at chi <= 1024; the two halves overlap.
+  // chip idle at chi <= 1024.  Where a step's GEMMs have few tiles on both
+  // ends, each launch carries both ends' (the issue of a launch costs the
+  // host as long as such a GEMM runs: 100 sites of chi = 100, 982 -> 585 us);
+  // larger steps run on two streams, issued site by site so both always
+  // have work.
   const int c = n_sites / 2, nr = n_sites - c;
   float* er[2] = {reinterpret_cast<float*>(ws + L.er0), reinterpret_cast<float*>(ws + L.er1)};
   float* tr = reinterpret_cast<float*>(ws + L.tr);
   uint32_t* rslots = reinterpret_cast<uint32_t*>(ws + L.rslots);   // rslots[i]: E_R at bond n - i
   double* part = reinterpret_cast<double*>(ws + L.part);
-  hipStream_t rs = st;
-  TN_TRY(side_stream(rs));
-  hipEvent_t fork = nullptr, join = nullptr;
-  TN_TRY(hip_check(hipEventCreateWithFlags(&fork, hipEventDisableTiming), "create event"));
-  if (hipEventCreateWithFlags(&join, hipEventDisableTiming) != hipSuccess) {
-    hipEventDestroy(fork);
-    return fail(TN_ERR_DEVICE, "create event failed");
-  }
-  hipEventRecord(fork, st);
-  hipStreamWaitEvent(rs, fork, 0);
-  hipLaunchKernelGGL(mps_init_kernel, dim3(grid_for(c + 1)), dim3(256), 0, st, e[0], slots, c + 1);
-  hipLaunchKernelGGL(mps_init_kernel, dim3(grid_for(nr + 1)), dim3(256), 0, rs, er[0], rslots, nr + 1);
-  int32_t rc = hip_check(hipGetLastError(), "mps init");
-  {
-    SharedChipScope shared;
-    for (int i = 0; i < std::max(c, nr) && rc == TN_OK; ++i) {
-      if (i < c) rc = inner_site(psi[i], phi[i], e[i & 1], e[(i + 1) & 1], t, slots, i, prec, st, sk, L.sk_floats);
-      if (rc == TN_OK && i < nr) {
-        const int k = n_sites - 1 - i;
-        rc = inner_site_right(psi[k], phi[k], er[i & 1], er[(i + 1) & 1], tr, rslots + i, rslots + i + 1, prec, rs,
-                              skr, L.sk_floats);
-      }
+  hipLaunchKernelGGL(mps_init_kernel, dim3(grid_for(nr + 1), 2), dim3(256), 0, st, e[0], slots, c + 1, er[0], rslots,
+                     nr + 1);
+  TN_TRY(hip_check(hipGetLastError(), "mps init"));
+  TwoStreams two(st);
+  int32_t rc = TN_OK;
+  for (int i = 0; i < nr && rc == TN_OK; ++i) {   // nr is c or c + 1
+    const int k = n_sites - 1 - i;
+    const bool left = i < c;
+    GemmDesc l1, l2, r1, r2;
+    if (left) rc = inner_plan(psi[i], phi[i], e[i & 1], e[(i + 1) & 1], t, slots + i, slots + i + 1, l1, l2);
+    if (rc == TN_OK)
+      rc = inner_plan_right(psi[k], phi[k], er[i & 1], er[(i + 1) & 1], tr, rslots + i, rslots + i + 1, r1, r2);
+    if (rc != TN_OK) break;
+    const GemmDesc *pl1 = left ? &l1 : nullptr, *pl2 = left ? &l2 : nullptr;
+    if ((!left || (direct_chosen(l1, prec) && direct_chosen(l2, prec))) && direct_chosen(r1, prec) &&
+        direct_chosen(r2, prec) && direct_pair_ok(pl1, &r1) && direct_pair_ok(pl2, &r2)) {
+      rc = two.join();
+      if (rc == TN_OK) rc = launch_direct_pair(pl1, &r1, prec, st);
+      if (rc == TN_OK) rc = launch_direct_pair(pl2, &r2, prec, st);
+      continue;
     }
+    rc = two.fork();
+    SharedChipScope shared;
+    if (rc == TN_OK && left) rc = inner_launch(l1, l2, prec, st, sk, L.sk_floats);
+    if (rc == TN_OK) rc = inner_launch(r1, r2, prec, two.side, skr, L.sk_floats);
   }
-  hipEventRecord(join, rs);
-  hipStreamWaitEvent(st, join, 0);
-  hipEventDestroy(fork);
-  hipEventDestroy(join);
+  const int32_t joined = two.join();
   TN_TRY(rc);
+  TN_TRY(joined);
   const int64_t cnt = dp[c] * dq[c];
   const int64_t parts = std::min<int64_t>(kEnvDotParts, (cnt + 255) / 256);
   hipLaunchKernelGGL(env_dot_partial_kernel, dim3((unsigned)parts), dim3(256), 0, st, e[c & 1], er[nr & 1], cnt, part);
@@ -801,45 +849,79 @@ int32_t tn_mps_env_sweep(int32_t n_sites, const tn_tensor* psi, const tn_tensor*
     return TN_OK;
   };
 
-  // Both directions: the right sweep runs on a side stream forked from and
-  // joined back into the caller's stream (capturable), and the two are
-  // issued site by site so both streams always have work queued.
-  hipStream_t rs = st;
-  hipEvent_t fork = nullptr, join = nullptr;
-  if (which == 3) {
-    TN_TRY(side_stream(rs));
-    TN_TRY(hip_check(hipEventCreateWithFlags(&fork, hipEventDisableTiming), "create event"));
-    if (hipEventCreateWithFlags(&join, hipEventDisableTiming) != hipSuccess) {
-      hipEventDestroy(fork);
-      return fail(TN_ERR_DEVICE, "create event failed");
+  // A left site kl and a right site kr (either -1: none) as two launches on
+  // the caller's stream, each with both directions' work: the first
+  // contraction with the operator step in its epilogue, then the second
+  // contraction.  Only where every product has few tiles; false: not done.
+  // TFIM, chi = 256, 30 sites, FP32: 669 -> 444 us (the seven to ten launches
+  // of a pair of sites were issued no faster than they ran).
+  auto small_sites = [&](int kl, tn_tensor& lc, int kr, tn_tensor& rc_, hipStream_t s, bool& done,
+                         TwoStreams& two) -> int32_t {
+    done = false;
+    if (d != 2) return TN_OK;
+    GemmDesc gl, gr;
+    WstepSite sl{&lc, kl >= 0 ? &psi[kl] : nullptr, kl >= 0 ? &mpo[kl] : nullptr, t2};
+    WstepSite sr{&rc_, kr >= 0 ? &psi[kr] : nullptr, kr >= 0 ? &mpo[kr] : nullptr, t2r};
+    tn_tensor nl{}, nr{};
+    GemmDesc g;
+    const int32_t one2[1] = {2}, zero[1] = {0};
+    if (kl >= 0) {
+      const int64_t da = dims[kl], db = dims[kl + 1], wl = w[kl], wr = w[kl + 1];
+      tn_tensor T1 = make_view(t1, TN_F32, {da, wl, d, db});
+      tn_tensor T2 = make_view(t2, TN_F32, {da, d, wr, db});
+      nl = L_out ? L_out[kl + 1] : make_view(buf[(kl + 1) & 1], TN_F32, {db, wr, db});
+      TN_TRY(plan_gemm(lc, psi[kl], 1, one2, zero, T1, g));
+      if (!direct_chosen(g, prec)) return TN_OK;
+      const int32_t a3[2] = {0, 1}, b3[2] = {0, 1};
+      TN_TRY(plan_gemm(psi[kl], T2, 2, a3, b3, nl, gl));
+      if (!direct_chosen(gl, prec)) return TN_OK;
     }
-    hipEventRecord(fork, st);
-    hipStreamWaitEvent(rs, fork, 0);
-  }
-  tn_tensor lcur, rcur;
-  if (which & 1) {
-    lcur = L_out ? L_out[0] : make_view(buf[0], TN_F32, {1, 1, 1});
-    hipLaunchKernelGGL(fill_one_kernel, dim3(1), dim3(1), 0, st, static_cast<float*>(lcur.data));
-  }
-  if (which & 2) {
-    rcur = R_out ? R_out[n_sites] : make_view(rbuf[n_sites & 1], TN_F32, {1, 1, 1});
-    hipLaunchKernelGGL(fill_one_kernel, dim3(1), dim3(1), 0, rs, static_cast<float*>(rcur.data));
-  }
-  int32_t rc = TN_OK;
-  {
+    if (kr >= 0) {
+      const int64_t da = dims[kr], db = dims[kr + 1], wl = w[kr], wr = w[kr + 1];
+      tn_tensor T1 = make_view(t1r, TN_F32, {da, d, db, wr});
+      tn_tensor T2 = make_view(t2r, TN_F32, {wl, da, d, db});
+      nr = R_out ? R_out[kr] : make_view(rbuf[kr & 1], TN_F32, {da, wl, da});
+      TN_TRY(plan_gemm(psi[kr], rc_, 1, one2, one2, T1, g));
+      if (!direct_chosen(g, prec)) return TN_OK;
+      const int32_t a3[2] = {1, 2}, b3[2] = {2, 3};
+      TN_TRY(plan_gemm(psi[kr], T2, 2, a3, b3, nr, gr));
+      if (!direct_chosen(gr, prec)) return TN_OK;
+    }
+    const WstepSite *pl = kl >= 0 ? &sl : nullptr, *pr = kr >= 0 ? &sr : nullptr;
+    const GemmDesc *ql = kl >= 0 ? &gl : nullptr, *qr = kr >= 0 ? &gr : nullptr;
+    if (!direct_wstep_ok(pl, pr) || !direct_pair_ok(ql, qr)) return TN_OK;
+    TN_TRY(two.join());
+    TN_TRY(launch_direct_wstep(pl, pr, prec, s));
+    TN_TRY(launch_direct_pair(ql, qr, prec, s));
+    if (kl >= 0) lc = nl;
+    if (kr >= 0) rc_ = nr;
+    done = true;
+    return TN_OK;
+  };
+
+  // Both directions: where the products are larger the right sweep runs on a
+  // side stream forked from and joined back into the caller's stream
+  // (capturable), and the two are issued site by site so both streams always
+  // have work queued.
+  TwoStreams two(st);
+  tn_tensor lcur{}, rcur{};
+  if (which & 1) lcur = L_out ? L_out[0] : make_view(buf[0], TN_F32, {1, 1, 1});
+  if (which & 2) rcur = R_out ? R_out[n_sites] : make_view(rbuf[n_sites & 1], TN_F32, {1, 1, 1});
+  hipLaunchKernelGGL(fill_one_kernel, dim3(1), dim3(64), 0, st, static_cast<float*>(lcur.data),
+                     static_cast<float*>(rcur.data));
+  int32_t rc = hip_check(hipGetLastError(), "environment init");
+  for (int i = 0; i < n_sites && rc == TN_OK; ++i) {
+    bool done = false;
+    rc = small_sites((which & 1) ? i : -1, lcur, (which & 2) ? n_sites - 1 - i : -1, rcur, st, done, two);
+    if (rc != TN_OK || done) continue;
+    if (which == 3) rc = two.fork();
     SharedChipScope shared(which == 3);
-    for (int i = 0; i < n_sites && rc == TN_OK; ++i) {
-      if (which & 1) rc = left_site(i, lcur, st);
-      if (rc == TN_OK && (which & 2)) rc = right_site(n_sites - 1 - i, rcur, rs);
-    }
+    if (rc == TN_OK && (which & 1)) rc = left_site(i, lcur, st);
+    if (rc == TN_OK && (which & 2)) rc = right_site(n_sites - 1 - i, rcur, which == 3 ? two.side : st);
   }
-  if (which == 3) {
-    hipEventRecord(join, rs);
-    hipStreamWaitEvent(st, join, 0);
-    hipEventDestroy(fork);
-    hipEventDestroy(join);
-  }
+  const int32_t joined = two.join();
   TN_TRY(rc);
+  TN_TRY(joined);
   const float* l_last = (which & 1) ? static_cast<const float*>(lcur.data) : nullptr;
   const float* r_first = (which & 2) ? static_cast<const float*>(rcur.data) : nullptr;
   if (energy2) {

@@ -103,3 +103,49 @@ def test_infinities_stay_in_their_rows(bad):
     assert np.array_equal(np.isnan(got[33]), np.isnan(ref[33]))
     assert np.array_equal(np.isposinf(got[33]), np.isposinf(ref[33]))
     assert np.allclose(got[:33], ref[:33], rtol=0, atol=1e-4)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "split_bf16"])
+@pytest.mark.parametrize("bond", [1, 2, 3, 5, 7, 8])
+def test_fused_operator_step(prec, bond):
+    """Sweeps whose sites all run on the fused step (operator bonds with and
+    without their own kernel, ragged outer extents, the ends' other bonds),
+    both directions together and each alone."""
+    rng = np.random.default_rng(94 + bond)
+    dims = [1, 2, 4, 7, 13, 37, 33, 18, 9, 4, 2, 1]
+    n = len(dims) - 1
+    psi = [(rng.standard_normal((dims[k], 2, dims[k + 1])) / np.sqrt(dims[k] * 2)).astype(np.float32) for k in range(n)]
+    w = [1] + [bond] * (n - 1) + [1]
+    mpo = [(rng.standard_normal((w[k], w[k + 1], 2, 2)) / np.sqrt(2 * w[k])).astype(np.float32) for k in range(n)]
+    gp, gm = [gpu(x) for x in psi], [gpu(x) for x in mpo]
+    ls, rs, _, _ = oracle.env_sweep(psi, mpo)
+    for left, right in [(True, True), (True, False), (False, True)]:
+        got_l, got_r, _ = tn.mps_env_sweep(gp, gm, left=left, right=right, prec=prec)
+        torch.cuda.synchronize()
+        for got, ref in ([(got_l, ls)] if left else []) + ([(got_r, rs)] if right else []):
+            for k in range(1, n):
+                g = got[k].cpu().double().numpy()
+                assert np.linalg.norm(g - ref[k]) <= TOL[prec] * np.linalg.norm(ref[k]), (left, right, k)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "split_bf16"])
+@pytest.mark.parametrize("dims", [[1, 3, 33, 70, 21, 1], [1, 2, 4, 900, 4, 2, 1], [1, 5, 1100, 1150, 7, 1]])
+def test_inner_product_in_shared_launches(prec, dims):
+    """Steps small enough for both ends to share launches, chains of odd
+    length (the last step has one end), bonds of psi and phi that differ, and
+    steps too large for it in the middle of such a chain (the ends then run on
+    their own streams and join again)."""
+    rng = np.random.default_rng(len(dims) + dims[2])
+    n = len(dims) - 1
+    chains = []
+    for q in (0, 1):
+        dd = [1] + [x + q for x in dims[1:-1]] + [1]
+        chains.append([(rng.standard_normal((dd[k], 3, dd[k + 1])) / np.sqrt(dd[k] * 3)).astype(np.float32)
+                       for k in range(n)])
+    psi, phi = chains
+    m, s = tn.mps_inner([gpu(x) for x in psi], [gpu(x) for x in phi], prec=prec).cpu().numpy()
+    ref = oracle.mps_inner(psi, phi)
+    value = ref[0] * np.exp(ref[1])
+    norms = [v[0] * np.exp(v[1]) for v in (oracle.mps_inner(psi, psi), oracle.mps_inner(phi, phi))]
+    # relative to the Cauchy-Schwarz scale: the overlap of two random chains cancels
+    assert abs(m * np.exp(s) - value) <= TOL[prec] * np.sqrt(norms[0] * norms[1])
