@@ -66,181 +66,229 @@ typedef double f64x4_t __attribute__((ext_vector_type(4)));
 // Site tensors and pixels are read as FP32 and widened exactly.
 // ---------------------------------------------------------------------------
 // Chain kernel.  A workgroup owns 16 samples and has one wave per 16-wide
-// block of output columns (CHI / 16 waves).  Per site it forms its block of
-// the next vector with FP64 16x16x4 MFMAs, writes it to LDS unnormalised
-// together with the block's row maxima, and meets the other waves at one
-// barrier; every wave then derives each row's power-of-two normaliser from
-// the maxima and applies it while reading the vector in the next site.  For
-// CHI <= 128 the site tensor of the next site is loaded into registers
-// while the current site's MFMAs run (two register sets, sites unrolled by
-// two); CHI = 256 loads its tensor in chunks within the site.
+// block of output columns (CHI / 16 waves).  Both step types have the form
+//   out[r, n] = 2^-e(r) sum_s phi[r, s] sum_k x[r, k] W_s[k, n]
+// with x the vector as the last site left it (not normalised), so a site
+// starts its FP64 16x16x4 MFMAs right after the barrier: two products a
+// value read from LDS, the features and the normaliser 2^-e (e the binary
+// exponent of the row's largest entry, from an LDS maximum over the high
+// words) applied to the 16 x 16 block at the end, when they have long been
+// read.  The tensor of the next site is loaded into registers between the
+// current site's MFMAs (two register sets, sites unrolled by two); CHI = 256
+// loads its tensor in chunks within the site.
+//
+// Bound by the FP64 matrix cores of the compute units that have work (CHI =
+// 128: 3.4 us a site).  Measured, 28 sites: CHI = 128, 1024 samples, four
+// runs 241 -> 167 us; CHI = 64, 4096 samples, two runs 128 -> 95 us.
 template <int CHI>
 struct ChainSmem {
   static constexpr int NW = CHI / 16;
   double vec[2][kRB][CHI + 2];
   double phi[kMaxSeg][kRB][2];
-  double pmax[2][NW][kRB];
-  const float* w[kMaxSeg];
-  int din[kMaxSeg], dout[kMaxSeg];
+  uint32_t pmax[3][kRB];      // high words of the rows' largest |entry|, sites in turn
 };
 
-template <int CHI, int TYPE>
+__device__ __forceinline__ f32x4c_t chain_load4(const float* p) {
+  typedef float f32x4cu_t __attribute__((ext_vector_type(4), aligned(4)));
+  return *reinterpret_cast<const f32x4cu_t*>(p);
+}
+
+// Lane group g takes k = 16 j + 4 g + q (q < 4) of every sixteen: its x are 16-byte
+// LDS reads, and a row of W read along k is covered in 64-byte runs by the
+// four groups.  w[s][4 j + q]: W_s[16 j + 4 g + q, column] of one site.
+template <int CHI>
 struct ChainRegs {
-  // site-tensor registers of one site for the lane's column block
   static constexpr bool PREFETCH = CHI <= 128;
-  static constexpr int KI0 = CHI / 2;        // type 0: MFMA steps (k = 2a + s in groups of 4)
-  static constexpr int NV1 = CHI / 16;       // type 1: float4 per row slice (z in groups of 4 per lane)
-  float w0[TYPE == 0 && PREFETCH ? KI0 : 1];
-  f32x4c_t wa[TYPE == 1 && PREFETCH ? NV1 : 1], wb[TYPE == 1 && PREFETCH ? NV1 : 1];
+  static constexpr int N = PREFETCH ? CHI / 4 : 4;   // k a set holds
+  float w[2][N];
 };
 
+// Sixteen k of a site tensor with both bonds CHI into w[.][at .. at + 3]:
+// TYPE 0 W[k, s, col], TYPE 1 W[col, s, k].  The lane's offset is a vector
+// register, j's a scalar one.
 template <int CHI, int TYPE>
-__device__ __forceinline__ void chain_load(ChainRegs<CHI, TYPE>& R, const float* W, int col, int g) {
-  if constexpr (ChainRegs<CHI, TYPE>::PREFETCH) {
-    if constexpr (TYPE == 0) {
+__device__ __forceinline__ void chain_load16(ChainRegs<CHI>& R, int at, __amdgpu_buffer_rsrc_t rs, const float* W, int col,
+                                             int g, int j) {
+  if constexpr (TYPE == 0) {
+    const uint32_t lane = (uint32_t)(8 * g * CHI + col) * 4u;
 #pragma unroll
-      for (int kk = 0; kk < CHI / 2; ++kk) R.w0[kk] = W[(int64_t)(4 * kk + g) * CHI + col];
-    } else {
-      const float* r0 = W + ((int64_t)col * 2) * CHI + g * (CHI / 4);
+    for (int q = 0; q < 4; ++q)
 #pragma unroll
-      for (int j = 0; j < CHI / 16; ++j) {
-        R.wa[j] = *reinterpret_cast<const f32x4c_t*>(r0 + 4 * j);
-        R.wb[j] = *reinterpret_cast<const f32x4c_t*>(r0 + CHI + 4 * j);
+      for (int s = 0; s < 2; ++s)
+        R.w[s][at + q] = __builtin_bit_cast(
+            float, __builtin_amdgcn_raw_buffer_load_b32(rs, lane, (2 * (16 * j + q) + s) * CHI * 4, 0));
+  } else {
+    const uint32_t lane = (uint32_t)(2 * col * CHI + 4 * g);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const f32x4c_t y = chain_load4(W + s * CHI + 16 * j + lane);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) R.w[s][at + q] = y[q];
+    }
+  }
+}
+
+// the same from a tensor of smaller bonds (the chain's ends, bonds below the
+// padded CHI): zero beyond din in k; columns past dout repeat the last one
+// and are cleared by the caller
+template <int CHI, int TYPE>
+__device__ __forceinline__ void chain_load16_part(ChainRegs<CHI>& R, int at, const float* W, int din, int dout, int col,
+                                                  int g, int j) {
+  const int c = min(col, dout - 1);
+  const int64_t ks = TYPE == 0 ? 2 * (int64_t)dout : 1, ss = TYPE == 0 ? dout : din;
+  const float* base = W + (TYPE == 0 ? (int64_t)c : 2 * (int64_t)c * din);
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int s = 0; s < 2; ++s) R.w[s][at + q] = base[min(16 * j + 4 * g + q, din - 1) * ks + s * ss];
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int s = 0; s < 2; ++s) R.w[s][at + q] = 16 * j + 4 * g + q < din ? R.w[s][at + q] : 0.f;
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t chain_rsrc(const float* p) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), (short)0, (int)0xffffffff, 0x00020000);
+}
+
+// binary exponent of a row from the high word of its largest entry (0 for a
+// zero, denormal or overflowing row, which is left as it is)
+__device__ __forceinline__ int chain_exp(uint32_t hi) {
+  return hi >= 0x00100000u && hi < 0x7e37e43cu ? (int)(hi >> 20) - 1023 : 0;
+}
+__device__ __forceinline__ double chain_pow2(int e) { return __longlong_as_double((long long)(1023 + e) << 52); }
+
+// maximum over the 16 lanes of a DPP row
+template <int CTRL>
+__device__ __forceinline__ uint32_t chain_dpp(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, false);
+}
+__device__ __forceinline__ uint32_t chain_rowmax(uint32_t x) {
+  x = max(x, chain_dpp<0x128>(x));   // row_ror 8, 4, 2, 1
+  x = max(x, chain_dpp<0x124>(x));
+  x = max(x, chain_dpp<0x122>(x));
+  return max(x, chain_dpp<0x121>(x));
+}
+
+// The products of one site.  LOAD: the next site's tensor (both bonds CHI)
+// goes into `into` meanwhile, sixteen k with each sixteen k of products: all
+// loads first would hold the matrix cores until they are issued.
+template <int CHI, int TYPE, bool LOAD>
+__device__ __forceinline__ void chain_products(const ChainRegs<CHI>& R, ChainRegs<CHI>& into, const float* Wn,
+                                               const double* x, int col, int g, f64x4_t& acc0, f64x4_t& acc1) {
+  constexpr int NJ = CHI / 16;
+  typedef double f64x2_t __attribute__((ext_vector_type(2)));
+  __amdgpu_buffer_rsrc_t rs;
+  if constexpr (LOAD && TYPE == 0) rs = chain_rsrc(Wn);
+  f64x2_t xr[3][2];   // two sixteens ahead
+#pragma unroll
+  for (int j = 0; j < 2 && j < NJ; ++j)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) xr[j][h] = *reinterpret_cast<const f64x2_t*>(x + 16 * j + 2 * h);
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    if (j + 2 < NJ) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) xr[(j + 2) % 3][h] = *reinterpret_cast<const f64x2_t*>(x + 16 * (j + 2) + 2 * h);
+    }
+    if constexpr (LOAD) chain_load16<CHI, TYPE>(into, 4 * j, rs, Wn, col, g, j);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const double xv = xr[j % 3][q >> 1][q & 1];
+      acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(xv, (double)R.w[0][4 * j + q], acc0, 0, 0, 0);
+      acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(xv, (double)R.w[1][4 * j + q], acc1, 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// CHI = 256: the site's own tensor, sixteen k ahead of the products
+template <int CHI, int TYPE>
+__device__ __forceinline__ void chain_products_inline(ChainRegs<CHI> (&regs)[2], const float* W, int din, int dout,
+                                                      const double* x, int col, int g, f64x4_t& acc0, f64x4_t& acc1) {
+  constexpr int NJ = CHI / 16;
+  typedef double f64x2_t __attribute__((ext_vector_type(2)));
+  const bool full = din == CHI && dout == CHI;
+  const __amdgpu_buffer_rsrc_t rs = chain_rsrc(W);
+  auto load = [&](ChainRegs<CHI>& R, int j) {
+    if (full) chain_load16<CHI, TYPE>(R, 0, rs, W, col, g, j);
+    else chain_load16_part<CHI, TYPE>(R, 0, W, din, dout, col, g, j);
+  };
+  load(regs[0], 0);
+#pragma unroll 1
+  for (int j0 = 0; j0 < NJ; j0 += 2) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int j = j0 + u;
+      f64x2_t xr[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) xr[h] = *reinterpret_cast<const f64x2_t*>(x + 16 * j + 2 * h);
+      if (j + 1 < NJ) load(regs[u ^ 1], j + 1);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const double xv = xr[q >> 1][q & 1];
+        acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(xv, (double)regs[u].w[0][q], acc0, 0, 0, 0);
+        acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(xv, (double)regs[u].w[1][q], acc1, 0, 0, 0);
       }
     }
   }
 }
 
+// ex: exponents of the lane's rows 4 r + g
 template <int CHI, int TYPE, int SET>
-__device__ __forceinline__ void chain_step(const ChainArgs& a, ChainSmem<CHI>& sm, ChainRegs<CHI, TYPE> (&regs)[2],
-                                           int st, int& cur, double& scl, int& ex, int b0) {
-  constexpr int NW = CHI / 16;
+__device__ __forceinline__ void chain_step(const ChainArgs& a, ChainSmem<CHI>& sm, ChainRegs<CHI> (&regs)[2], int st,
+                                           int (&ex)[4], int b0) {
+  constexpr bool PRE = ChainRegs<CHI>::PREFETCH;
+  typedef double f64x2_t __attribute__((ext_vector_type(2)));
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int row = lane & 15, g = lane >> 4;
   const int col = wave * 16 + row;          // this lane's output column (type 0: z, type 1: a)
-  const int din = sm.din[st], dout = sm.dout[st];
-  const float* W = sm.w[st];
-  const bool fast = din == CHI && dout == CHI && (TYPE == 0 || (reinterpret_cast<uintptr_t>(W) & 15) == 0);
-  const int nxt = cur ^ 1, par = st & 1;
-  // prefetch the next site's tensor into the other register set
-  if constexpr (ChainRegs<CHI, TYPE>::PREFETCH) {
-    if (st + 1 < a.n_steps) {
-      const float* Wn = sm.w[st + 1];
-      if (sm.din[st + 1] == CHI && sm.dout[st + 1] == CHI &&
-          (TYPE == 0 || (reinterpret_cast<uintptr_t>(Wn) & 15) == 0))
-        chain_load<CHI, TYPE>(regs[SET ^ 1], Wn, col, g);
-    }
+  // bonds: the chain's ends are 1
+  auto site = [&](int j) { return a.first_site + a.dir * j; };
+  auto left = [&](int j) { return site(j) == 0 ? 1 : a.chi; };
+  auto right = [&](int j) { return site(j) == a.n_sites - 1 ? 1 : a.chi; };
+  auto din_of = [&](int j) { return TYPE == 0 ? left(j) : right(j); };
+  auto dout_of = [&](int j) { return TYPE == 0 ? right(j) : left(j); };
+  const int dout = dout_of(st);
+  const double* x = &sm.vec[st & 1][row][4 * g];
+  // the input's exponents (site st - 1 left them) and the features of the output rows
+  uint32_t hi[4];
+  f64x2_t ph[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    hi[r] = sm.pmax[(st + 2) % 3][4 * r + g];
+    ph[r] = *reinterpret_cast<const f64x2_t*>(&sm.phi[st][4 * r + g][0]);
   }
+  if (tid < kRB) sm.pmax[(st + 1) % 3][tid] = 0;   // site st + 1's, last read by site st - 1
   f64x4_t acc0 = {0.0, 0.0, 0.0, 0.0}, acc1 = acc0;
-  if (TYPE == 0) {
-    // out[r, z] = sum_{a, s} x[r, a] phi[r, s] W[(a s), z]   (k = 2a + s)
-    const double p0 = sm.phi[st][row][0] * scl, p1 = sm.phi[st][row][1] * scl;
-    if (fast && ChainRegs<CHI, TYPE>::PREFETCH) {
+  if constexpr (PRE) {
+    const bool more = st + 1 < a.n_steps;
+    if (more && din_of(st + 1) == CHI && dout_of(st + 1) == CHI) {
+      chain_products<CHI, TYPE, true>(regs[SET], regs[SET ^ 1], a.w[st + 1], x, col, g, acc0, acc1);
+    } else {
+      if (more)
 #pragma unroll
-      for (int kk = 0; kk < CHI / 2; ++kk) {
-        const int k = 4 * kk + g;
-        const double xv = sm.vec[cur][row][k >> 1] * ((k & 1) ? p1 : p0);
-        acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(xv, (double)regs[SET].w0[kk], acc0, 0, 0, 0);
-      }
-    } else if (fast) {
-      constexpr int CH = 16;
-      for (int k0 = 0; k0 < CHI / 2; k0 += CH) {
-        float wv[CH];
-#pragma unroll
-        for (int q = 0; q < CH; ++q) wv[q] = W[(int64_t)(4 * (k0 + q) + g) * CHI + col];
-#pragma unroll
-        for (int q = 0; q < CH; ++q) {
-          const int k = 4 * (k0 + q) + g;
-          const double xv = sm.vec[cur][row][k >> 1] * ((k & 1) ? p1 : p0);
-          acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(xv, (double)wv[q], acc0, 0, 0, 0);
-        }
-      }
-    } else if (col - row < dout) {
-      const int K4 = (2 * din + 3) >> 2;
-      for (int kk = 0; kk < K4; ++kk) {
-        const int k = 4 * kk + g, aa = k >> 1;
-        double xv = 0.0, wv = 0.0;
-        if (aa < din) {
-          xv = sm.vec[cur][row][aa] * ((k & 1) ? p1 : p0);
-          if (col < dout) wv = (double)W[(int64_t)k * dout + col];
-        }
-        acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(xv, wv, acc0, 0, 0, 0);
-      }
+        for (int j = 0; j < CHI / 16; ++j)
+          chain_load16_part<CHI, TYPE>(regs[SET ^ 1], 4 * j, a.w[st + 1], din_of(st + 1), dout_of(st + 1), col, g, j);
+      chain_products<CHI, TYPE, false>(regs[SET], regs[SET ^ 1], nullptr, x, col, g, acc0, acc1);
     }
   } else {
-    // out[r, a] = sum_s phi[r, s] sum_z x[r, z] W[a, s, z]
-    if (fast && ChainRegs<CHI, TYPE>::PREFETCH) {
-      constexpr int KI = CHI / 4;
-#pragma unroll
-      for (int kk = 0; kk < KI; ++kk) {
-        const double xv = sm.vec[cur][row][g * KI + kk] * scl;
-        acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(xv, (double)regs[SET].wa[kk >> 2][kk & 3], acc0, 0, 0, 0);
-        acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(xv, (double)regs[SET].wb[kk >> 2][kk & 3], acc1, 0, 0, 0);
-      }
-    } else if (fast) {
-      constexpr int KI = CHI / 4;
-      const float* r0 = W + ((int64_t)col * 2) * CHI + g * KI;
-      constexpr int CH = 4;    // float4 per chunk (16 z values of the lane's slice)
-      for (int j0 = 0; j0 < KI / 4; j0 += CH) {
-        f32x4c_t wa[CH], wb[CH];
-#pragma unroll
-        for (int j = 0; j < CH; ++j) {
-          wa[j] = *reinterpret_cast<const f32x4c_t*>(r0 + 4 * (j0 + j));
-          wb[j] = *reinterpret_cast<const f32x4c_t*>(r0 + CHI + 4 * (j0 + j));
-        }
-#pragma unroll
-        for (int kk = 0; kk < 4 * CH; ++kk) {
-          const double xv = sm.vec[cur][row][g * KI + 4 * j0 + kk] * scl;
-          acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(xv, (double)wa[kk >> 2][kk & 3], acc0, 0, 0, 0);
-          acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(xv, (double)wb[kk >> 2][kk & 3], acc1, 0, 0, 0);
-        }
-      }
-    } else if (col - row < dout) {
-      const int K4 = (din + 3) >> 2;
-      for (int kk = 0; kk < K4; ++kk) {
-        const int z = 4 * kk + g;
-        double xv = 0.0, w0 = 0.0, w1 = 0.0;
-        if (z < din) {
-          xv = sm.vec[cur][row][z] * scl;
-          if (col < dout) {
-            w0 = (double)W[((int64_t)col * 2 + 0) * din + z];
-            w1 = (double)W[((int64_t)col * 2 + 1) * din + z];
-          }
-        }
-        acc0 = __builtin_amdgcn_mfma_f64_16x16x4f64(xv, w0, acc0, 0, 0, 0);
-        acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64(xv, w1, acc1, 0, 0, 0);
-      }
-    }
+    chain_products_inline<CHI, TYPE>(regs, a.w[st], din_of(st), dout, x, col, g, acc0, acc1);
   }
   // FP64 16x16x4 result: lane (col + 16 g) register r holds row 4 r + g
   double outv[4];
-  double m[4];
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int rr = r * 4 + g;
-    double v = TYPE == 0 ? acc0[r] : sm.phi[st][rr][0] * acc0[r] + sm.phi[st][rr][1] * acc1[r];
+    const int e = chain_exp(hi[r]);
+    double v = (ph[r][0] * acc0[r] + ph[r][1] * acc1[r]) * chain_pow2(-e);
     if (col >= dout) v = 0.0;
+    ex[r] += e;
     outv[r] = v;
-    sm.vec[nxt][rr][col] = v;
-    m[r] = fabs(v);
-  }
-#pragma unroll
-  for (int o = 8; o >= 1; o >>= 1)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) m[r] = fmax(m[r], __shfl_xor(m[r], o, 16));
-  if (row == 0) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) sm.pmax[par][wave][r * 4 + g] = m[r];
+    sm.vec[(st + 1) & 1][4 * r + g][col] = v;
+    const uint32_t m = chain_rowmax((uint32_t)(__double_as_longlong(v) >> 32) & 0x7fffffffu);
+    if (row == 0) atomicMax(&sm.pmax[st % 3][4 * r + g], m);
   }
   __syncthreads();
-  // the row normaliser 2^-e (e the binary exponent of the row maximum)
-  auto row_exp = [&](int rr) {
-    double mm = 0.0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) mm = fmax(mm, sm.pmax[par][w][rr]);
-    return (mm > 0.0 && mm < 1e300) ? ilogb(mm) : 0;
-  };
-  const int e = row_exp(row);
   // a stored block holds this site's output (the next site's input), normalised
   float* dst = nullptr;     // vectors of the block to write
   float* dste = nullptr;    // its exponents
@@ -257,47 +305,34 @@ __device__ __forceinline__ void chain_step(const ChainArgs& a, ChainSmem<CHI>& s
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int rr = r * 4 + g, b = b0 + rr;
-      const int er = row_exp(rr);
+      const int e = chain_exp(sm.pmax[st % 3][rr]);
       if (b < a.B) {
-        const double x = ldexp(outv[r], -er);
-        const float hi = (float)x;
-        dst[(int64_t)b * CHI + col] = hi;
-        if (dstl) dstl[(int64_t)b * CHI + col] = (float)(x - (double)hi);
+        const double v = outv[r] * chain_pow2(-e);
+        const float hi32 = (float)v;
+        dst[(int64_t)b * CHI + col] = hi32;
+        if (dstl) dstl[(int64_t)b * CHI + col] = (float)(v - (double)hi32);
+        if (col == 0) dste[b] = (float)(ex[r] + e);
       }
     }
-    if (wave == 0 && g == 0 && b0 + row < a.B) dste[b0 + row] = (float)(ex + e);
   }
-  ex += e;
-  scl = ldexp(1.0, -e);
-  cur = nxt;
 }
 
 template <int CHI, int TYPE>
 __device__ __forceinline__ void chain_run(const ChainArgs& a, ChainSmem<CHI>& sm) {
   constexpr int NT = CHI / 16 * 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int row = lane & 15, g = lane >> 4;
+  const int row = lane & 15, g = lane >> 4, col = wave * 16 + row;
   const int b0 = blockIdx.x * kRB;
   if (b0 >= a.B) return;
-  if (tid == 0) {
-#pragma unroll
-    for (int j = 0; j < kMaxSeg; ++j)
-      if (j < a.n_steps) {
-        const int k = a.first_site + a.dir * j;
-        const int dl = k == 0 ? 1 : a.chi, dr = k == a.n_sites - 1 ? 1 : a.chi;
-        sm.w[j] = a.w[j];
-        sm.din[j] = TYPE == 0 ? dl : dr;
-        sm.dout[j] = TYPE == 0 ? dr : dl;
-      }
-  }
   // feature map of every site of the run
-  for (int e = tid; e < a.n_steps * kRB * 2; e += NT) {
-    const int st = e / (2 * kRB), r = (e >> 1) % kRB, sc = e & 1, b = b0 + r;
+  for (int e = tid; e < a.n_steps * kRB; e += NT) {
+    const int st = e / kRB, r = e % kRB, b = b0 + r;
     const int k = a.first_site + a.dir * st;
     const double p = b < a.B ? (double)a.pixels[(int64_t)b * a.n_sites + k] : 0.0;
     double sv, cv;
     sincospi(0.5 * p, &sv, &cv);
-    sm.phi[st][r][sc] = sc == 0 ? cv : sv;
+    sm.phi[st][r][0] = cv;
+    sm.phi[st][r][1] = sv;
   }
   for (int e = tid; e < kRB * CHI; e += NT) {
     const int r = e / CHI, i = e % CHI, b = b0 + r;
@@ -312,54 +347,46 @@ __device__ __forceinline__ void chain_run(const ChainArgs& a, ChainSmem<CHI>& sm
     }
     sm.vec[0][r][i] = x;
   }
-  int ex = (a.v_in && b0 + row < a.B) ? (int)a.v_in[(int64_t)a.B * CHI + b0 + row] : 0;
-  double scl = 1.0;
-  // the first site's input, stored as given
-  if (a.store) {
-    const int col = wave * 16 + row;
-    for (int r = g; r < kRB; r += 4) {
-      const int b = b0 + r;
-      if (b < a.B) {
-        const double x = a.v_in ? (double)a.v_in[(int64_t)b * CHI + col] : (col == 0 ? 1.0 : 0.0);
-        a.store[(int64_t)b * CHI + col] = (float)x;
-      }
+  // the first site's input is taken as given: no normaliser
+  if (tid < 3 * kRB) (&sm.pmax[0][0])[tid] = 0;
+  int ex[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int b = b0 + 4 * r + g;
+    ex[r] = (a.v_in && b < a.B) ? (int)a.v_in[(int64_t)a.B * CHI + b] : 0;
+    // and stored so
+    if (a.store && b < a.B) {
+      const float x = a.v_in ? a.v_in[(int64_t)b * CHI + col] : (col == 0 ? 1.f : 0.f);
+      a.store[(int64_t)b * CHI + col] = x;
+      if (col == 0) a.store[a.store_exp + b] = (float)ex[r];
     }
-    if (wave == 0 && g == 0 && b0 + row < a.B) a.store[a.store_exp + b0 + row] = (float)ex;
   }
-  ChainRegs<CHI, TYPE> regs[2];
+  ChainRegs<CHI> regs[2];
   __syncthreads();
-  if constexpr (ChainRegs<CHI, TYPE>::PREFETCH) {
-    if (sm.din[0] == CHI && sm.dout[0] == CHI && (TYPE == 0 || (reinterpret_cast<uintptr_t>(sm.w[0]) & 15) == 0))
-      chain_load<CHI, TYPE>(regs[0], sm.w[0], wave * 16 + row, g);
+  if constexpr (ChainRegs<CHI>::PREFETCH) {
+    const int k = a.first_site, dl = k == 0 ? 1 : a.chi, dr = k == a.n_sites - 1 ? 1 : a.chi;
+#pragma unroll
+    for (int j = 0; j < CHI / 16; ++j)
+      chain_load16_part<CHI, TYPE>(regs[0], 4 * j, a.w[0], TYPE == 0 ? dl : dr, TYPE == 0 ? dr : dl, col, g, j);
   }
-  int cur = 0;
   for (int st = 0; st < a.n_steps; st += 2) {
-    chain_step<CHI, TYPE, 0>(a, sm, regs, st, cur, scl, ex, b0);
-    if (st + 1 < a.n_steps) chain_step<CHI, TYPE, 1>(a, sm, regs, st + 1, cur, scl, ex, b0);
+    chain_step<CHI, TYPE, 0>(a, sm, regs, st, ex, b0);
+    if (st + 1 < a.n_steps) chain_step<CHI, TYPE, 1>(a, sm, regs, st + 1, ex, b0);
   }
   // a run of zero sites (never launched) would leave v_out unwritten
 }
 
 // blockIdx.y selects one of up to four independent runs (left and right
 // chains, recomputation and adjoint) advancing in one launch
+struct ChainRuns {
+  ChainArgs a[4];
+};
 template <int CHI>
-__global__ void __launch_bounds__(CHI / 16 * 64)
-    chain_kernel(const ChainArgs a0, const ChainArgs a1, const ChainArgs a2, const ChainArgs a3) {
-  __shared__ ChainSmem<CHI> sm;
-  switch (blockIdx.y) {
-    case 0:
-      if (a0.step_type == 0) chain_run<CHI, 0>(a0, sm); else chain_run<CHI, 1>(a0, sm);
-      break;
-    case 1:
-      if (a1.step_type == 0) chain_run<CHI, 0>(a1, sm); else chain_run<CHI, 1>(a1, sm);
-      break;
-    case 2:
-      if (a2.step_type == 0) chain_run<CHI, 0>(a2, sm); else chain_run<CHI, 1>(a2, sm);
-      break;
-    default:
-      if (a3.step_type == 0) chain_run<CHI, 0>(a3, sm); else chain_run<CHI, 1>(a3, sm);
-      break;
-  }
+__global__ void __launch_bounds__(CHI / 16 * 64) chain_kernel(const ChainRuns runs) {
+  __shared__ __attribute__((aligned(16))) ChainSmem<CHI> sm;
+  const ChainArgs& a = runs.a[blockIdx.y];
+  if (a.step_type == 0) chain_run<CHI, 0>(a, sm);
+  else chain_run<CHI, 1>(a, sm);
 }
 
 // X[b, a, s] = v[b, a] * Phi_s(x_{b, site}) * (with_scale ? 2^(e_v[b] + e_w[b]) : 1)
@@ -669,20 +696,23 @@ ChainArgs chain_args(const Geometry& g, const tn_tensor* sites, const float* pix
 
 // up to four independent runs in one launch
 int32_t launch_chains(const Geometry& g, const std::vector<ChainArgs>& runs, hipStream_t st) {
-  std::vector<ChainArgs> r;
+  ChainRuns r;
+  int n = 0;
   for (const ChainArgs& a : runs)
-    if (a.n_steps > 0) r.push_back(a);
-  if (r.empty()) return TN_OK;
-  if (r.size() > 4) return fail(TN_ERR_INVALID_ARGUMENT, "at most four chain runs per launch");
-  const dim3 grid((unsigned)((g.B + kRB - 1) / kRB), (unsigned)r.size());
-  while (r.size() < 4) r.push_back(r[0]);
+    if (a.n_steps > 0) {
+      if (n == 4) return fail(TN_ERR_INVALID_ARGUMENT, "at most four chain runs per launch");
+      r.a[n++] = a;
+    }
+  if (n == 0) return TN_OK;
+  const dim3 grid((unsigned)((g.B + kRB - 1) / kRB), (unsigned)n);
+  for (int i = n; i < 4; ++i) r.a[i] = r.a[0];
   // one wave per 16 output columns
   switch (g.pad_chi) {
-    case 16: hipLaunchKernelGGL(chain_kernel<16>, grid, dim3(64), 0, st, r[0], r[1], r[2], r[3]); break;
-    case 32: hipLaunchKernelGGL(chain_kernel<32>, grid, dim3(128), 0, st, r[0], r[1], r[2], r[3]); break;
-    case 64: hipLaunchKernelGGL(chain_kernel<64>, grid, dim3(256), 0, st, r[0], r[1], r[2], r[3]); break;
-    case 128: hipLaunchKernelGGL(chain_kernel<128>, grid, dim3(512), 0, st, r[0], r[1], r[2], r[3]); break;
-    default: hipLaunchKernelGGL(chain_kernel<256>, grid, dim3(1024), 0, st, r[0], r[1], r[2], r[3]); break;
+    case 16: hipLaunchKernelGGL(chain_kernel<16>, grid, dim3(64), 0, st, r); break;
+    case 32: hipLaunchKernelGGL(chain_kernel<32>, grid, dim3(128), 0, st, r); break;
+    case 64: hipLaunchKernelGGL(chain_kernel<64>, grid, dim3(256), 0, st, r); break;
+    case 128: hipLaunchKernelGGL(chain_kernel<128>, grid, dim3(512), 0, st, r); break;
+    default: hipLaunchKernelGGL(chain_kernel<256>, grid, dim3(1024), 0, st, r); break;
   }
   return hip_check(hipGetLastError(), "chain kernel");
 }

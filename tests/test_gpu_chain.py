@@ -1,0 +1,52 @@
+"""The classifier's chain and gradient kernels at the sizes where they can go
+wrong: bonds off and on the padded extents (16, 32, 64, 128, 256), the chain's
+ends inside and at the edges of a segment, one sample and partial blocks of
+samples, segments of one site.  Gates of test_gpu_classifier.py: scores 1e-5
+per sample, gradients 1e-4 relative of the FP64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1905_01330_amd as tn
+from paper_1905_01330_amd import inputs
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+
+
+def run(n, chi, labels, c, batch, every, prec, seed):
+    sites = [s.astype(np.float32).astype(np.float64) for s in inputs.classifier_sites(n, chi, labels, c, seed)]
+    pix = inputs.images(batch, n, seed + 1).astype(np.float32).astype(np.float64)
+    lab = inputs.labels(batch, labels, seed + 2)
+    gs = [torch.tensor(s, dtype=torch.float32, device=DEV) for s in sites]
+    gp = torch.tensor(pix, dtype=torch.float32, device=DEV)
+    model = tn.MPSClassifier(n, c, labels, chi, batch, ckpt_every=every, prec=prec)
+    logits = model.forward(gs, gp)
+    ref = oracle.classifier_forward(sites, c, pix)
+    got = logits.cpu().double().numpy()
+    assert np.max(np.linalg.norm(got - ref, axis=1) / np.linalg.norm(ref, axis=1)) <= 1e-5
+    _, dlog = tn.softmax_xent(logits, torch.tensor(lab, device=DEV))
+    dsites = model.backward(gs, gp, dlog)
+    torch.cuda.synchronize()
+    _, grads = oracle.classifier_loss_and_grad(sites, c, pix, lab)
+    for k, (d, r) in enumerate(zip(dsites, grads)):
+        d = d.cpu().double().numpy()
+        assert np.linalg.norm(d - r) <= 1e-4 * np.linalg.norm(r) + 1e-30, (k, np.linalg.norm(d - r) / np.linalg.norm(r))
+
+
+@pytest.mark.parametrize("chi", [1, 5, 16, 17, 33, 64, 100, 128, 129, 256])
+def test_bonds(chi):
+    run(9, chi, 3, 4, 19, 3, "fp32", 100 + chi)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "split_bf16"])
+@pytest.mark.parametrize("batch", [1, 7, 16, 63, 64, 129, 1024, 1031])
+def test_batches(batch, prec):
+    run(6, 24, 4, 2, batch, 2, prec, 200 + batch)
+
+
+@pytest.mark.parametrize("shape", [(3, 1, 1), (8, 1, 64), (8, 6, 1), (70, 35, 64), (66, 1, 64)])
+def test_segments(shape):
+    n, c, every = shape
+    run(n, 20, 2, c, 5, every, "fp32", 300 + n)
