@@ -13,13 +13,14 @@
 // kept as integers).  Up to four independent runs share one launch.  The
 // forward stores a vector every `ckpt_every` sites; the backward recomputes
 // each segment from its checkpoint while carrying the adjoint through it
-// with the mirrored step, then forms the segment's weight gradients as one
-// batched batch-reduction GEMM on the contraction kernel.
+// with the mirrored step, then forms the segment's weight gradients (sums over
+// the batch) of both sides in one launch.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <vector>
 
+#include "gemm_direct_kernel.h"
 #include "internal.h"
 
 namespace tn {
@@ -408,64 +409,208 @@ __global__ void expand_kernel(const float* vblk, const float* wblk_exp, const fl
   }
 }
 
-// One segment of gradient operands at once.  A segment buffer holds E
+// Weight gradients of one segment per chain side.  A segment buffer holds E
 // vector slots of B x pc floats followed by E x B exponents (at + eoff).
-// Batch entry j is site k_j = k0 - j:
-//   X_j[b, a, s] = V_j[b, a] Phi_s(x_{b, k_j}) 2^(e_V(b) + e_G(b))
-// with V_j in slot n-1-j of vsrc and e_G the exponents of slot j of gsrc
-// (the GEMM's other operand).  a runs over chi.
-__global__ void expand_seg_kernel(const float* vsrc, const float* gsrc, int64_t eoff, int n, int k0,
-                                  const float* pixels, int n_pix, int B, int pc, int chi, float* x) {
-  const int j = blockIdx.y;
-  const float* v = vsrc + (int64_t)(n - 1 - j) * B * pc;
-  const float* ve = vsrc + eoff + (int64_t)(n - 1 - j) * B;
-  const float* ge = gsrc + eoff + (int64_t)j * B;
-  const int k = k0 - j;
-  float* xj = x + (int64_t)j * B * chi * 2;
-  const int64_t total = (int64_t)B * chi * 2;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int s = (int)(e & 1);
-    const int64_t ba = e >> 1;
-    const int b = (int)(ba / chi), aa = (int)(ba % chi);
-    float sv, cv;
-    sincospif(0.5f * pixels[(int64_t)b * n_pix + k], &sv, &cv);
-    const int ex = (int)ve[b] + (int)ge[b];
-    xj[e] = ldexpf(v[(int64_t)b * pc + aa] * (s == 0 ? cv : sv), ex);
-  }
-}
+// Site k_j = k0 - j:
+//   dA_{k_j}[a, s, z] = sum_b (V_j[b, a] Phi_s(x_{b, k_j}) 2^(e_V(b) + e_G(b))) G_j[b, z]
+// with V_j in slot n - 1 - j of v and G_j in slot j of g.
+//
+// A workgroup owns 32 a (both s) by 64 z of one site and cuts the samples
+// over its eight waves, each reading its samples' V and G rows straight into
+// the operand registers (lanes along a and z) and forming the two features'
+// products with V there: the expanded operand, twice V, never reaches memory,
+// and the sums go straight into the caller's gradient tensors.  The features
+// and exponents of a site are computed once a workgroup, kGradSamples at a
+// time.  Bound by the FP32 matrix cores (chi = 128, 1024 samples, 56 sites:
+// 3.8e9 flops, 24 us).  Measured, that launch: 49 us; the expanded operand, a
+// batched GEMM and the scatter of its blocks took 164 us.
+constexpr int kGradSamples = 1024;   // samples whose features are in LDS at a time
 
-struct ScatterArgs {
+struct GradSide {
+  const float* v;
+  const float* g;
+  int n, k0;
+};
+struct GradArgs {
+  GradSide side[2];
+  int first;                  // entry of this launch's first (entries: side 0's sites, then side 1's)
   float* dst[kMaxSeg];
-  int64_t st[kMaxSeg][3];
+  int64_t st[kMaxSeg][3];     // their strides
+  int64_t eoff;
+  const float* pixels;
+  int n_pix, B, pc, chi, tiles_a;
 };
 
-// dA_{k_j}[a, s, z] = sum_c G_{j,c}[a, s, z] (the S batch chunks, summed in
-// a fixed order) for a < d_left(k_j), z < d_right(k_j)
-__global__ void scatter_grad_kernel(const float* gbuf, int n, int S, int k0, int n_sites, int chi, const ScatterArgs sa) {
-  const int j = blockIdx.y;
-  const int k = k0 - j;
-  const int dl = k == 0 ? 1 : chi, dr = k == n_sites - 1 ? 1 : chi;
-  const int64_t blk = (int64_t)chi * 2 * chi;
-  const float* src = gbuf + (int64_t)j * S * blk;
-  float* dst = nullptr;
-  int64_t s0 = 0, s1 = 0, s2 = 0;
+template <int P>
+__global__ void __launch_bounds__(kDirectWaves * 64) __attribute__((amdgpu_waves_per_eu(2)))
+    segment_grad_kernel(const GradArgs ga) {
+  constexpr int CH = DirectInfo<P>::CH, NQ = DirectInfo<P>::NQ;
+  constexpr int U = PrecInfo<P>::bf ? 2 : 4;   // chunks in flight
+  constexpr int WAVES = kDirectWaves;
+  __shared__ __attribute__((aligned(16))) float red[WAVES * 2 * 1024];
+  __shared__ __attribute__((aligned(16))) float phi[2][kGradSamples];
+  __shared__ __attribute__((aligned(16))) int exps[kGradSamples];
+  const int entry = ga.first + blockIdx.y, sd = entry >= ga.side[0].n ? 1 : 0, j = sd ? entry - ga.side[0].n : entry;
+  const GradSide& S = ga.side[sd];
+  const int B = ga.B, pc = ga.pc, k = S.k0 - j;
+  const float* V = S.v + (int64_t)(S.n - 1 - j) * B * pc;
+  const float* G = S.g + (int64_t)j * B * pc;
+  const float* ve = S.v + ga.eoff + (int64_t)(S.n - 1 - j) * B;
+  const float* ge = S.g + ga.eoff + (int64_t)j * B;
+  const int lane = threadIdx.x & 63, r = lane & 31, h4 = (lane >> 5) * 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tz = blockIdx.x / ga.tiles_a, ta = blockIdx.x - tz * ga.tiles_a;
+  const int a0 = ta * 32, z0 = tz * 64;
+  // columns past the padded bond repeat the last one and are not stored
+  const int va = min(a0 + r, pc - 1), g0 = min(z0 + r, pc - 1), g1 = min(z0 + 32 + r, pc - 1);
+  f32x16_t acc[2][2];   // [s][z block]
 #pragma unroll
-  for (int q = 0; q < kMaxSeg; ++q)
-    if (q == j) {
-      dst = sa.dst[q];
-      s0 = sa.st[q][0];
-      s1 = sa.st[q][1];
-      s2 = sa.st[q][2];
+  for (int s = 0; s < 2; ++s)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) acc[s][q] = f32x16_t{};
+
+  struct Frag {
+    f32x4_t v[NQ], g[2][NQ];
+  };
+  for (int base = 0; base < B; base += kGradSamples) {
+    const int nb = min(kGradSamples, B - base);
+    if (base) __syncthreads();   // the last samples' features are used up
+    for (int i = threadIdx.x; i < kGradSamples; i += WAVES * 64) {
+      float sv = 0.f, cv = 0.f;
+      int e = 0;
+      if (i < nb) {
+        sincospif(0.5f * ga.pixels[(int64_t)(base + i) * ga.n_pix + k], &sv, &cv);
+        e = (int)ve[base + i] + (int)ge[base + i];
+      }
+      phi[0][i] = cv;
+      phi[1][i] = sv;
+      exps[i] = e;
     }
-  const int64_t total = (int64_t)dl * 2 * dr;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int z = (int)(e % dr);
-    const int64_t as = e / dr;
-    const int sidx = (int)(as & 1), aa = (int)(as >> 1);
-    const int64_t o = ((int64_t)aa * 2 + sidx) * chi + z;
-    float v = 0.f;
-    for (int c = 0; c < S; ++c) v += src[c * blk + o];
-    dst[aa * s0 + sidx * s1 + z * s2] = v;
+    __syncthreads();
+    const int nch = (nb + CH - 1) / CH;
+    int c = wave * nch / WAVES;
+    const int c1 = (wave + 1) * nch / WAVES;
+    // the lane's column and half in a vector register, the sample in a scalar one
+    const __amdgpu_buffer_rsrc_t rv = chain_rsrc(V + (int64_t)base * pc), rg = chain_rsrc(G + (int64_t)base * pc);
+    auto at = [&](__amdgpu_buffer_rsrc_t rs, uint32_t voff, int soff) {
+      return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, voff, soff, 0));
+    };
+    auto load = [&](Frag& f, int ch) {
+      if ((ch + 1) * CH <= nb) {
+        const uint32_t lv = (uint32_t)(h4 * pc + va) * 4u, l0 = (uint32_t)(h4 * pc + g0) * 4u,
+                       l1 = (uint32_t)(h4 * pc + g1) * 4u;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int so = (ch * CH + 8 * q + i) * pc * 4;
+            f.v[q][i] = at(rv, lv, so);
+            f.g[0][q][i] = at(rg, l0, so);
+            f.g[1][q][i] = at(rg, l1, so);
+          }
+      } else {
+        // samples past the end repeat the last one (cleared below)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int row = min(ch * CH + 8 * q + h4 + i, nb - 1) * pc;
+            f.v[q][i] = at(rv, (uint32_t)(row + va) * 4u, 0);
+            f.g[0][q][i] = at(rg, (uint32_t)(row + g0) * 4u, 0);
+            f.g[1][q][i] = at(rg, (uint32_t)(row + g1) * 4u, 0);
+          }
+      }
+    };
+    auto products = [&](Frag& f, int ch) {
+      if ((ch + 1) * CH > nb) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (ch * CH + 8 * q + h4 + i >= nb) f.v[q][i] = f.g[0][q][i] = f.g[1][q][i] = 0.f;
+      }
+      f32x4_t x[2][NQ];
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const int at = ch * CH + 8 * q + h4;
+        const f32x4_t c0 = *reinterpret_cast<const f32x4_t*>(&phi[0][at]);
+        const f32x4_t c1v = *reinterpret_cast<const f32x4_t*>(&phi[1][at]);
+        const int4 e = *reinterpret_cast<const int4*>(&exps[at]);
+        const int ee[4] = {e.x, e.y, e.z, e.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          x[0][q][i] = ldexpf(f.v[q][i] * c0[i], ee[i]);
+          x[1][q][i] = ldexpf(f.v[q][i] * c1v[i], ee[i]);
+        }
+      }
+      if constexpr (!PrecInfo<P>::bf) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+              acc[s][q] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[s][0][i], f.g[q][0][i], acc[s][q], 0, 0, 0);
+      } else {
+        constexpr int NPL = PrecInfo<P>::planes;
+        bf16x8_t px[2][NPL], pg[2][NPL];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          direct_planes<P>(x[s], px[s]);
+          direct_planes<P>(f.g[s], pg[s]);
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            f32x16_t t = {};
+#pragma unroll
+            for (int m = 0; m < PrecInfo<P>::nprod; ++m)
+              t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(px[s][prod_a(P, m)], pg[q][prod_b(P, m)], t, 0, 0, 0);
+            acc[s][q] += t;
+          }
+      }
+    };
+    Frag f[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (c + u < c1) load(f[u], c + u);
+    for (; c < c1; c += U) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (c + u < c1) {
+          products(f[u], c + u);
+          if (c + u + U < c1) load(f[u], c + u + U);
+        }
+    }
+  }
+
+  // the waves' sums, one s at a time: [wave][z block][register / 4][lane][register % 4]
+  const int dl = k == 0 ? 1 : ga.chi, dr = k == ga.n_pix - 1 ? 1 : ga.chi;
+  float* dst = ga.dst[blockIdx.y];
+  const int64_t sa = ga.st[blockIdx.y][0], ss = ga.st[blockIdx.y][1], sz = ga.st[blockIdx.y][2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    if (s) __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const f32x4_t y = {acc[s][q][4 * e], acc[s][q][4 * e + 1], acc[s][q][4 * e + 2], acc[s][q][4 * e + 3]};
+        *reinterpret_cast<f32x4_t*>(red + ((wave * 2 + q) * 4 + e) * 256 + lane * 4) = y;
+      }
+    __syncthreads();
+    // a wave finishes four registers of one z block: rows 8 e + 4 (lane / 32) + i
+    const int q = wave >> 2, e = wave & 3;
+    f32x4_t t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) t += *reinterpret_cast<const f32x4_t*>(red + ((w * 2 + q) * 4 + e) * 256 + lane * 4);
+    const int z = z0 + 32 * q + r;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int aa = a0 + 8 * e + h4 + i;
+      if (aa < dl && z < dr) dst[aa * sa + s * ss + z * sz] = t[i];
+    }
   }
 }
 
@@ -577,18 +722,7 @@ struct Geometry {
   std::vector<int> right_b;    // right boundaries N = t_0 > ... > t_m = c + 1
   int64_t vb;                  // floats per vector block
   size_t ckpt_floats;
-  int S;                       // batch chunks of the weight-gradient GEMMs
 };
-
-// Batch chunks for the weight-gradient GEMMs (K = batch is long, the output
-// 2 chi x chi small): split the batch while it divides evenly, the chunks
-// keep at least 64 samples and a segment has fewer than 2048 64 x 64 tiles.
-int grad_chunks(int B, int chi, int E) {
-  const int64_t tiles = (int64_t)((2 * chi + 63) / 64) * ((chi + 63) / 64);
-  int S = 1;
-  while (S < 16 && B % (2 * S) == 0 && B / (2 * S) >= 64 && (int64_t)E * S * tiles < 2048) S *= 2;
-  return S;
-}
 
 int pad_of(int chi) {
   for (int p : {16, 32, 64, 128, 256})
@@ -615,7 +749,6 @@ int32_t geometry(int32_t N, int32_t c, int32_t L, int32_t B, int32_t chi, int32_
   for (int t = N; t > c + 1; t -= E) g.right_b.push_back(t);
   g.right_b.push_back(c + 1);
   g.vb = vblock_floats(B, g.pad_chi);
-  g.S = grad_chunks(B, chi, E);
   g.ckpt_floats = (size_t)(g.left_b.size() + g.right_b.size()) * g.vb;
   return TN_OK;
 }
@@ -623,11 +756,10 @@ int32_t geometry(int32_t N, int32_t c, int32_t L, int32_t B, int32_t chi, int32_
 size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct WsLayout {
-  size_t vtmp0, vtmp1, xbuf, tbuf, ybuf, gubuf, seg_v[2], seg_g[2], xseg[2], gbuf[2], part, total;
+  size_t vtmp0, vtmp1, xbuf, tbuf, ybuf, gubuf, seg_v[2], seg_g[2], part, total;
 };
 
-// per chain side (left, right): recomputed vectors, adjoints, expanded
-// gradient operands and dense gradient blocks of one segment
+// per chain side (left, right): recomputed vectors and adjoints of one segment
 WsLayout ws_layout(const Geometry& g) {
   WsLayout w;
   const size_t vb = (size_t)g.vb * 4;
@@ -642,8 +774,6 @@ WsLayout ws_layout(const Geometry& g) {
   for (int side = 0; side < 2; ++side) {
     w.seg_v[side] = o; o += al(E * vb);
     w.seg_g[side] = o; o += al(E * vb);
-    w.xseg[side] = o; o += al(E * (size_t)g.B * g.chi * 2 * 4);
-    w.gbuf[side] = o; o += al(E * (size_t)g.S * g.chi * 2 * g.chi * 4);
   }
   w.part = o; o += al((size_t)g.B * 8);
   w.total = o;
@@ -724,50 +854,35 @@ int32_t launch_chain(const Geometry& g, const tn_tensor* sites, const float* pix
                        st);
 }
 
-// Weight gradients of one segment: dA_{k_j} = sum_b X_j[b, (a s)] G_j[b, z]
-// for j < n, k_j = k0 - j, X_j formed from vsrc (see expand_seg_kernel) and
-// G_j the vectors of slot j of gsrc.  One batched GEMM over (j, chunk c of
-// the batch) into S partial blocks per site, then a scatter that sums them
-// into the caller's gradient tensors.
-int32_t segment_grads(const Geometry& g, const float* vsrc, const float* gsrc, int n, int k0, const float* px,
-                      float* xseg, float* gbuf, tn_tensor* dsites, int32_t prec, hipStream_t st) {
+// Weight gradients of a segment on each side (n = 0: none): see segment_grad_kernel
+int32_t segment_grads(const Geometry& g, const GradSide& s0, const GradSide& s1, const float* px, tn_tensor* dsites,
+                      int32_t prec, hipStream_t st) {
+  const int n = s0.n + s1.n;
   if (n <= 0) return TN_OK;
-  const int B = g.B, chi = g.chi, pc = g.pad_chi, S = g.S, Bc = B / S;
-  const int64_t eoff = (int64_t)g.E * B * pc;
-  hipLaunchKernelGGL(expand_seg_kernel, dim3(std::min<unsigned>(blocks_of((int64_t)B * chi * 2), 2048), n), dim3(256),
-                     0, st, vsrc, gsrc, eoff, n, k0, px, g.N, B, pc, chi, xseg);
-  TN_TRY(hip_check(hipGetLastError(), "expand segment"));
-  tn_tensor xv = make_view(xseg, TN_F32, {Bc, chi, 2});
-  tn_tensor gv;
-  std::memset(&gv, 0, sizeof(gv));
-  gv.data = const_cast<float*>(gsrc);
-  gv.dtype = TN_F32;
-  gv.rank = 2;
-  gv.shape[0] = Bc;
-  gv.shape[1] = chi;
-  gv.stride[0] = pc;
-  gv.stride[1] = 1;
-  tn_tensor ov = make_view(gbuf, TN_F32, {chi, 2, chi});
-  const int32_t pa[1] = {0}, pb[1] = {0};
-  GemmDesc d;
-  TN_TRY(plan_gemm(xv, gv, 1, pa, pb, ov, d));
-  // batch entry j * S + c: X_j rows and G_j rows of chunk c, partial block (j, c)
-  d.batch = n * S;
-  d.a_bs = (int64_t)Bc * chi * 2;
-  d.b_bs = (int64_t)Bc * pc;
-  d.c_bs = (int64_t)chi * 2 * chi;
-  choose_modes(d);
-  TN_TRY(launch_gemm(d, prec, st));
-  ScatterArgs sa;
-  std::memset(&sa, 0, sizeof(sa));
-  for (int j = 0; j < n; ++j) {
-    const tn_tensor& t = dsites[k0 - j];
-    sa.dst[j] = static_cast<float*>(t.data);
-    for (int q = 0; q < 3; ++q) sa.st[j][q] = t.stride[q];
+  GradArgs ga;
+  std::memset(&ga, 0, sizeof(ga));
+  ga.side[0] = s0;
+  ga.side[1] = s1;
+  ga.eoff = (int64_t)g.E * g.B * g.pad_chi;
+  ga.pixels = px;
+  ga.n_pix = g.N;
+  ga.B = g.B;
+  ga.pc = g.pad_chi;
+  ga.chi = g.chi;
+  ga.tiles_a = (g.chi + 31) / 32;
+  auto f = prec == TN_PREC_SPLIT_BF16 ? segment_grad_kernel<P_X6> : segment_grad_kernel<P_FP32>;
+  for (ga.first = 0; ga.first < n; ga.first += kMaxSeg) {
+    const int cnt = std::min(kMaxSeg, n - ga.first);
+    for (int i = 0; i < cnt; ++i) {
+      const int e = ga.first + i;
+      const tn_tensor& t = dsites[e < s0.n ? s0.k0 - e : s1.k0 - (e - s0.n)];
+      ga.dst[i] = static_cast<float*>(t.data);
+      for (int q = 0; q < 3; ++q) ga.st[i][q] = t.stride[q];
+    }
+    hipLaunchKernelGGL(f, dim3((unsigned)(ga.tiles_a * ((g.chi + 63) / 64)), (unsigned)cnt), dim3(kDirectWaves * 64), 0,
+                       st, ga);
   }
-  hipLaunchKernelGGL(scatter_grad_kernel, dim3(blocks_of((int64_t)chi * 2 * chi), n), dim3(256), 0, st, gbuf, n, S, k0,
-                     g.N, chi, sa);
-  return hip_check(hipGetLastError(), "scatter gradients");
+  return hip_check(hipGetLastError(), "segment gradients");
 }
 
 // T[b, l, z] = sum_{a s} Xc[b, a, s] A_c[a, s, l, z]
@@ -938,8 +1053,6 @@ int32_t tn_mps_classifier_backward(int32_t n_sites, int32_t label_site, int32_t 
   float* ubar = reinterpret_cast<float*>(ws + w.vtmp1);   // adjoint of the right vector
   float* segv[2] = {reinterpret_cast<float*>(ws + w.seg_v[0]), reinterpret_cast<float*>(ws + w.seg_v[1])};
   float* segg[2] = {reinterpret_cast<float*>(ws + w.seg_g[0]), reinterpret_cast<float*>(ws + w.seg_g[1])};
-  float* xseg[2] = {reinterpret_cast<float*>(ws + w.xseg[0]), reinterpret_cast<float*>(ws + w.xseg[1])};
-  float* gbuf[2] = {reinterpret_cast<float*>(ws + w.gbuf[0]), reinterpret_cast<float*>(ws + w.gbuf[1])};
   const tn_tensor& ac = sites[label_site];
 
   // ---- label site
@@ -998,16 +1111,12 @@ int32_t tn_mps_classifier_backward(int32_t n_sites, int32_t label_site, int32_t 
       runs.push_back(chain_args(g, sites, px, 0, t1, 1, n, ubar, ubar, segg[1], 0));
     }
     TN_TRY(launch_chains(g, runs, st));
-    if (jl >= 0) {
-      // site k = s1-1-j:  X from v_k (segv slot n-1-j), G = abar_{k+1} (segg slot j)
-      const int s0 = g.left_b[jl], s1 = g.left_b[jl + 1];
-      TN_TRY(segment_grads(g, segv[0], segg[0], s1 - s0, s1 - 1, px, xseg[0], gbuf[0], dsites, prec, st));
-    }
-    if (jr >= 0) {
-      // site k = t0-1-j:  X from ubar_k (segg slot n-1-j), G = u_{k+1} (segv slot j)
-      const int t0 = g.right_b[jr], t1 = g.right_b[jr + 1];
-      TN_TRY(segment_grads(g, segg[1], segv[1], t0 - t1, t0 - 1, px, xseg[1], gbuf[1], dsites, prec, st));
-    }
+    GradSide sl{}, sr{};
+    // site k = s1-1-j: from v_k (segv slot n-1-j) and abar_{k+1} (segg slot j)
+    if (jl >= 0) sl = {segv[0], segg[0], g.left_b[jl + 1] - g.left_b[jl], g.left_b[jl + 1] - 1};
+    // site k = t0-1-j: from ubar_k (segg slot n-1-j) and u_{k+1} (segv slot j)
+    if (jr >= 0) sr = {segg[1], segv[1], g.right_b[jr] - g.right_b[jr + 1], g.right_b[jr] - 1};
+    TN_TRY(segment_grads(g, sl, sr, px, dsites, prec, st));
   }
   return TN_OK;
 }

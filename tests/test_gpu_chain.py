@@ -50,3 +50,20 @@ def test_batches(batch, prec):
 def test_segments(shape):
     n, c, every = shape
     run(n, 20, 2, c, 5, every, "fp32", 300 + n)
+
+
+def test_gradients_through_strides():
+    """The gradient kernel writes the caller's views: reversed axes and a gap."""
+    n, chi, labels, c, batch = 7, 20, 3, 3, 33
+    sites = [s.astype(np.float32) for s in inputs.classifier_sites(n, chi, labels, c, 7)]
+    gs = [torch.tensor(s, device=DEV) for s in sites]
+    gp = torch.tensor(inputs.images(batch, n, 8).astype(np.float32), device=DEV)
+    model = tn.MPSClassifier(n, c, labels, chi, batch, ckpt_every=2)
+    _, dlog = tn.softmax_xent(model.forward(gs, gp), torch.zeros(batch, dtype=torch.int64, device=DEV))
+    plain = model.backward(gs, gp, dlog)
+    views = [torch.full(tuple(reversed(s.shape)) + (2,), 7.0, device=DEV)[..., 0].permute(*reversed(range(s.dim())))
+             for s in gs]
+    model.backward(gs, gp, dlog, views)
+    torch.cuda.synchronize()
+    for p, v in zip(plain, views):
+        assert torch.equal(p, v)
