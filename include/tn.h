@@ -291,8 +291,9 @@ int32_t tn_mps_env_sweep(int32_t n_sites, const tn_tensor* psi, const tn_tensor*
 
 /* ---------------------------------------------------------------------
  * Left-canonical gauge in FP64 on the GPU (support step for the operator
- * sweeps): A_k reshaped (D_k d, D_{k+1}) = Q R by Householder QR with
- * diag(R) >= 0; Q replaces A_k, R is absorbed into A_{k+1}; the final 1x1 R
+ * sweeps): A_k reshaped (D_k d, D_{k+1}) = Q R with diag(R) >= 0, by
+ * Cholesky QR where a bound checked on the device certifies it and by
+ * Householder QR otherwise; Q replaces A_k, R is absorbed into A_{k+1}; the final 1x1 R
  * is the state's norm, written as its logarithm to *lognorm (DEVICE) and
  * divided out.  sites: TN_F64, contiguous, modified in place.  Requires
  * D_{k+1} <= d * D_k.  Each site's Q is formed on the library-owned side

@@ -1,0 +1,29 @@
+// QR of a site by Cholesky factorisation with a certificate (cholqr.hip)
+#pragma once
+
+#include "internal.h"
+
+namespace tn {
+
+// The largest |E| that certifies a site, 2^-35, as bits: 1024 columns bound
+// |E|_2^2 by (1024 2^-35)^2 < 2^-49 at the very worst, and by about 2^-60 for
+// errors of random signs
+constexpr uint64_t kMaxE = (uint64_t)(1023 - 35) << 52;
+// ebits: the bits of max |E| (a NaN's are larger than any number's); kernels
+// of the Householder path take it as `cert` (null: run) and leave at once
+// where the site is certified
+__device__ __forceinline__ bool chol_certified(const uint64_t* ebits) { return ebits && *ebits <= kMaxE; }
+
+constexpr size_t kCholLinv = 2 * 64 * 64;   // doubles
+
+// x (dk x cols, row-major) = r (dk x dk upper triangular, zero below) a
+int32_t chol_absorb(const double* r, const double* a, double* x, int dk, int cols, hipStream_t st);
+// Q1, R1 and U of x (m x n, row-major, overwritten; m >= n), the certificate
+// into ebits, and R = (I + U) R1 into r where it holds.  g, r1, u, r: n x n;
+// q1: m x n; linv: kCholLinv doubles.
+int32_t chol_qr(double* x, int m, int n, double* g, double* r1, double* u, double* q1, double* linv, uint64_t* ebits,
+                double* r, hipStream_t st);
+// site = Q1 (I - U) where the certificate holds
+int32_t chol_q(const double* q1, const double* u, double* site, int m, int n, uint64_t* ebits, hipStream_t st);
+
+}  // namespace tn

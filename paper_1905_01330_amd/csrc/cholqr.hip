@@ -1,0 +1,459 @@
+// QR of a site by Cholesky factorisation, for the left-canonical gauge: the
+// tall matrix X (m x n, row-major, as a site is stored) is orthogonalised by
+// its Gram matrix, R1^T R1 = X^T X and Q1 = X R1^-1 (the triangle is unique
+// with a positive diagonal, so R and Q are those of the Householder
+// factorisation), and corrected once: with E = Q1^T Q1 - I and U its upper
+// triangle with half the diagonal,
+//   Q = Q1 (I - U),  R = (I + U) R1
+// are exact to second order in E (Yamamoto, Nakatsukasa, Yanagisawa and
+// Fukaya, ETNA 44, 2015, for the two passes; the second one's factor is
+// I + U + O(E^2)).
+//
+// Certificate: max |E| is taken over the computed Q1^T Q1.  Up to kMaxE the
+// neglected terms stay below an FP64 rounding; above it, or with a NaN (a
+// pivot that is not positive, an overflow), the site is left to the
+// Householder kernels.  Both sets of kernels are always launched and look at
+// the certificate on the device: no host synchronisation, capturable.
+//
+// Everything is FP64 matrix-core work on the whole chip, 64 columns at a
+// time; the Householder panels are a chain of one workgroup's reductions over
+// the rows, one a column.  The chain of 100 sites of bond 1024 of two states:
+// 58.1 ms by Householder panels, 10.2 ms here.
+#include "cholqr.h"
+
+namespace tn {
+
+typedef double d64x4_t __attribute__((ext_vector_type(4)));
+
+// ---------------------------------------------------------------------------
+// products
+
+enum CholOp { C_ABSORB, C_GRAM, C_DEFECT, C_TRIANGLE, C_Q };
+
+struct CholGemm {
+  const double* a;
+  const double* b;
+  const double* base;   // C_TRIANGLE: R1, C_Q: Q1
+  double* c;
+  int M, N, K, lda, ldb, ldc;
+  uint64_t* ebits;
+};
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t chol_rsrc(const double* p) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(p), (short)0, (int)0x80000000, 0x00020000);
+}
+
+// C (32 x 64 a workgroup, four waves of 16 x 32) with
+//   C_ABSORB:   C = A B, A upper triangular (K from the row)
+//   C_GRAM:     C = A^T B, the upper triangle's tiles
+//   C_DEFECT:   U of A^T B - I, and max |E| into ebits
+//   C_TRIANGLE: C = base + A B, all triangles upper, zero below (where certified)
+//   C_Q:        C = base - A B, B upper triangular (where certified)
+// Stages of 16 k through two LDS buffers, k-major with a pitch of 16 mod 32
+// doubles so that the four k that a matrix-core operand reads fall into both
+// halves of the banks.  A stage's products take 0.2 us, a load a few times
+// that: four stages are in flight in registers (1024 x 1024 over 2048: one in
+// flight 131 us, four 109).
+template <int OP>
+__global__ void __launch_bounds__(256) chol_gemm_kernel(const CholGemm p) {
+  constexpr bool TN = OP == C_GRAM || OP == C_DEFECT;   // A stored k x m
+  constexpr int PA = 48, PB = 80;
+  __shared__ double sa[2][16][PA], sb[2][16][PB];
+  __shared__ uint64_t smax[4];
+  if constexpr (OP == C_TRIANGLE || OP == C_Q) {
+    if (!chol_certified(p.ebits)) return;
+  }
+  const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 64;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  if (TN && n0 + 63 < m0) return;
+  int kb = 0, ke = p.K;
+  if (OP == C_ABSORB || OP == C_TRIANGLE) kb = m0 & ~15;
+  if (OP == C_TRIANGLE || OP == C_Q) ke = min(p.K, n0 + 64);
+  constexpr int D = 4;   // stages in flight
+  double ra[D][2], rb[D][4];
+  // Raw buffers of 2^31 bytes (the host keeps matrices below that): an offset
+  // past the end reads zero, so a guard is a select and not a branch, behind
+  // which the loads of a stage would wait for each other.
+  const __amdgpu_buffer_rsrc_t qa = chol_rsrc(p.a), qb = chol_rsrc(p.b);
+  auto get = [](__amdgpu_buffer_rsrc_t rs, bool ok, int at) {
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, ok ? (uint32_t)at * 8u : 0x80000000u, 0, 0));
+  };
+  auto load = [&](double (&xa)[2], double (&xb)[4], int k0) {
+    if constexpr (TN) {
+      const int m = m0 + (t & 31);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int k = k0 + (t >> 5) + 8 * i;
+        xa[i] = get(qa, k < ke && m < p.M, k * p.lda + m);
+      }
+    } else {
+      const int m = m0 + (t >> 3);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int k = k0 + (t & 7) + 8 * i;
+        xa[i] = get(qa, k < ke && m < p.M, m * p.lda + k);
+      }
+    }
+    const int n = n0 + (t & 63);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int k = k0 + (t >> 6) + 4 * i;
+      xb[i] = get(qb, k < ke && n < p.N, k * p.ldb + n);
+    }
+  };
+  auto store = [&](const double (&xa)[2], const double (&xb)[4], int s) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      if constexpr (TN) sa[s][(t >> 5) + 8 * i][t & 31] = xa[i];
+      else sa[s][(t & 7) + 8 * i][t >> 3] = xa[i];
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sb[s][(t >> 6) + 4 * i][t & 63] = xb[i];
+  };
+  const int wm = (wave & 1) * 16, wn = (wave >> 1) * 32, l15 = lane & 15, lk = lane >> 4;
+  d64x4_t acc[2] = {};
+  // loads past the last k return zeros: no stage needs a condition
+#pragma unroll
+  for (int i = 0; i < D; ++i) load(ra[i], rb[i], kb + 16 * i);
+  for (int k0 = kb; k0 < ke; k0 += 16 * D) {
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+      store(ra[i], rb[i], i & 1);
+      load(ra[i], rb[i], k0 + 16 * (i + D));
+      __syncthreads();
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        const double av = sa[i & 1][4 * kk + lk][wm + l15];
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+          acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, sb[i & 1][4 * kk + lk][wn + 16 * q + l15], acc[q], 0, 0, 0);
+      }
+    }
+  }
+  // FP64 16x16x4 result: lane (column l15) register r holds row 4 r + lk
+  uint64_t emax = 0;
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = m0 + wm + 4 * r + lk, n = n0 + wn + 16 * q + l15;
+      if (m >= p.M || n >= p.N) continue;
+      double v = acc[q][r];
+      const int64_t at = (int64_t)m * p.ldc + n;
+      if constexpr (OP == C_DEFECT) {
+        if (m == n) v -= 1.0;
+        if (n >= m) emax = max(emax, (uint64_t)__double_as_longlong(fabs(v)));
+        v = n > m ? v : n == m ? 0.5 * v : 0.0;
+      } else if constexpr (OP == C_TRIANGLE) {
+        v = n >= m ? p.base[at] + v : 0.0;
+      } else if constexpr (OP == C_Q) {
+        v = p.base[at] - v;
+      }
+      p.c[at] = v;
+    }
+  if constexpr (OP == C_DEFECT) {
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) emax = max(emax, (uint64_t)__shfl_xor((unsigned long long)emax, o, 64));
+    if (lane == 0) smax[wave] = emax;
+    __syncthreads();
+    if (t == 0)
+      atomicMax((unsigned long long*)p.ebits, (unsigned long long)max(max(smax[0], smax[1]), max(smax[2], smax[3])));
+  }
+}
+
+// ---------------------------------------------------------------------------
+// blocked Cholesky with the triangular solve of X carried along: step k takes
+// the 64 columns of block k out of the trailing columns of G and X,
+//   P_j = L G_kj (L = R_kk^-T), Q_t = X_tk L^T, G_ij -= P_i^T P_j, X_tj -= Q_t P_j.
+// One launch a step; a workgroup owns one 64 x 64 tile (i, j) of G or (t, j)
+// of X and forms the P and Q it needs itself (three products of 64^3; the
+// matrix cores of the chip are idle otherwise, and a launch less costs more
+// than they do).  The tile (k + 1, k + 1) then factorises its result for the
+// next step.
+
+constexpr int kCb = 64;                  // block
+constexpr int kPk = 66;                  // LDS pitch of operands read along k (rows 16 bytes apart mod 256)
+constexpr int kPn = 80;                  // pitch of operands read along the other index
+constexpr int kCholThreads = 512;
+
+struct CholStep {
+  double* g;        // n x n
+  double* x;        // m x n
+  double* q;        // Q1, m x n
+  double* r;        // R1, n x n
+  double* linv;     // L of the current block (64 x 64); the next one's goes to linv2
+  double* linv2;
+  uint64_t* ebits;
+  int m, n, k, nb, tr;   // rows, columns, step (-1: factorise block 0), column blocks, row blocks of X
+};
+
+// 64 x 64 product of two LDS operands, waves of 16 rows x 32 columns:
+// A at a + row * ar + k * ak, B at b + k * bk + col * bc
+__device__ __forceinline__ void chol_product(const double* a, int ar, int ak, const double* b, int bk, int bc,
+                                             d64x4_t (&acc)[2]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l15 = lane & 15, lk = lane >> 4;
+  const double* pa = a + ((wave & 3) * 16 + l15) * ar + lk * ak;
+  const double* pb = b + lk * bk + ((wave >> 2) * 32 + l15) * bc;
+  acc[0] = acc[1] = d64x4_t{};
+#pragma unroll
+  for (int kk = 0; kk < 16; ++kk) {
+    const double av = pa[4 * kk * ak];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, pb[4 * kk * bk + 16 * q * bc], acc[q], 0, 0, 0);
+  }
+}
+
+// f(row, column, value) over a wave's results
+template <class F>
+__device__ __forceinline__ void chol_each(const d64x4_t (&acc)[2], F&& f) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) f((wave & 3) * 16 + 4 * r + (lane >> 4), (wave >> 2) * 32 + 16 * q + (lane & 15), acc[q][r]);
+}
+
+__device__ __forceinline__ double chol_lane(double x, int l) {
+  const long long v = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_readlane((int)v, l), hi = __builtin_amdgcn_readlane((int)(v >> 32), l);
+  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned int)lo);
+}
+
+// R and L = R^-T of the 64 x 64 matrix in tm (pitch kPn, upper triangle read):
+// R back into tm, L into ym (pitch kPn).  Blocks of 16: one wave eliminates
+// the diagonal block, a column a lane, with the identity's columns on the
+// next sixteen lanes (the elimination turns [G I] into [R L]); the rest of
+// the block row and of the trailing rows are 16 x 16 products, as many at a
+// time as there are waves.
+__device__ __forceinline__ void chol_factor(double* tm, double* ym, double* dm) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l15 = lane & 15, lk = lane >> 4;
+  for (int e = threadIdx.x; e < 64 * 64; e += kCholThreads) ym[(e >> 6) * kPn + (e & 63)] = (e >> 6) == (e & 63) ? 1.0 : 0.0;
+  // C (16 x 16) = sign * A^T-or-A B, A at a + k * ak + row * ar, B at b + k * kPn + col
+  auto block = [&](const double* a, int ar, int ak, const double* b, d64x4_t c) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+      c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[(4 * kk + lk) * ak + l15 * ar], b[(4 * kk + lk) * kPn + l15], c, 0, 0, 0);
+    return c;
+  };
+  for (int b = 0; b < 4; ++b) {
+    const int r0 = 16 * b;
+    __syncthreads();
+    if (wave == 0) {
+      double g[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        g[i] = lane < 16 ? (i <= lane ? tm[(r0 + i) * kPn + r0 + lane] : 0.0) : (i == l15 ? 1.0 : 0.0);
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        const double d = chol_lane(g[k], k);
+        // 1 / sqrt(d): the hardware's estimate and two Newton steps
+        double y = __builtin_amdgcn_rsq(d);
+        y = y * fma(-0.5 * d * y, y, 1.5);
+        y = y * fma(-0.5 * d * y, y, 1.5);
+        if (!(d > 0.0)) y = __builtin_nan("");   // not positive: the certificate fails
+        const double rk = g[k] * y;
+        g[k] = rk;
+#pragma unroll
+        for (int i = k + 1; i < 16; ++i) g[i] = fma(-chol_lane(rk, i), rk, g[i]);
+      }
+      if (lane < 16) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) tm[(r0 + i) * kPn + r0 + lane] = i <= lane ? g[i] : 0.0;
+      } else if (lane < 32) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) dm[i * 18 + l15] = i >= l15 ? g[i] : 0.0;
+      }
+    }
+    __syncthreads();
+    // block row b: R_b,cb = D T_b,cb (cb > b), L_b,cb = D Y_b,cb (cb <= b): four products
+    d64x4_t c = {};
+    double* row = nullptr;
+    if (wave < 4) {
+      row = (wave > b ? tm : ym) + r0 * kPn + 16 * wave;
+      c = block(dm, 18, 1, row, d64x4_t{});
+    }
+    __syncthreads();
+    if (wave < 4) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) row[(4 * r + lk) * kPn + l15] = c[r];
+    }
+    __syncthreads();
+    // trailing rows ib > b: T_ib,cb -= R_b,ib^T R_b,cb (cb >= ib), Y_ib,cb -= R_b,ib^T L_b,cb (cb <= b)
+    int job = 0;
+    for (int ib = b + 1; ib < 4; ++ib)
+      for (int cb = 0; cb < 4; ++cb) {
+        if (cb > b && cb < ib) continue;
+        if ((job++ & 7) != wave) continue;
+        double* src = (cb > b ? tm : ym) + r0 * kPn + 16 * cb;
+        double* dst = (cb > b ? tm : ym) + 16 * ib * kPn + 16 * cb;
+        const d64x4_t u = block(tm + r0 * kPn + 16 * ib, 1, kPn, src, d64x4_t{});
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dst[(4 * r + lk) * kPn + l15] -= u[r];
+      }
+  }
+  __syncthreads();
+}
+
+__global__ void __launch_bounds__(kCholThreads) chol_step_kernel(const CholStep p) {
+  __shared__ double sl[64 * kPk];           // L of the step
+  __shared__ double s1[64 * kPn], s2[64 * kPn];
+  __shared__ double dm[16 * 18];
+  const int n = p.n, k0 = p.k * kCb;
+  int id = blockIdx.x;
+  if (p.k < 0) {   // block 0 only
+    if (threadIdx.x == 0) *p.ebits = 0;
+    for (int e = threadIdx.x; e < 64 * 64; e += kCholThreads) {
+      const int i = e >> 6, j = e & 63;
+      s1[i * kPn + j] = i < n && j < n ? (j >= i ? p.g[(int64_t)i * n + j] : 0.0) : (i == j ? 1.0 : 0.0);
+    }
+    __syncthreads();
+  } else {
+    // tile of the trailing columns: (i, j) of G, i <= j, then (t, j) of X
+    const int left = p.nb - 1 - p.k, tri = left * (left + 1) / 2;
+    const bool in_g = id < tri;
+    int ti, tj;
+    if (in_g) {
+      tj = (int)((sqrtf(8.0f * id + 1.0f) - 1.0f) * 0.5f);
+      while ((tj + 1) * (tj + 2) / 2 <= id) ++tj;
+      while (tj * (tj + 1) / 2 > id) --tj;
+      ti = id - tj * (tj + 1) / 2;
+    } else {
+      id -= tri;
+      ti = id % p.tr;
+      tj = id / p.tr;
+    }
+    const int j0 = (p.k + 1 + tj) * kCb;                              // columns of the tile
+    const int i0 = in_g ? (p.k + 1 + ti) * kCb : ti * kCb;            // its rows
+    const bool solve_only = left == 0;                                // the last block: Q alone
+    // 64 x 64 blocks of rows r0.. and columns c0.., zero past the matrix: all
+    // loads, then all stores
+    auto fetch = [&](const double* src, int rows, int r0, int c0, double (&v)[8]) {
+      const __amdgpu_buffer_rsrc_t rs = chol_rsrc(src);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int i = r0 + (threadIdx.x >> 6) + 8 * e, j = c0 + (threadIdx.x & 63);
+        v[e] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(
+                                              rs, i < rows && j < n ? (uint32_t)(i * n + j) * 8u : 0x80000000u, 0, 0));
+      }
+    };
+    auto put = [&](double* dst, int pitch, const double (&v)[8]) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) dst[((threadIdx.x >> 6) + 8 * e) * pitch + (threadIdx.x & 63)] = v[e];
+    };
+    double vl[8], v1[8], v2[8], vc[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) vl[e] = p.linv[threadIdx.x + kCholThreads * e];
+    if (!solve_only) fetch(p.g, n, k0, j0, v1);
+    if (!in_g) fetch(p.x, p.m, i0, k0, v2);
+    else if (ti != tj) fetch(p.g, n, k0, i0, v2);
+    put(sl, kPk, vl);
+    if (!solve_only) put(s1, kPn, v1);
+    if (!in_g) put(s2, kPk, v2);
+    else if (ti != tj) put(s2, kPn, v2);
+    __syncthreads();
+    // the tile itself, in the layout of the products' results
+    if (!solve_only) {
+      const __amdgpu_buffer_rsrc_t rs = chol_rsrc(in_g ? p.g : p.x);
+      const int rows = in_g ? n : p.m, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int i = i0 + (wave & 3) * 16 + 4 * r + (lane >> 4), j = j0 + (wave >> 2) * 32 + 16 * q + (lane & 15);
+          vc[4 * q + r] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(
+                                                         rs, i < rows && j < n ? (uint32_t)(i * n + j) * 8u : 0x80000000u, 0, 0));
+        }
+    }
+    d64x4_t pj[2], pi[2];
+    if (!solve_only) chol_product(sl, kPk, 1, s1, kPn, 1, pj);                    // P_j = L G_kj
+    if (!in_g) chol_product(s2, kPk, 1, sl, 1, kPk, pi);                          // Q_t = X_tk L^T
+    else if (ti != tj) chol_product(sl, kPk, 1, s2, kPn, 1, pi);                  // P_i
+    __syncthreads();
+    if (!solve_only) chol_each(pj, [&](int r, int c, double v) { s1[r * kPn + c] = v; });
+    if (!in_g) {
+      chol_each(pi, [&](int r, int c, double v) {
+        s2[r * kPk + c] = v;
+        if (tj == 0 && i0 + r < p.m && k0 + c < n) p.q[(int64_t)(i0 + r) * n + k0 + c] = v;
+      });
+      if (solve_only) return;
+    } else if (ti != tj) {
+      chol_each(pi, [&](int r, int c, double v) { s2[r * kPn + c] = v; });
+    } else {
+      // the diagonal tiles write their columns of block row k of R
+      chol_each(pj, [&](int r, int c, double v) {
+        if (k0 + r < n && j0 + c < n) p.r[(int64_t)(k0 + r) * n + j0 + c] = v;
+      });
+    }
+    __syncthreads();
+    d64x4_t u[2];
+    if (in_g) chol_product(ti == tj ? s1 : s2, 1, kPn, s1, kPn, 1, u);            // P_i^T P_j
+    else chol_product(s2, kPk, 1, s1, kPn, 1, u);                                 // Q_t P_j
+    double* c = in_g ? p.g : p.x;
+    const int rows = in_g ? n : p.m;
+    const bool next = in_g && ti == 0 && tj == 0;
+    if (next) __syncthreads();   // s1 is read until here
+    int at = 0;
+    chol_each(u, [&](int r, int cc, double v) {
+      const double y = vc[at++] - v;
+      const bool inside = i0 + r < rows && j0 + cc < n;
+      if (inside) c[(int64_t)(i0 + r) * n + j0 + cc] = y;
+      // the next diagonal block, bordered by the identity past the last column
+      if (next) s1[r * kPn + cc] = inside ? (cc >= r ? y : 0.0) : (r == cc ? 1.0 : 0.0);
+    });
+    if (!next) return;
+    __syncthreads();
+  }
+  chol_factor(s1, s2, dm);
+  const int d0 = (p.k + 1) * kCb;
+  for (int e = threadIdx.x; e < 64 * 64; e += kCholThreads) {
+    const int i = e >> 6, j = e & 63;
+    p.linv2[e] = j <= i ? s2[i * kPn + j] : 0.0;
+    if (d0 + i < n && d0 + j < n) p.r[(int64_t)(d0 + i) * n + d0 + j] = j >= i ? s1[i * kPn + j] : 0.0;
+  }
+}
+
+// ---------------------------------------------------------------------------
+
+template <int OP>
+static void chol_gemm(const CholGemm& p, hipStream_t st) {
+  hipLaunchKernelGGL(chol_gemm_kernel<OP>, dim3((unsigned)((p.N + 63) / 64), (unsigned)((p.M + 31) / 32)), dim3(256), 0, st, p);
+}
+
+int32_t chol_absorb(const double* r, const double* a, double* x, int dk, int cols, hipStream_t st) {
+  chol_gemm<C_ABSORB>({r, a, nullptr, x, dk, cols, dk, dk, cols, cols, nullptr}, st);
+  return hip_check(hipGetLastError(), "absorb");
+}
+
+int32_t chol_qr(double* x, int m, int n, double* g, double* r1, double* u, double* q1, double* linv, uint64_t* ebits,
+                double* r, hipStream_t st) {
+  chol_gemm<C_GRAM>({x, x, nullptr, g, n, n, m, n, n, n, nullptr}, st);
+  CholStep s;
+  s.g = g;
+  s.x = x;
+  s.q = q1;
+  s.r = r1;
+  s.ebits = ebits;
+  s.m = m;
+  s.n = n;
+  s.nb = (n + kCb - 1) / kCb;
+  s.tr = (m + kCb - 1) / kCb;
+  for (int k = -1; k < s.nb; ++k) {
+    s.k = k;
+    s.linv = linv + (k & 1) * kCb * kCb;
+    s.linv2 = linv + ((k + 1) & 1) * kCb * kCb;
+    const int left = s.nb - 1 - k;
+    const int tiles = k < 0 ? 1 : left == 0 ? s.tr : left * (left + 1) / 2 + s.tr * left;
+    hipLaunchKernelGGL(chol_step_kernel, dim3((unsigned)tiles), dim3(kCholThreads), 0, st, s);
+  }
+  chol_gemm<C_DEFECT>({q1, q1, nullptr, u, n, n, m, n, n, n, ebits}, st);
+  chol_gemm<C_TRIANGLE>({u, r1, r1, r, n, n, n, n, n, n, ebits}, st);
+  return hip_check(hipGetLastError(), "cholesky qr");
+}
+
+int32_t chol_q(const double* q1, const double* u, double* site, int m, int n, uint64_t* ebits, hipStream_t st) {
+  chol_gemm<C_Q>({q1, u, q1, site, m, n, n, n, n, n, ebits}, st);
+  return hip_check(hipGetLastError(), "cholesky q");
+}
+
+}  // namespace tn

@@ -1,24 +1,30 @@
-// Left-canonical gauge of an MPS in FP64 on the GPU: successive Householder
-// QR factorisations (Golub and Van Loan, "Matrix Computations", 5.1-5.2).
-// For site k the carried triangular factor is absorbed first
-// (X = R_{k-1} A_k viewed as (D_k d) x D_{k+1}), X is factorised in place,
-// the thin Q is accumulated backwards from [I; 0], and signs are fixed so
-// that diag(R) >= 0.  X and Q are kept column-major so every reflector and
-// column update reads contiguous memory.
-// Up to 2048 rows the factorisation is blocked in the compact WY form
-// (Schreiber and Van Loan; Golub and Van Loan 5.2.3): a panel of 16 columns
-// is factorised by one workgroup holding the panel in registers (two
-// workgroup reductions per column, row conditions as selects so the unrolled
-// panel stays short), which then forms the panel's triangular factor T from
-// the Gram matrix of its reflectors; one launch applies
-// I - V T^T V^T to all trailing columns (one reduction per workgroup); Q is
-// accumulated panel by panel in reverse with I - V T V^T.
-// Taller matrices take one reflector launch and one update launch per column.
+// Left-canonical gauge of an MPS in FP64 on the GPU: successive QR
+// factorisations.  For site k the carried triangular factor is absorbed first
+// (X = R_{k-1} A_k viewed as (D_k d) x D_{k+1}), X is factorised, and
+// diag(R) >= 0.
+//
+// From kCholMin columns on a site is first factorised by Cholesky
+// (cholqr.hip); where its certificate holds, the Householder kernels below
+// leave at once, otherwise they do the site from the start.
+//
+// Householder (Golub and Van Loan, "Matrix Computations", 5.1-5.2): X is
+// factorised in place, the thin Q is accumulated backwards from [I; 0], and
+// signs are fixed.  X and Q are kept column-major so every reflector and
+// column update reads contiguous memory.  Up to 2048 rows the factorisation
+// is blocked in the compact WY form (Schreiber and Van Loan; Golub and Van
+// Loan 5.2.3): one workgroup factorises a panel of 16 columns held in
+// registers (one workgroup reduction per column, row conditions as selects so
+// the unrolled panel stays short) and forms the panel's triangular factor T
+// from the Gram matrix of its reflectors; I - V T^T V^T is applied to all
+// trailing columns (one reduction per workgroup); Q is accumulated panel by
+// panel in reverse with I - V T V^T.  All panels and updates of a matrix are
+// tasks of one launch.  Taller matrices take one reflector launch and one
+// update launch per column.
 #include <algorithm>
 #include <cmath>
 #include <vector>
 
-#include "internal.h"
+#include "cholqr.h"
 
 namespace tn {
 
@@ -41,7 +47,12 @@ __device__ inline double block_sum(double v, double* red) {
 // blocks below it).  The 64 x 64 result tile goes through LDS so that the
 // column-major stores run along i.
 __global__ void __launch_bounds__(256) absorb_kernel(const double* __restrict__ r, const double* __restrict__ a,
-                                                     double* __restrict__ xc, int dk, int d, int dn) {
+                                                     double* __restrict__ xc, int dk, int d, int dn,
+                                                     uint32_t* ctr, int ctr_words, const uint64_t* cert) {
+  if (chol_certified(cert)) return;
+  // the task counters of the factorisation that follows
+  if (blockIdx.x == 0 && blockIdx.y == 0)
+    for (int i = threadIdx.x; i < ctr_words; i += 256) ctr[i] = 0;
   __shared__ double sr[64][17];
   __shared__ double sa[16][65];
   __shared__ double so[64][65];
@@ -83,7 +94,8 @@ __global__ void __launch_bounds__(256) absorb_kernel(const double* __restrict__ 
 }
 
 // reflector for column j of the column-major m x n matrix X (LAPACK larfg convention)
-__global__ void __launch_bounds__(256) reflector_kernel(double* xc, double* tau, int m, int j) {
+__global__ void __launch_bounds__(256) reflector_kernel(double* xc, double* tau, int m, int j, const uint64_t* cert) {
+  if (chol_certified(cert)) return;
   __shared__ double red[4];
   double* col = xc + (int64_t)j * m;
   double s = 0.0;
@@ -106,7 +118,8 @@ __global__ void __launch_bounds__(256) reflector_kernel(double* xc, double* tau,
 
 // apply H_j = I - tau v v^T (v_j = 1, v_i = X[i, j] below) to columns c0.. of Y (m rows, column-major)
 __global__ void __launch_bounds__(256) reflect_cols_kernel(const double* __restrict__ xc, const double* __restrict__ tau,
-                                                           double* y, int m, int j, int c0) {
+                                                           double* y, int m, int j, int c0, const uint64_t* cert) {
+  if (chol_certified(cert)) return;
   __shared__ double red[4];
   const double t = tau[j];
   if (t == 0.0) return;
@@ -232,67 +245,60 @@ __device__ inline void qr_block_sum(double (&v)[NV], double (*red)[kQrWaves * 64
   buf ^= 1;
 }
 
-// the reflector of panel column J (a template argument, so the register
-// panel is only indexed by constants), then its update of the panel columns
-// to its right; the same arithmetic as reflector_kernel + reflect_cols_kernel.
-// Row conditions are selects, not branches, to keep the unrolled panel short.
+// The reflector of panel column J (a template argument, so the register
+// panel is only indexed by constants) and its update of the panel columns to
+// its right, the same reflector as reflector_kernel + reflect_cols_kernel with
+// one workgroup reduction: the products of column J with itself and the
+// columns to its right below row gj, s_c = sum x_J x_c, give both the norm
+// (c = J) and, with row gj's entries y_c and v = [1; x_J scale],
+// v^T x_c = y_c + scale s_c.  (Two reductions, the second over the scaled
+// column: a 512 x 512 split's factorisation and the rest 0.7 ms slower, of
+// 25.3.)  Row conditions are selects, not branches, to keep the
+// unrolled panel short.
 template <int J>
-__device__ __forceinline__ void qr_panel_step(double (&x)[kQrRows][kQrNb], double (*red)[kQrWaves * 64], int& buf,
-                                              double* tau, int m, int j0, int nb) {
+__device__ __forceinline__ void qr_panel_step(double (&x)[kQrRows][kQrNb], double (*red)[kQrWaves * 64],
+                                              double (*top)[kQrNb], int& buf, double* tau, int m, int j0, int nb) {
   if constexpr (J < kQrNb) {
     if (J < nb) {
+      constexpr int NW = kQrNb - J;
       const int gj = j0 + J;
-      double s[2] = {0.0, 0.0};   // sigma (rows below gj), alpha (row gj)
+      double s[NW];
+#pragma unroll
+      for (int c = 0; c < NW; ++c) s[c] = 0.0;
 #pragma unroll
       for (int q = 0; q < kQrRows; ++q) {
         const int row = threadIdx.x + kQrThreads * q;
-        const double xv = x[q][J];
-        s[0] += (row > gj && row < m) ? xv * xv : 0.0;
-        s[1] += row == gj ? xv : 0.0;
+        const double xv = row > gj && row < m ? x[q][J] : 0.0;
+#pragma unroll
+        for (int c = 0; c < NW; ++c) s[c] += xv * x[q][J + c];
+        if (row == gj) {
+#pragma unroll
+          for (int c = 0; c < NW; ++c) top[buf][c] = x[q][J + c];
+        }
       }
-      qr_block_sum<2, 2>(s, red, buf);
-      const double sigma = s[0], alpha = s[1];
+      const int at = buf;
+      qr_block_sum<NW, (NW > 8 ? 16 : NW > 4 ? 8 : NW > 2 ? 4 : NW > 1 ? 2 : 1)>(s, red, buf);
+      const double sigma = s[0], alpha = top[at][0];
       double t = 0.0;
-      if (sigma != 0.0) {
+      if (sigma != 0.0) {   // the same in every thread
         const double beta = -copysign(sqrt(alpha * alpha + sigma), alpha);
         const double scale = 1.0 / (alpha - beta);
         t = (beta - alpha) / beta;
+        double w[NW];
+#pragma unroll
+        for (int c = 1; c < NW; ++c) w[c] = t * (top[at][c] + scale * s[c]);
 #pragma unroll
         for (int q = 0; q < kQrRows; ++q) {
           const int row = threadIdx.x + kQrThreads * q;
-          const double xv = x[q][J];
-          x[q][J] = (row > gj && row < m) ? xv * scale : (row == gj ? beta : xv);
+          const double v = row > gj && row < m ? x[q][J] * scale : (row == gj ? 1.0 : 0.0);
+          x[q][J] = row > gj && row < m ? v : (row == gj ? beta : x[q][J]);
+#pragma unroll
+          for (int c = 1; c < NW; ++c) x[q][J + c] -= w[c] * v;
         }
       }
       if (threadIdx.x == 0) tau[gj] = t;
-      if constexpr (J + 1 < kQrNb) {
-        // t is the same in every thread, so the barriers inside are reached by all
-        if (t != 0.0 && J + 1 < nb) {
-          constexpr int NW = kQrNb - J - 1;
-          double v[kQrRows];   // the reflector at this thread's rows: 1 at gj, X below, 0 above
-#pragma unroll
-          for (int q = 0; q < kQrRows; ++q) {
-            const int row = threadIdx.x + kQrThreads * q;
-            v[q] = (row > gj && row < m) ? x[q][J] : (row == gj ? 1.0 : 0.0);
-          }
-          double w[NW];
-#pragma unroll
-          for (int c = 0; c < NW; ++c) {
-            w[c] = 0.0;
-#pragma unroll
-            for (int q = 0; q < kQrRows; ++q) w[c] += v[q] * x[q][J + 1 + c];
-          }
-          qr_block_sum<NW, (NW > 8 ? 16 : NW > 4 ? 8 : NW > 2 ? 4 : NW > 1 ? 2 : 1)>(w, red, buf);
-#pragma unroll
-          for (int c = 0; c < NW; ++c) {
-            const double tw = t * w[c];
-#pragma unroll
-            for (int q = 0; q < kQrRows; ++q) x[q][J + 1 + c] -= tw * v[q];
-          }
-        }
-      }
     }
-    qr_panel_step<J + 1>(x, red, buf, tau, m, j0, nb);
+    qr_panel_step<J + 1>(x, red, top, buf, tau, m, j0, nb);
   }
 }
 
@@ -300,11 +306,16 @@ __device__ __forceinline__ void qr_panel_step(double (&x)[kQrRows][kQrNb], doubl
 // place, then form the panel's triangular factor (LAPACK larft, forward,
 // columnwise): H_0 ... H_{nb-1} = I - V T V^T with T[j][j] = tau_j and
 // T[0:j, j] = -tau_j T[0:j, 0:j] (V[:, 0:j]^T v_j); T row-major 16 x 16.
-__global__ void __launch_bounds__(kQrThreads) qr_panel_kernel(double* xc, double* tau, double* tf, int m, int j0,
-                                                              int nb) {
-  __shared__ double red[2][kQrWaves * 64];
-  __shared__ double gram[kQrNb * kQrNb];
-  __shared__ double tl[kQrNb * kQrNb];
+struct QrPanelSmem {
+  double red[2][kQrWaves * 64];
+  double top[2][kQrNb];
+  double gram[kQrNb * kQrNb];
+  double tl[kQrNb * kQrNb];
+};
+__device__ inline void qr_panel(double* xc, double* tau, double* tf, int m, int j0, int nb, QrPanelSmem& sm) {
+  auto& red = sm.red;
+  auto& gram = sm.gram;
+  auto& tl = sm.tl;
   int buf = 0;
   double x[kQrRows][kQrNb];
 #pragma unroll
@@ -313,7 +324,7 @@ __global__ void __launch_bounds__(kQrThreads) qr_panel_kernel(double* xc, double
 #pragma unroll
     for (int c = 0; c < kQrNb; ++c) x[q][c] = (row < m && c < nb) ? xc[(int64_t)(j0 + c) * m + row] : 0.0;
   }
-  qr_panel_step<0>(x, red, buf, tau, m, j0, nb);
+  qr_panel_step<0>(x, red, sm.top, buf, tau, m, j0, nb);
 #pragma unroll
   for (int q = 0; q < kQrRows; ++q) {
     const int row = threadIdx.x + kQrThreads * q;
@@ -405,26 +416,18 @@ __device__ inline void qr_load_v(const double* __restrict__ xc, int m, int j0, i
   }
 }
 
-// apply the panel j0 .. j0+nb-1 (reflectors in X, triangular factor T) to
-// columns c0 .. c0+ncols-1 of Y: Y -= V T^T (V^T Y) in the factorisation
-// (transpose = 1: H_{nb-1} ... H_0 Y), Y -= V T (V^T Y) for the accumulation
-// of Q (transpose = 0: H_0 ... H_{nb-1} Y)
-__global__ void __launch_bounds__(kQrThreads) qr_apply_kernel(const double* __restrict__ xc,
-                                                              const double* __restrict__ tf, double* y, int m, int j0,
-                                                              int nb, int c0, int ncols, int transpose) {
+// Y (this workgroup's kQrCb columns, thread t's rows t + 512 q in yv) times
+// the panel j0 .. j0+nb-1 (reflectors in X, triangular factor T):
+// Y -= V T^T (V^T Y) in the factorisation (transpose: H_{nb-1} ... H_0 Y),
+// Y -= V T (V^T Y) for products with Q (H_0 ... H_{nb-1} Y)
+struct QrApplySmem {
+  double red[kQrWaves * kQrNb * kQrCb];
+  double sw[kQrNb * kQrCb], sw2[kQrNb * kQrCb], st[kQrNb * kQrNb];
+};
+__device__ inline void qr_apply(const double* __restrict__ xc, const double* __restrict__ tf, int m, int j0, int nb,
+                                bool transpose, double (&yv)[kQrRows][kQrCb], QrApplySmem& sm) {
   constexpr int NW = kQrNb * kQrCb;   // 64 entries of W = V^T Y
-  __shared__ double red[kQrWaves * NW];
-  __shared__ double sw[NW], sw2[NW], st[kQrNb * kQrNb];
-  for (int e = threadIdx.x; e < kQrNb * kQrNb; e += kQrThreads) st[e] = tf[(j0 / kQrNb) * kQrNb * kQrNb + e];
-  const int cb0 = c0 + blockIdx.x * kQrCb;
-  double yv[kQrRows][kQrCb];
-#pragma unroll
-  for (int q = 0; q < kQrRows; ++q) {
-    const int row = threadIdx.x + kQrThreads * q;
-#pragma unroll
-    for (int c = 0; c < kQrCb; ++c)
-      yv[q][c] = (row < m && cb0 + c < c0 + ncols) ? y[(int64_t)(cb0 + c) * m + row] : 0.0;
-  }
+  for (int e = threadIdx.x; e < kQrNb * kQrNb; e += kQrThreads) sm.st[e] = tf[(j0 / kQrNb) * kQrNb * kQrNb + e];
   double w[NW];
 #pragma unroll
   for (int j = 0; j < kQrNb; ++j) {
@@ -440,21 +443,22 @@ __global__ void __launch_bounds__(kQrThreads) qr_apply_kernel(const double* __re
   }
   const double r = qr_reduce_scatter<NW>(w);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  red[wave * NW + lane] = r;
+  sm.red[wave * NW + lane] = r;
   __syncthreads();
   if (threadIdx.x < NW) {
     double t = 0.0;
 #pragma unroll
-    for (int wv = 0; wv < kQrWaves; ++wv) t += red[wv * NW + threadIdx.x];
-    sw[threadIdx.x] = t;
+    for (int wv = 0; wv < kQrWaves; ++wv) t += sm.red[wv * NW + threadIdx.x];
+    sm.sw[threadIdx.x] = t;
   }
   __syncthreads();
   if (threadIdx.x < NW) {
     const int j = threadIdx.x / kQrCb, c = threadIdx.x % kQrCb;
     double t = 0.0;
 #pragma unroll
-    for (int l = 0; l < kQrNb; ++l) t += (transpose ? st[l * kQrNb + j] : st[j * kQrNb + l]) * sw[l * kQrCb + c];
-    sw2[threadIdx.x] = t;
+    for (int l = 0; l < kQrNb; ++l)
+      t += (transpose ? sm.st[l * kQrNb + j] : sm.st[j * kQrNb + l]) * sm.sw[l * kQrCb + c];
+    sm.sw2[threadIdx.x] = t;
   }
   __syncthreads();
 #pragma unroll 2
@@ -463,23 +467,138 @@ __global__ void __launch_bounds__(kQrThreads) qr_apply_kernel(const double* __re
     qr_load_v(xc, m, j0, nb, j, v);
 #pragma unroll
     for (int c = 0; c < kQrCb; ++c) {
-      const double w2 = sw2[j * kQrCb + c];
+      const double w2 = sm.sw2[j * kQrCb + c];
 #pragma unroll
       for (int q = 0; q < kQrRows; ++q) yv[q][c] -= v[q] * w2;
     }
   }
+}
+
+__device__ inline void qr_load_y(const double* y, int m, int cb0, int ncols, double (&yv)[kQrRows][kQrCb]) {
+#pragma unroll
+  for (int q = 0; q < kQrRows; ++q) {
+    const int row = threadIdx.x + kQrThreads * q;
+#pragma unroll
+    for (int c = 0; c < kQrCb; ++c) yv[q][c] = (row < m && cb0 + c < ncols) ? y[(int64_t)(cb0 + c) * m + row] : 0.0;
+  }
+}
+__device__ inline void qr_store_y(double* y, int m, int cb0, int ncols, const double (&yv)[kQrRows][kQrCb]) {
 #pragma unroll
   for (int q = 0; q < kQrRows; ++q) {
     const int row = threadIdx.x + kQrThreads * q;
     if (row < m) {
 #pragma unroll
       for (int c = 0; c < kQrCb; ++c)
-        if (cb0 + c < c0 + ncols) y[(int64_t)(cb0 + c) * m + row] = yv[q][c];
+        if (cb0 + c < ncols) y[(int64_t)(cb0 + c) * m + row] = yv[q][c];
     }
   }
 }
 
-__global__ void eye_kernel(double* qc, int m, int n) {
+// The whole factorisation in one launch.  Its tasks are the panels and the
+// applications of a panel to a group of kQrCb columns; workgroups take them
+// from a counter in an order in which every task comes after those it needs:
+//   panel 0; then for p = 0, 1, ...: apply p to the columns of panel p + 1,
+//   panel p + 1, apply p to the other columns
+// so that the next panel runs while the last one is still being applied.  A
+// workgroup that waits does so for tasks with smaller numbers, which running
+// workgroups have taken; the one with the smallest number never waits, so
+// every wait ends whatever share of the grid is resident.
+// ctr: the task counter, the number of finished panels, and per column group
+// the number of panels applied to it (zero at the start).
+__host__ __device__ inline int qr_groups(int n) { return (n + kQrCb - 1) / kQrCb; }
+
+__device__ inline void qr_wait(const uint32_t* flag, uint32_t want) {
+  if (threadIdx.x == 0)
+    while (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < want) __builtin_amdgcn_s_sleep(4);
+}
+__device__ inline void qr_acquire() {
+  __syncthreads();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+}
+__device__ inline void qr_signal(uint32_t* flag, uint32_t value) {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_store(flag, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__global__ void __launch_bounds__(kQrThreads) qr_factor_kernel(double* xc, double* tau, double* tf, int m, int n,
+                                                               uint32_t* ctr, const uint64_t* cert) {
+  if (chol_certified(cert)) return;
+  __shared__ union {
+    QrPanelSmem panel;
+    QrApplySmem apply;
+  } sm;
+  __shared__ int s_task;
+  const int groups = qr_groups(n), panels = (n + kQrNb - 1) / kQrNb;
+  constexpr int GP = kQrNb / kQrCb;   // column groups a panel
+  uint32_t* done = ctr + 1;
+  uint32_t* applied = ctr + 2;
+  // tasks base .. base + size - 1: panel p's applications and panel p + 1
+  int p = -1, base = 0, size = 1;
+  for (;;) {
+    __syncthreads();
+    if (threadIdx.x == 0) s_task = (int)atomicAdd(ctr, 1u);
+    __syncthreads();
+    const int task = s_task;
+    while (p < panels && task >= base + size) {
+      base += size;
+      ++p;
+      const int ng = groups - GP * (p + 1);
+      size = p >= panels ? 0 : (ng > 0 ? ng : 0) + (p + 1 < panels ? 1 : 0);
+    }
+    if (p >= panels) return;
+    const int local = task - base, ng = p < 0 ? 0 : groups - GP * (p + 1), first = ng < GP ? ng : GP;
+    if (local == first) {   // panel p + 1
+      const int q = p + 1, j0 = q * kQrNb;
+      for (int g = GP * q; q > 0 && g < GP * (q + 1) && g < groups; ++g) qr_wait(applied + g, (uint32_t)q);
+      qr_acquire();
+      qr_panel(xc, tau, tf, m, j0, n - j0 < kQrNb ? n - j0 : kQrNb, sm.panel);
+      qr_signal(done, (uint32_t)(q + 1));
+    } else {
+      const int g = GP * (p + 1) + local - (local > first ? 1 : 0), j0 = p * kQrNb;
+      qr_wait(done, (uint32_t)(p + 1));
+      qr_wait(applied + g, (uint32_t)p);
+      qr_acquire();
+      double yv[kQrRows][kQrCb];
+      qr_load_y(xc, m, g * kQrCb, n, yv);
+      qr_apply(xc, tf, m, j0, n - j0 < kQrNb ? n - j0 : kQrNb, true, yv, sm.apply);
+      qr_store_y(xc, m, g * kQrCb, n, yv);
+      qr_signal(applied + g, (uint32_t)(p + 1));
+    }
+  }
+}
+
+// Y := Q Y (eye: Y = Q [I; 0]), kQrCb columns a workgroup, all panels from the
+// last (eye: from the first that reaches the columns) with Y in registers
+__global__ void __launch_bounds__(kQrThreads) qr_form_kernel(const double* __restrict__ xc, const double* __restrict__ tf,
+                                                             double* y, int m, int n, int ncols, bool eye,
+                                                             const uint64_t* cert) {
+  if (chol_certified(cert)) return;
+  __shared__ QrApplySmem sm;
+  const int cb0 = blockIdx.x * kQrCb;
+  double yv[kQrRows][kQrCb];
+  if (eye) {
+#pragma unroll
+    for (int q = 0; q < kQrRows; ++q)
+#pragma unroll
+      for (int c = 0; c < kQrCb; ++c) yv[q][c] = (int)threadIdx.x + kQrThreads * q == cb0 + c ? 1.0 : 0.0;
+  } else {
+    qr_load_y(y, m, cb0, ncols, yv);
+  }
+  const int last = (n - 1) / kQrNb;
+  for (int p = eye ? min(last, cb0 / kQrNb) : last; p >= 0; --p) {
+    __syncthreads();
+    qr_apply(xc, tf, m, p * kQrNb, min(kQrNb, n - p * kQrNb), false, yv, sm);
+  }
+  qr_store_y(y, m, cb0, ncols, yv);
+}
+
+__global__ void qr_reset_kernel(uint32_t* ctr, int words) {
+  for (int i = threadIdx.x; i < words; i += blockDim.x) ctr[i] = 0;
+}
+
+__global__ void eye_kernel(double* qc, int m, int n, const uint64_t* cert) {
+  if (chol_certified(cert)) return;
   const int64_t total = (int64_t)m * n;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
     int64_t c = e / m, i = e - c * m;
@@ -490,7 +609,8 @@ __global__ void eye_kernel(double* qc, int m, int n) {
 // site[i, s, b] = Q[(i d + s), b] * sign(R[b, b]);  R_next[r, c] = sign(R[r, r]) * R[r, c] (upper)
 // Q with column signs so that diag(R) >= 0, written over the site
 __global__ void finalize_q_kernel(const double* __restrict__ xc, const double* __restrict__ qc, double* site, int m,
-                                  int n) {
+                                  int n, const uint64_t* cert) {
+  if (chol_certified(cert)) return;
   const int64_t total = (int64_t)m * n;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
     int64_t row = e / n, b = e - row * n;   // row-major site index (row = i*d + s)
@@ -500,7 +620,8 @@ __global__ void finalize_q_kernel(const double* __restrict__ xc, const double* _
 }
 
 // R with row signs (diag(R) >= 0), row-major, for the next site's absorb
-__global__ void finalize_r_kernel(const double* __restrict__ xc, double* rnext, int m, int n) {
+__global__ void finalize_r_kernel(const double* __restrict__ xc, double* rnext, int m, int n, const uint64_t* cert) {
+  if (chol_certified(cert)) return;
   const int64_t tr = (int64_t)n * n;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < tr; e += (int64_t)gridDim.x * blockDim.x) {
     int64_t r = e / n, c = e - r * n;
@@ -529,32 +650,36 @@ static unsigned blocks_for(int64_t n) {
 // triangle, the reflectors below), T factors in tf; and the product Q y.
 bool householder_qr_fits(int64_t m) { return m <= (int64_t)kQrThreads * kQrRows; }
 
-size_t householder_tf_doubles(int64_t n) { return (size_t)((n + kQrNb - 1) / kQrNb) * kQrNb * kQrNb; }
+// the panels' T factors, then the task counters of the factorisation
+static size_t qr_tf_doubles(int64_t n) { return (size_t)((n + kQrNb - 1) / kQrNb) * kQrNb * kQrNb; }
+static size_t qr_ctr_words(int64_t n) { return 2 + (size_t)qr_groups((int)n); }
+size_t householder_tf_doubles(int64_t n) { return qr_tf_doubles(n) + (qr_ctr_words(n) + 1) / 2; }
+
+// as many workgroups as the widest application has column groups, one a compute unit
+static int qr_grid(int n) { return std::max(1, std::min(256, qr_groups(n))); }
 
 int32_t householder_qr(double* xc, int m, int n, double* tau, double* tf, hipStream_t st) {
-  for (int j0 = 0; j0 < n; j0 += kQrNb) {
-    const int nb = std::min(kQrNb, n - j0);
-    hipLaunchKernelGGL(qr_panel_kernel, dim3(1), dim3(kQrThreads), 0, st, xc, tau, tf, m, j0, nb);
-    const int rest = n - j0 - nb;
-    if (rest > 0)
-      hipLaunchKernelGGL(qr_apply_kernel, dim3((unsigned)((rest + kQrCb - 1) / kQrCb)), dim3(kQrThreads), 0, st, xc, tf,
-                         xc, m, j0, nb, j0 + nb, rest, 1);
-  }
+  uint32_t* ctr = reinterpret_cast<uint32_t*>(tf + qr_tf_doubles(n));
+  hipLaunchKernelGGL(qr_reset_kernel, dim3(1), dim3(256), 0, st, ctr, (int)qr_ctr_words(n));
+  hipLaunchKernelGGL(qr_factor_kernel, dim3((unsigned)qr_grid(n)), dim3(kQrThreads), 0, st, xc, tau, tf, m, n, ctr,
+                     (const uint64_t*)nullptr);
   return hip_check(hipGetLastError(), "householder qr");
 }
 
 // y (m x ncols, column-major) := Q y, the panels applied last to first
 int32_t householder_apply_q(const double* xc, int m, int n, const double* tf, double* y, int ncols, hipStream_t st) {
-  for (int j0 = (n - 1) / kQrNb * kQrNb; j0 >= 0; j0 -= kQrNb) {
-    const int nb = std::min(kQrNb, n - j0);
-    hipLaunchKernelGGL(qr_apply_kernel, dim3((unsigned)((ncols + kQrCb - 1) / kQrCb)), dim3(kQrThreads), 0, st, xc, tf,
-                       y, m, j0, nb, 0, ncols, 0);
-  }
+  hipLaunchKernelGGL(qr_form_kernel, dim3((unsigned)qr_groups(ncols)), dim3(kQrThreads), 0, st, xc, tf, y, m, n, ncols,
+                     false, (const uint64_t*)nullptr);
   return hip_check(hipGetLastError(), "householder apply");
 }
 
+// Sites of at least this many columns are factorised by Cholesky first
+// (cholqr.hip); below, the two panels of Householder cost less than its ten
+// launches.
+constexpr int kCholMin = 32;
+
 struct QrLayout {
-  size_t x[2], q[2], r, tau, tf[2], total;
+  size_t x[2], q[2], r, tau, tf[2], g, r1, u[2], linv, ebits, total;
 };
 
 static int32_t qr_check(int32_t n, const tn_tensor* sites, QrLayout& L) {
@@ -584,12 +709,21 @@ static int32_t qr_check(int32_t n, const tn_tensor* sites, QrLayout& L) {
     L.q[h] = o;
     o += al256(mx * 8);
     L.tf[h] = o;
-    o += al256((4096 / kQrNb) * kQrNb * kQrNb * 8);
+    o += al256(householder_tf_doubles(4096) * 8);
   }
   L.r = o;
   o += al256(std::max<int64_t>(mr, 1) * 8);
   L.tau = o;
   o += al256(4096 * 8);
+  // Cholesky path: the Gram matrix, R1, U and the certificate per set
+  for (size_t* p : {&L.g, &L.r1, &L.u[0], &L.u[1]}) {
+    *p = o;
+    o += al256(std::max<int64_t>(mr, 1) * 8);
+  }
+  L.linv = o;
+  o += al256(kCholLinv * 8);
+  L.ebits = o;
+  o += al256(2 * 8);
   L.total = o;
   int64_t maxn = 1;
   for (int k = 0; k < n; ++k) maxn = std::max(maxn, sites[k].shape[2]);
@@ -651,25 +785,33 @@ int32_t tn_mps_left_canonicalize(int32_t n_sites, tn_tensor* sites, double* logn
     const int m = dk * d, n = dn;
     double* a = static_cast<double*>(sites[k].data);
     hipStreamWaitEvent(st, ev_q[h], 0);   // site k-2's Q no longer reads this set
+    // Cholesky first: the site's X and Q1 take the places of the Householder
+    // path's, which then forms its own X again, or leaves at once where the
+    // certificate holds
+    uint64_t* cert = nullptr;
+    double* u = reinterpret_cast<double*>(ws + L.u[h]);
+    if (n >= kCholMin && (int64_t)m * n < (1 << 28)) {
+      cert = reinterpret_cast<uint64_t*>(ws + L.ebits) + h;
+      rc = chol_absorb(r, a, xc, dk, d * dn, st);
+      if (rc == TN_OK)
+        rc = chol_qr(xc, m, n, reinterpret_cast<double*>(ws + L.g), reinterpret_cast<double*>(ws + L.r1), u, qc,
+                     reinterpret_cast<double*>(ws + L.linv), cert, r, st);
+      if (rc != TN_OK) break;
+    }
     dim3 g((unsigned)((d * dn + 63) / 64), (unsigned)((dk + 63) / 64));
-    hipLaunchKernelGGL(absorb_kernel, g, dim3(256), 0, st, r, a, xc, dk, d, dn);
+    hipLaunchKernelGGL(absorb_kernel, g, dim3(256), 0, st, r, a, xc, dk, d, dn,
+                       reinterpret_cast<uint32_t*>(tf + qr_tf_doubles(n)), (int)qr_ctr_words(n), cert);
     const bool blocked = m <= kQrThreads * kQrRows;
     if (blocked) {
-      for (int j0 = 0; j0 < n; j0 += kQrNb) {
-        const int nb = std::min(kQrNb, n - j0);
-        hipLaunchKernelGGL(qr_panel_kernel, dim3(1), dim3(kQrThreads), 0, st, xc, tau, tf, m, j0, nb);
-        const int rest = n - j0 - nb;
-        if (rest > 0)
-          hipLaunchKernelGGL(qr_apply_kernel, dim3((unsigned)((rest + kQrCb - 1) / kQrCb)), dim3(kQrThreads), 0, st, xc,
-                             tf, xc, m, j0, nb, j0 + nb, rest, 1);
-      }
+      hipLaunchKernelGGL(qr_factor_kernel, dim3((unsigned)qr_grid(n)), dim3(kQrThreads), 0, st, xc, tau, tf, m, n,
+                         reinterpret_cast<uint32_t*>(tf + qr_tf_doubles(n)), cert);
     } else {
       for (int j = 0; j < n; ++j) {
-        hipLaunchKernelGGL(reflector_kernel, dim3(1), dim3(256), 0, st, xc, tau, m, j);
-        if (j + 1 < n) hipLaunchKernelGGL(reflect_cols_kernel, dim3(n - j - 1), dim3(256), 0, st, xc, tau, xc, m, j, j + 1);
+        hipLaunchKernelGGL(reflector_kernel, dim3(1), dim3(256), 0, st, xc, tau, m, j, cert);
+        if (j + 1 < n) hipLaunchKernelGGL(reflect_cols_kernel, dim3(n - j - 1), dim3(256), 0, st, xc, tau, xc, m, j, j + 1, cert);
       }
     }
-    hipLaunchKernelGGL(finalize_r_kernel, dim3(blocks_for((int64_t)n * n)), dim3(256), 0, st, xc, r, m, n);
+    hipLaunchKernelGGL(finalize_r_kernel, dim3(blocks_for((int64_t)n * n)), dim3(256), 0, st, xc, r, m, n, cert);
     // Q: on the side stream for the blocked path; the column path's Q needs
     // tau, which the next site overwrites, so it stays on the caller's stream
     hipStream_t qs = blocked ? side : st;
@@ -677,18 +819,17 @@ int32_t tn_mps_left_canonicalize(int32_t n_sites, tn_tensor* sites, double* logn
       hipEventRecord(ev_fact, st);
       hipStreamWaitEvent(side, ev_fact, 0);
     }
-    hipLaunchKernelGGL(eye_kernel, dim3(blocks_for((int64_t)m * n)), dim3(256), 0, qs, qc, m, n);
+    if (cert) rc = chol_q(qc, u, a, m, n, cert, qs);
+    if (rc != TN_OK) break;
     if (blocked) {
-      for (int j0 = (n - 1) / kQrNb * kQrNb; j0 >= 0; j0 -= kQrNb) {
-        const int nb = std::min(kQrNb, n - j0);
-        hipLaunchKernelGGL(qr_apply_kernel, dim3((unsigned)((n - j0 + kQrCb - 1) / kQrCb)), dim3(kQrThreads), 0, qs, xc,
-                           tf, qc, m, j0, nb, j0, n - j0, 0);
-      }
+      hipLaunchKernelGGL(qr_form_kernel, dim3((unsigned)qr_groups(n)), dim3(kQrThreads), 0, qs, xc, tf, qc, m, n, n, true,
+                         cert);
     } else {
+      hipLaunchKernelGGL(eye_kernel, dim3(blocks_for((int64_t)m * n)), dim3(256), 0, qs, qc, m, n, cert);
       for (int j = n - 1; j >= 0; --j)
-        hipLaunchKernelGGL(reflect_cols_kernel, dim3(n - j), dim3(256), 0, qs, xc, tau, qc, m, j, j);
+        hipLaunchKernelGGL(reflect_cols_kernel, dim3(n - j), dim3(256), 0, qs, xc, tau, qc, m, j, j, cert);
     }
-    hipLaunchKernelGGL(finalize_q_kernel, dim3(blocks_for((int64_t)m * n)), dim3(256), 0, qs, xc, qc, a, m, n);
+    hipLaunchKernelGGL(finalize_q_kernel, dim3(blocks_for((int64_t)m * n)), dim3(256), 0, qs, xc, qc, a, m, n, cert);
     hipEventRecord(ev_q[h], qs);
     rc = hip_check(hipGetLastError(), "canonicalize");
   }
