@@ -53,7 +53,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t chol_rsrc(const double* p) {
 // doubles so that the four k that a matrix-core operand reads fall into both
 // halves of the banks.  A stage's products take 0.2 us, a load a few times
 // that: four stages are in flight in registers (1024 x 1024 over 2048: one in
-// flight 131 us, four 109).
+// flight 131 us, four 70).
 template <int OP>
 __global__ void __launch_bounds__(256) chol_gemm_kernel(const CholGemm p) {
   constexpr bool TN = OP == C_GRAM || OP == C_DEFECT;   // A stored k x m

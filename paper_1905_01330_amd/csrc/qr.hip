@@ -255,9 +255,9 @@ __device__ inline void qr_block_sum(double (&v)[NV], double (*red)[kQrWaves * 64
 // column: a 512 x 512 split's factorisation and the rest 0.7 ms slower, of
 // 25.3.)  Row conditions are selects, not branches, to keep the
 // unrolled panel short.
-template <int J>
-__device__ __forceinline__ void qr_panel_step(double (&x)[kQrRows][kQrNb], double (*red)[kQrWaves * 64],
-                                              double (*top)[kQrNb], int& buf, double* tau, int m, int j0, int nb) {
+template <int J, int NR>
+__device__ __forceinline__ void qr_panel_step(double (&x)[NR][kQrNb], double (*red)[kQrWaves * 64],
+                                              double (*top)[kQrNb], int& buf, double* tau, int m, int r0, int j0, int nb) {
   if constexpr (J < kQrNb) {
     if (J < nb) {
       constexpr int NW = kQrNb - J;
@@ -266,8 +266,8 @@ __device__ __forceinline__ void qr_panel_step(double (&x)[kQrRows][kQrNb], doubl
 #pragma unroll
       for (int c = 0; c < NW; ++c) s[c] = 0.0;
 #pragma unroll
-      for (int q = 0; q < kQrRows; ++q) {
-        const int row = threadIdx.x + kQrThreads * q;
+      for (int q = 0; q < NR; ++q) {
+        const int row = r0 + threadIdx.x + kQrThreads * q;
         const double xv = row > gj && row < m ? x[q][J] : 0.0;
 #pragma unroll
         for (int c = 0; c < NW; ++c) s[c] += xv * x[q][J + c];
@@ -288,8 +288,8 @@ __device__ __forceinline__ void qr_panel_step(double (&x)[kQrRows][kQrNb], doubl
 #pragma unroll
         for (int c = 1; c < NW; ++c) w[c] = t * (top[at][c] + scale * s[c]);
 #pragma unroll
-        for (int q = 0; q < kQrRows; ++q) {
-          const int row = threadIdx.x + kQrThreads * q;
+        for (int q = 0; q < NR; ++q) {
+          const int row = r0 + threadIdx.x + kQrThreads * q;
           const double v = row > gj && row < m ? x[q][J] * scale : (row == gj ? 1.0 : 0.0);
           x[q][J] = row > gj && row < m ? v : (row == gj ? beta : x[q][J]);
 #pragma unroll
@@ -298,7 +298,7 @@ __device__ __forceinline__ void qr_panel_step(double (&x)[kQrRows][kQrNb], doubl
       }
       if (threadIdx.x == 0) tau[gj] = t;
     }
-    qr_panel_step<J + 1>(x, red, top, buf, tau, m, j0, nb);
+    qr_panel_step<J + 1, NR>(x, red, top, buf, tau, m, r0, j0, nb);
   }
 }
 
@@ -312,22 +312,24 @@ struct QrPanelSmem {
   double gram[kQrNb * kQrNb];
   double tl[kQrNb * kQrNb];
 };
+template <int NR>
 __device__ inline void qr_panel(double* xc, double* tau, double* tf, int m, int j0, int nb, QrPanelSmem& sm) {
   auto& red = sm.red;
   auto& gram = sm.gram;
   auto& tl = sm.tl;
+  const int r0 = j0;   // rows above the panel's first are done
   int buf = 0;
-  double x[kQrRows][kQrNb];
+  double x[NR][kQrNb];
 #pragma unroll
-  for (int q = 0; q < kQrRows; ++q) {
-    const int row = threadIdx.x + kQrThreads * q;
+  for (int q = 0; q < NR; ++q) {
+    const int row = r0 + threadIdx.x + kQrThreads * q;
 #pragma unroll
     for (int c = 0; c < kQrNb; ++c) x[q][c] = (row < m && c < nb) ? xc[(int64_t)(j0 + c) * m + row] : 0.0;
   }
-  qr_panel_step<0>(x, red, sm.top, buf, tau, m, j0, nb);
+  qr_panel_step<0, NR>(x, red, sm.top, buf, tau, m, r0, j0, nb);
 #pragma unroll
-  for (int q = 0; q < kQrRows; ++q) {
-    const int row = threadIdx.x + kQrThreads * q;
+  for (int q = 0; q < NR; ++q) {
+    const int row = r0 + threadIdx.x + kQrThreads * q;
     if (row < m) {
 #pragma unroll
       for (int c = 0; c < kQrNb; ++c)
@@ -337,8 +339,8 @@ __device__ inline void qr_panel(double* xc, double* tau, double* tf, int m, int 
   // the reflectors in place of the panel: v_c is 1 at row j0 + c, X below it,
   // 0 above (and 0 in the columns past nb)
 #pragma unroll
-  for (int q = 0; q < kQrRows; ++q) {
-    const int row = threadIdx.x + kQrThreads * q;
+  for (int q = 0; q < NR; ++q) {
+    const int row = r0 + threadIdx.x + kQrThreads * q;
 #pragma unroll
     for (int c = 0; c < kQrNb; ++c) {
       const int gc = j0 + c;
@@ -365,7 +367,7 @@ __device__ inline void qr_panel(double* xc, double* tau, double* tf, int m, int 
           }
         const int i = pp - base;
 #pragma unroll
-        for (int q = 0; q < kQrRows; ++q) g[p] += x[q][i] * x[q][j];
+        for (int q = 0; q < NR; ++q) g[p] += x[q][i] * x[q][j];
       }
     }
     const double v = qr_reduce_scatter<16>(g);
@@ -406,17 +408,18 @@ __device__ inline void qr_panel(double* xc, double* tau, double* tf, int m, int 
   for (int e = threadIdx.x; e < kQrNb * kQrNb; e += kQrThreads) tf[(j0 / kQrNb) * kQrNb * kQrNb + e] = tl[e];
 }
 
-// reflector j of the panel at this thread's rows: 1 at row j0+j, X below, 0 above
-__device__ inline void qr_load_v(const double* __restrict__ xc, int m, int j0, int nb, int j, double (&v)[kQrRows]) {
+// reflector j of the panel at this thread's rows (from r0 on): 1 at row j0+j, X below, 0 above
+template <int NR>
+__device__ inline void qr_load_v(const double* __restrict__ xc, int m, int r0, int j0, int nb, int j, double (&v)[NR]) {
   const int gj = j0 + j;
 #pragma unroll
-  for (int q = 0; q < kQrRows; ++q) {
-    const int row = threadIdx.x + kQrThreads * q;
+  for (int q = 0; q < NR; ++q) {
+    const int row = r0 + threadIdx.x + kQrThreads * q;
     v[q] = j >= nb ? 0.0 : (row == gj ? 1.0 : ((row > gj && row < m) ? xc[(int64_t)gj * m + row] : 0.0));
   }
 }
 
-// Y (this workgroup's kQrCb columns, thread t's rows t + 512 q in yv) times
+// Y (this workgroup's kQrCb columns, thread t's rows r0 + t + 512 q in yv) times
 // the panel j0 .. j0+nb-1 (reflectors in X, triangular factor T):
 // Y -= V T^T (V^T Y) in the factorisation (transpose: H_{nb-1} ... H_0 Y),
 // Y -= V T (V^T Y) for products with Q (H_0 ... H_{nb-1} Y)
@@ -424,20 +427,21 @@ struct QrApplySmem {
   double red[kQrWaves * kQrNb * kQrCb];
   double sw[kQrNb * kQrCb], sw2[kQrNb * kQrCb], st[kQrNb * kQrNb];
 };
-__device__ inline void qr_apply(const double* __restrict__ xc, const double* __restrict__ tf, int m, int j0, int nb,
-                                bool transpose, double (&yv)[kQrRows][kQrCb], QrApplySmem& sm) {
+template <int NR>
+__device__ inline void qr_apply(const double* __restrict__ xc, const double* __restrict__ tf, int m, int r0, int j0, int nb,
+                                bool transpose, double (&yv)[NR][kQrCb], QrApplySmem& sm) {
   constexpr int NW = kQrNb * kQrCb;   // 64 entries of W = V^T Y
   for (int e = threadIdx.x; e < kQrNb * kQrNb; e += kQrThreads) sm.st[e] = tf[(j0 / kQrNb) * kQrNb * kQrNb + e];
   double w[NW];
 #pragma unroll
   for (int j = 0; j < kQrNb; ++j) {
-    double v[kQrRows];
-    qr_load_v(xc, m, j0, nb, j, v);
+    double v[NR];
+    qr_load_v(xc, m, r0, j0, nb, j, v);
 #pragma unroll
     for (int c = 0; c < kQrCb; ++c) {
       double s = 0.0;
 #pragma unroll
-      for (int q = 0; q < kQrRows; ++q) s += v[q] * yv[q][c];
+      for (int q = 0; q < NR; ++q) s += v[q] * yv[q][c];
       w[j * kQrCb + c] = s;
     }
   }
@@ -463,35 +467,46 @@ __device__ inline void qr_apply(const double* __restrict__ xc, const double* __r
   __syncthreads();
 #pragma unroll 2
   for (int j = 0; j < kQrNb; ++j) {
-    double v[kQrRows];
-    qr_load_v(xc, m, j0, nb, j, v);
+    double v[NR];
+    qr_load_v(xc, m, r0, j0, nb, j, v);
 #pragma unroll
     for (int c = 0; c < kQrCb; ++c) {
       const double w2 = sm.sw2[j * kQrCb + c];
 #pragma unroll
-      for (int q = 0; q < kQrRows; ++q) yv[q][c] -= v[q] * w2;
+      for (int q = 0; q < NR; ++q) yv[q][c] -= v[q] * w2;
     }
   }
 }
 
-__device__ inline void qr_load_y(const double* y, int m, int cb0, int ncols, double (&yv)[kQrRows][kQrCb]) {
+template <int NR>
+__device__ inline void qr_load_y(const double* y, int m, int r0, int cb0, int ncols, double (&yv)[NR][kQrCb]) {
 #pragma unroll
-  for (int q = 0; q < kQrRows; ++q) {
-    const int row = threadIdx.x + kQrThreads * q;
+  for (int q = 0; q < NR; ++q) {
+    const int row = r0 + threadIdx.x + kQrThreads * q;
 #pragma unroll
     for (int c = 0; c < kQrCb; ++c) yv[q][c] = (row < m && cb0 + c < ncols) ? y[(int64_t)(cb0 + c) * m + row] : 0.0;
   }
 }
-__device__ inline void qr_store_y(double* y, int m, int cb0, int ncols, const double (&yv)[kQrRows][kQrCb]) {
+template <int NR>
+__device__ inline void qr_store_y(double* y, int m, int r0, int cb0, int ncols, const double (&yv)[NR][kQrCb]) {
 #pragma unroll
-  for (int q = 0; q < kQrRows; ++q) {
-    const int row = threadIdx.x + kQrThreads * q;
+  for (int q = 0; q < NR; ++q) {
+    const int row = r0 + threadIdx.x + kQrThreads * q;
     if (row < m) {
 #pragma unroll
       for (int c = 0; c < kQrCb; ++c)
         if (cb0 + c < ncols) y[(int64_t)(cb0 + c) * m + row] = yv[q][c];
     }
   }
+}
+
+// panel j0 of X applied to X's columns cb0 .. of its group
+template <int NR>
+__device__ inline void qr_update(double* xc, const double* tf, int m, int j0, int nb, int cb0, int n, QrApplySmem& sm) {
+  double yv[NR][kQrCb];
+  qr_load_y<NR>(xc, m, j0, cb0, n, yv);
+  qr_apply<NR>(xc, tf, m, j0, j0, nb, true, yv, sm);
+  qr_store_y<NR>(xc, m, j0, cb0, n, yv);
 }
 
 // The whole factorisation in one launch.  Its tasks are the panels and the
@@ -552,17 +567,20 @@ __global__ void __launch_bounds__(kQrThreads) qr_factor_kernel(double* xc, doubl
       const int q = p + 1, j0 = q * kQrNb;
       for (int g = GP * q; q > 0 && g < GP * (q + 1) && g < groups; ++g) qr_wait(applied + g, (uint32_t)q);
       qr_acquire();
-      qr_panel(xc, tau, tf, m, j0, n - j0 < kQrNb ? n - j0 : kQrNb, sm.panel);
+      const int nb = n - j0 < kQrNb ? n - j0 : kQrNb;
+      if (m - j0 <= kQrThreads) qr_panel<1>(xc, tau, tf, m, j0, nb, sm.panel);
+      else if (m - j0 <= 2 * kQrThreads) qr_panel<2>(xc, tau, tf, m, j0, nb, sm.panel);
+      else qr_panel<kQrRows>(xc, tau, tf, m, j0, nb, sm.panel);
       qr_signal(done, (uint32_t)(q + 1));
     } else {
       const int g = GP * (p + 1) + local - (local > first ? 1 : 0), j0 = p * kQrNb;
       qr_wait(done, (uint32_t)(p + 1));
       qr_wait(applied + g, (uint32_t)p);
       qr_acquire();
-      double yv[kQrRows][kQrCb];
-      qr_load_y(xc, m, g * kQrCb, n, yv);
-      qr_apply(xc, tf, m, j0, n - j0 < kQrNb ? n - j0 : kQrNb, true, yv, sm.apply);
-      qr_store_y(xc, m, g * kQrCb, n, yv);
+      const int nb = n - j0 < kQrNb ? n - j0 : kQrNb;
+      if (m - j0 <= kQrThreads) qr_update<1>(xc, tf, m, j0, nb, g * kQrCb, n, sm.apply);
+      else if (m - j0 <= 2 * kQrThreads) qr_update<2>(xc, tf, m, j0, nb, g * kQrCb, n, sm.apply);
+      else qr_update<kQrRows>(xc, tf, m, j0, nb, g * kQrCb, n, sm.apply);
       qr_signal(applied + g, (uint32_t)(p + 1));
     }
   }
@@ -570,27 +588,28 @@ __global__ void __launch_bounds__(kQrThreads) qr_factor_kernel(double* xc, doubl
 
 // Y := Q Y (eye: Y = Q [I; 0]), kQrCb columns a workgroup, all panels from the
 // last (eye: from the first that reaches the columns) with Y in registers
+template <int NR>
 __global__ void __launch_bounds__(kQrThreads) qr_form_kernel(const double* __restrict__ xc, const double* __restrict__ tf,
                                                              double* y, int m, int n, int ncols, bool eye,
                                                              const uint64_t* cert) {
   if (chol_certified(cert)) return;
   __shared__ QrApplySmem sm;
   const int cb0 = blockIdx.x * kQrCb;
-  double yv[kQrRows][kQrCb];
+  double yv[NR][kQrCb];
   if (eye) {
 #pragma unroll
-    for (int q = 0; q < kQrRows; ++q)
+    for (int q = 0; q < NR; ++q)
 #pragma unroll
       for (int c = 0; c < kQrCb; ++c) yv[q][c] = (int)threadIdx.x + kQrThreads * q == cb0 + c ? 1.0 : 0.0;
   } else {
-    qr_load_y(y, m, cb0, ncols, yv);
+    qr_load_y<NR>(y, m, 0, cb0, ncols, yv);
   }
   const int last = (n - 1) / kQrNb;
   for (int p = eye ? min(last, cb0 / kQrNb) : last; p >= 0; --p) {
     __syncthreads();
-    qr_apply(xc, tf, m, p * kQrNb, min(kQrNb, n - p * kQrNb), false, yv, sm);
+    qr_apply<NR>(xc, tf, m, 0, p * kQrNb, min(kQrNb, n - p * kQrNb), false, yv, sm);
   }
-  qr_store_y(y, m, cb0, ncols, yv);
+  qr_store_y<NR>(y, m, 0, cb0, ncols, yv);
 }
 
 __global__ void qr_reset_kernel(uint32_t* ctr, int words) {
@@ -658,6 +677,17 @@ size_t householder_tf_doubles(int64_t n) { return qr_tf_doubles(n) + (qr_ctr_wor
 // as many workgroups as the widest application has column groups, one a compute unit
 static int qr_grid(int n) { return std::max(1, std::min(256, qr_groups(n))); }
 
+// Y := Q Y or Q [I; 0], the rows 1, 2 or 4 a thread as in the factorisation (a
+// panel's rows start at its first; with 4 a thread throughout, 512 x 512 took
+// 2.49 ms to factorise and 0.38 ms here, now 1.91 and 0.21)
+static void launch_form(const double* xc, const double* tf, double* y, int m, int n, int ncols, bool eye,
+                        const uint64_t* cert, hipStream_t st) {
+  const dim3 grid((unsigned)qr_groups(ncols)), blk(kQrThreads);
+  if (m <= kQrThreads) hipLaunchKernelGGL(qr_form_kernel<1>, grid, blk, 0, st, xc, tf, y, m, n, ncols, eye, cert);
+  else if (m <= 2 * kQrThreads) hipLaunchKernelGGL(qr_form_kernel<2>, grid, blk, 0, st, xc, tf, y, m, n, ncols, eye, cert);
+  else hipLaunchKernelGGL(qr_form_kernel<kQrRows>, grid, blk, 0, st, xc, tf, y, m, n, ncols, eye, cert);
+}
+
 int32_t householder_qr(double* xc, int m, int n, double* tau, double* tf, hipStream_t st) {
   uint32_t* ctr = reinterpret_cast<uint32_t*>(tf + qr_tf_doubles(n));
   hipLaunchKernelGGL(qr_reset_kernel, dim3(1), dim3(256), 0, st, ctr, (int)qr_ctr_words(n));
@@ -668,8 +698,7 @@ int32_t householder_qr(double* xc, int m, int n, double* tau, double* tf, hipStr
 
 // y (m x ncols, column-major) := Q y, the panels applied last to first
 int32_t householder_apply_q(const double* xc, int m, int n, const double* tf, double* y, int ncols, hipStream_t st) {
-  hipLaunchKernelGGL(qr_form_kernel, dim3((unsigned)qr_groups(ncols)), dim3(kQrThreads), 0, st, xc, tf, y, m, n, ncols,
-                     false, (const uint64_t*)nullptr);
+  launch_form(xc, tf, y, m, n, ncols, false, nullptr, st);
   return hip_check(hipGetLastError(), "householder apply");
 }
 
@@ -822,8 +851,7 @@ int32_t tn_mps_left_canonicalize(int32_t n_sites, tn_tensor* sites, double* logn
     if (cert) rc = chol_q(qc, u, a, m, n, cert, qs);
     if (rc != TN_OK) break;
     if (blocked) {
-      hipLaunchKernelGGL(qr_form_kernel, dim3((unsigned)qr_groups(n)), dim3(kQrThreads), 0, qs, xc, tf, qc, m, n, n, true,
-                         cert);
+      launch_form(xc, tf, qc, m, n, n, true, cert, qs);
     } else {
       hipLaunchKernelGGL(eye_kernel, dim3(blocks_for((int64_t)m * n)), dim3(256), 0, qs, qc, m, n, cert);
       for (int j = n - 1; j >= 0; --j)

@@ -31,12 +31,17 @@
 // similar size first cuts the sweeps needed on graded spectra by a third.
 // A pair whose columns are already orthogonal to the tolerance is left
 // alone; the host ends the sweeps when a sweep rotated no pair.
+//
+// From kGramMinCols columns on the sweeps rotate the Gram matrix of the
+// columns instead (jacobi.hip), to the same bound on the columns'
+// orthogonality; those above are for narrower nodes, for nodes whose matrices
+// do not fit that file's buffers, and in case it has not converged.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <vector>
 
-#include "internal.h"
+#include "jacobi.h"
 
 namespace tn {
 
@@ -49,6 +54,10 @@ constexpr int kRows = 64;       // rows staged per chunk
 constexpr int kMaxSweeps = 100;
 constexpr int kPrecondMinCols = 32;   // narrower nodes converge in a few sweeps anyway
 constexpr int kInnerSweeps = 14;
+// fewer columns are one or two block pairs of the kernels above: 24 x 24 takes
+// 0.56 ms with them; 32 x 32 0.68 against 0.77, 64 x 64 1.1 against 1.6
+constexpr int kGramMinCols = 32;
+constexpr int kGramSweeps = 30;       // sweeps on the Gram matrix before the columns' own take over
 
 // Strided matrix view of the node: element (i, j) at p + off(i over rows) + off(j over cols)
 struct MatView {
@@ -497,8 +506,6 @@ __global__ void __launch_bounds__(kNT) jacobi_lds_kernel(double* W, double* V, i
   }
 }
 
-__global__ void zero_int_kernel(int* p) { p[0] = 0; }
-
 // X (C x Cp, column-major) = R^T for the upper triangle R of the factorised
 // W (R x C, column-major): X[r, c] = R[c, r] for c <= r; zero above the
 // diagonal of X and in the padding columns
@@ -537,8 +544,9 @@ __global__ void svd_copy_kernel(const double* __restrict__ src, double* __restri
     dst[e] = src[e];
 }
 
-// sigma[c] = || W[:, c] ||_2, one 256-thread workgroup per column
-__global__ void column_norm_kernel(const double* W, int64_t R, double* sigma) {
+// sigma[c] = || W[:, c] ||_2, one 256-thread workgroup per column; *zero = 0 (if not null)
+__global__ void column_norm_kernel(const double* W, int64_t R, double* sigma, int* zero) {
+  if (zero && blockIdx.x == 0 && threadIdx.x == 0) *zero = 0;
   __shared__ double part[kNT];
   const int64_t c = blockIdx.x;
   double s = 0.0;
@@ -676,7 +684,9 @@ struct SvdGeom {
   bool lds;              // block pairs resident in LDS (one-sided rotations)
   int transposed;        // W = A^T
   bool precond;          // Jacobi on R^T from a Householder QR of W (see the decompose call)
-  size_t w_off, v_off, sigma_off, order_off, perm_off, ctl_off, x_off, t_off, tau_off, tf_off, total;
+  bool gram;             // sweeps on the Gram matrix first (jacobi.hip)
+  size_t w_off, v_off, sigma_off, order_off, perm_off, ctl_off, x_off, t_off, tau_off, tf_off, x2_off, v2_off, g_off,
+      total;
 };
 
 size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -725,6 +735,11 @@ int32_t svd_geometry(const tn_tensor* a, int32_t n_left, SvdGeom& g) {
   if (g.nb < 2) g.nb = 2;
   if (g.nb % 2) g.nb += 1;
   g.Cp = (int64_t)g.nb * g.kb;
+  g.gram = g.C >= kGramMinCols && jac_fits(jr, jac_padded(g.C));
+  if (g.gram) {   // whole block pairs of both kinds of sweep
+    g.Cp = jac_padded(g.C);
+    g.nb = (int)(g.Cp / g.kb);
+  }
   size_t o = 0;
   g.w_off = o;
   o += al256((size_t)g.R * g.Cp * 8);
@@ -750,6 +765,16 @@ int32_t svd_geometry(const tn_tensor* a, int32_t n_left, SvdGeom& g) {
     o += al256((size_t)g.C * 8);
     g.tf_off = o;
     o += al256(householder_tf_doubles(g.C) * 8);
+  }
+  // sweeps on the Gram matrix: the other copies of X (or W) and V, the scratch
+  g.x2_off = g.v2_off = g.g_off = o;
+  if (g.gram) {
+    g.x2_off = o;
+    o += al256((size_t)jr * g.Cp * 8);
+    g.v2_off = o;
+    o += al256((size_t)g.Cp * g.Cp * 8);
+    g.g_off = o;
+    o += al256(jac_scratch_doubles(g.Cp) * 8);
   }
   g.total = o;
   return TN_OK;
@@ -897,12 +922,40 @@ int32_t tn_split_node_decompose(const tn_tensor* a, int32_t n_left, int32_t max_
     // pairs count as orthogonal when |g_ij| <= tol sqrt(g_ii g_jj): a few
     // roundings of a dot product of length `rows`
     const double tol = 8.0 * std::sqrt((double)rows) * 2.220446049250313e-16;
+    auto rank_columns = [&](const double* m) {
+      hipLaunchKernelGGL(column_norm_kernel, dim3((unsigned)g.Cp), dim3(kNT), 0, st, m, rows, sigma, ctl);
+      hipLaunchKernelGGL(rank_kernel, dim3((unsigned)((g.Cp + 3) / 4)), dim3(256), 0, st, sigma, (int)g.Cp, perm);
+    };
+    if (g.gram) {
+      double* xs[2] = {M, reinterpret_cast<double*>(ws + g.x2_off)};
+      double* vs[2] = {V, reinterpret_cast<double*>(ws + g.v2_off)};
+      double* scratch = reinterpret_cast<double*>(ws + g.g_off);
+      int at = 0;
+      bool done = false;
+      while (!done && done_sweeps < kGramSweeps) {
+        rank_columns(xs[at]);
+        TN_TRY(jac_gram(xs[at], (int)rows, (int)g.Cp, sigma, perm, tol, scratch, ctl, st));
+        int pairs = 0;
+        TN_TRY(hip_check(hipMemcpyAsync(&pairs, ctl, sizeof(int), hipMemcpyDeviceToHost, st), "read sweep counter"));
+        TN_TRY(hip_check(hipStreamSynchronize(st), "sweep sync"));
+        ++done_sweeps;
+        done = pairs == 0;
+        if (done) break;
+        TN_TRY(jac_sweep(xs[at], vs[at], xs[at ^ 1], vs[at ^ 1], (int)rows, (int)g.Cp, perm, tol, scratch, st));
+        at ^= 1;
+      }
+      if (at) {
+        const auto blocks = [](int64_t n) { return dim3((unsigned)std::min<int64_t>((n + 255) / 256, 16384)); };
+        hipLaunchKernelGGL(svd_copy_kernel, blocks(rows * g.Cp), dim3(256), 0, st, xs[1], M, rows * g.Cp);
+        hipLaunchKernelGGL(svd_copy_kernel, blocks(g.Cp * g.Cp), dim3(256), 0, st, vs[1], V, g.Cp * g.Cp);
+        TN_TRY(hip_check(hipGetLastError(), "jacobi sweep"));
+      }
+      if (done) return TN_OK;
+    }
     for (int sw = 0; sw < kMaxSweeps; ++sw) {
       // columns in descending order of their norms: the blocks of a sweep then
       // pair columns of similar size first (fewer sweeps on graded spectra)
-      hipLaunchKernelGGL(column_norm_kernel, dim3((unsigned)g.Cp), dim3(kNT), 0, st, M, rows, sigma);
-      hipLaunchKernelGGL(rank_kernel, dim3((unsigned)((g.Cp + 3) / 4)), dim3(256), 0, st, sigma, (int)g.Cp, perm);
-      hipLaunchKernelGGL(zero_int_kernel, dim3(1), dim3(1), 0, st, ctl);
+      rank_columns(M);
       for (int r = 0; r < g.nb - 1; ++r) {
         const dim3 grid(g.nb / 2), blk(kNT);
         if (!g.lds)
@@ -920,7 +973,7 @@ int32_t tn_split_node_decompose(const tn_tensor* a, int32_t n_left, int32_t max_
       int rotated = 0;
       TN_TRY(hip_check(hipMemcpyAsync(&rotated, ctl, sizeof(int), hipMemcpyDeviceToHost, st), "read sweep counter"));
       TN_TRY(hip_check(hipStreamSynchronize(st), "sweep sync"));
-      done_sweeps = sw + 1;
+      ++done_sweeps;
       if (rotated == 0) break;
     }
     return TN_OK;
@@ -943,7 +996,7 @@ int32_t tn_split_node_decompose(const tn_tensor* a, int32_t n_left, int32_t max_
     hipLaunchKernelGGL(svd_x_from_r_kernel, dim3(gx), dim3(256), 0, st, W, g.R, g.C, g.Cp, X);
     TN_TRY(hip_check(hipGetLastError(), "svd precondition"));
     TN_TRY(sweep_until_done(X, g.C));
-    hipLaunchKernelGGL(column_norm_kernel, dim3((unsigned)g.Cp), dim3(kNT), 0, st, X, g.C, sigma);
+    hipLaunchKernelGGL(column_norm_kernel, dim3((unsigned)g.Cp), dim3(kNT), 0, st, X, g.C, sigma, (int*)nullptr);
     hipLaunchKernelGGL(svd_precond_t_kernel, dim3(gx), dim3(256), 0, st, V, sigma, g.R, g.C, g.Cp, T);
     hipLaunchKernelGGL(svd_precond_v_kernel, dim3(gx), dim3(256), 0, st, X, sigma, g.C, g.Cp, V);
     TN_TRY(hip_check(hipGetLastError(), "svd precondition"));
@@ -951,7 +1004,7 @@ int32_t tn_split_node_decompose(const tn_tensor* a, int32_t n_left, int32_t max_
     hipLaunchKernelGGL(svd_copy_kernel, dim3(gx), dim3(256), 0, st, T, W, g.R * g.Cp);
     TN_TRY(hip_check(hipGetLastError(), "svd precondition"));
   }
-  hipLaunchKernelGGL(column_norm_kernel, dim3((unsigned)g.Cp), dim3(kNT), 0, st, W, g.R, sigma);
+  hipLaunchKernelGGL(column_norm_kernel, dim3((unsigned)g.Cp), dim3(kNT), 0, st, W, g.R, sigma, (int*)nullptr);
   hipLaunchKernelGGL(rank_kernel, dim3((unsigned)((g.Cp + 3) / 4)), dim3(256), 0, st, sigma, (int)g.Cp, order);
   hipLaunchKernelGGL(truncate_kernel, dim3(1), dim3(64), 0, st, sigma, order, (int)g.C, max_singular_values,
                      max_truncation_err, ctl + 1);

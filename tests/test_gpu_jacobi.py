@@ -1,0 +1,91 @@
+"""The node split's sweeps on the Gram matrix at the sizes where they can go
+wrong: columns off and on the block pairs (32), the smallest that take them,
+rows on both sides of the preconditioning's limit, spectra that are graded,
+degenerate, of low rank or zero, scales near the ends of FP64's range.
+
+Gates: the columns count as orthogonal at |x_i . x_j| <= 8 sqrt(rows) eps |x_i|
+|x_j|, twice that for the vectors; values and the product to 1e-13 of the
+largest value (a thousand roundings of the up to 600 terms a value sums)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_1905_01330_amd as tn
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+EPS = np.finfo(np.float64).eps
+
+
+def check(a):
+    u, s, vt, _ = tn.split_node_full_svd(torch.tensor(a, device=DEV), [0], [1])
+    torch.cuda.synchronize()
+    u, s, vt = (x.cpu().numpy() for x in (u, s, vt))
+    s = np.diag(s) if s.ndim == 2 else s
+    ref = np.linalg.svd(a, compute_uv=False)
+    top = max(ref[0], np.finfo(np.float64).tiny)
+    assert np.abs(s - ref).max() <= 1e-13 * top
+    assert np.abs((u * s) @ vt - a).max() <= 1e-13 * top
+    # rank-deficient nodes: vectors of values at rounding level are not compared
+    big = s > 1e-12 * top
+    gate = 16 * np.sqrt(max(a.shape)) * EPS
+    for q in (u[:, big].T, vt[big]):
+        assert np.abs(q @ q.T - np.eye(int(big.sum()))).max(initial=0) <= gate
+
+
+def spectrum(m, n, s, seed):
+    rng = np.random.default_rng(seed)
+    u = np.linalg.qr(rng.standard_normal((m, len(s))))[0]
+    v = np.linalg.qr(rng.standard_normal((n, len(s))))[0]
+    return (u * s) @ v.T
+
+
+@pytest.mark.parametrize("n", [31, 32, 33, 63, 64, 65, 96, 97, 130, 257])
+@pytest.mark.parametrize("extra", [0, 1, 70])
+def test_shapes(n, extra):
+    check(np.random.default_rng(n + extra).standard_normal((n, n + extra)))
+
+
+@pytest.mark.parametrize("shape", [(2049, 32), (2100, 70), (40, 2500), (512, 300), (513, 300), (1025, 64), (1500, 50)])
+def test_long_sides(shape):
+    check(np.random.default_rng(shape[0]).standard_normal(shape))
+
+
+@pytest.mark.parametrize("rows", [90, 2060])
+@pytest.mark.parametrize("kind", ["graded", "degenerate", "rank 5", "zero columns", "orthogonal", "zero", "equal columns"])
+def test_spectra(kind, rows):
+    n = 66
+    if kind == "graded":
+        a = spectrum(rows, n, np.exp(-0.5 * np.arange(n)), 1)
+    elif kind == "degenerate":
+        a = spectrum(rows, n, np.r_[np.ones(33), np.full(33, 0.5)], 2)
+    elif kind == "rank 5":
+        a = spectrum(rows, n, np.arange(5, 0, -1.0), 3)
+    elif kind == "orthogonal":
+        a = np.eye(rows, n)[:, ::-1] * np.arange(1.0, n + 1)
+    else:
+        a = np.random.default_rng(4).standard_normal((rows, n))
+        if kind == "zero":
+            a[:] = 0
+        elif kind == "zero columns":
+            a[:, 7::9] = 0
+        else:
+            a[:, 40:] = a[:, 3:4]
+    check(a)
+
+
+@pytest.mark.parametrize("scale", [1e-120, 1e-60, 1e60])
+def test_scales(scale):
+    check(scale * np.random.default_rng(5).standard_normal((50, 48)))
+
+
+def test_small_values_next_to_large_ones():
+    """Columns of very different size: each value keeps its own digits (the
+    spread columns are orthogonal to 1e-8, so their norms are the values' to 1e-15)."""
+    rng = np.random.default_rng(6)
+    q = np.linalg.qr(rng.standard_normal((80, 40)))[0]
+    norms = 10.0 ** (-rng.permutation(40) / 3.0)
+    u, s, vt, _ = tn.split_node_full_svd(torch.tensor(q * norms, device=DEV), [0], [1])
+    s = s.cpu().numpy()
+    s = np.diag(s) if s.ndim == 2 else s
+    np.testing.assert_allclose(s, np.sort(norms)[::-1], rtol=1e-13)
