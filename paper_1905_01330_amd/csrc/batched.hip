@@ -48,45 +48,50 @@ __device__ inline int slot_exponent(uint32_t bits) {
   return e - 127;
 }
 
-// one workgroup per chain: sum_{a', a} E_L[a', a] E_R[a', a] at the middle
-// bond in FP64 (products of FP32 values are exact), times 2^(the exponents
-// applied on both sides), written as a mantissa in [0.5, 1) and a log scale
-constexpr int kFinishThreads = 1024;
+// sum_{a', a} E_L[a', a] E_R[a', a] at the middle bond in FP64 (products of
+// FP32 values are exact), kFinishParts workgroups a chain (one took 113 us for
+// a bond of 500), then times 2^(the exponents applied on both sides), written
+// as a mantissa in [0.5, 1) and a log scale
+constexpr int kFinishParts = 16, kFinishThreads = 1024;
 
-__global__ void __launch_bounds__(kFinishThreads) batched_finish_kernel(const ChainRec* chains, int n_chains,
-                                                                        double* out2) {
+__global__ void __launch_bounds__(kFinishThreads) batched_sum_kernel(const ChainRec* chains, double* parts) {
   constexpr int NW = kFinishThreads / 64;
-  __shared__ double red[2][NW];
-  const int c = blockIdx.x;
-  if (c >= n_chains) return;
-  const ChainRec r = chains[c];
+  __shared__ double red[NW];
+  const ChainRec r = chains[blockIdx.x];
   const float* el = r.e[r.c & 1];
   const float* er = r.er[(r.n - r.c) & 1];
-  double v = 0.0, s = 0.0;
-  for (int64_t i = threadIdx.x; i < r.cnt; i += kFinishThreads) v += (double)el[i] * (double)er[i];
-  for (int i = threadIdx.x; i < r.c; i += kFinishThreads) s += (double)slot_exponent(r.slots[i]);
-  for (int i = threadIdx.x; i < r.n - r.c; i += kFinishThreads) s += (double)slot_exponent(r.rslots[i]);
+  double v = 0.0;
+#pragma unroll 8
+  for (int64_t i = blockIdx.y * kFinishThreads + threadIdx.x; i < r.cnt; i += kFinishParts * kFinishThreads)
+    v += (double)el[i] * (double)er[i];
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    v += __shfl_xor(v, o, 64);
-    s += __shfl_xor(s, o, 64);
-  }
-  if ((threadIdx.x & 63) == 0) {
-    red[0][threadIdx.x >> 6] = v;
-    red[1][threadIdx.x >> 6] = s;
-  }
+  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   if (threadIdx.x == 0) {
-    double total = 0.0, ex = 0.0;
+    double total = 0.0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      total += red[0][w];
-      ex += red[1][w];
-    }
+    for (int w = 0; w < NW; ++w) total += red[w];
+    parts[blockIdx.x * kFinishParts + blockIdx.y] = total;
+  }
+}
+
+__global__ void __launch_bounds__(64) batched_finish_kernel(const ChainRec* chains, const double* parts, double* out2) {
+  const int c = blockIdx.x;
+  const ChainRec r = chains[c];
+  double s = 0.0;
+  for (int i = threadIdx.x; i < r.c; i += 64) s += (double)slot_exponent(r.slots[i]);
+  for (int i = threadIdx.x; i < r.n - r.c; i += 64) s += (double)slot_exponent(r.rslots[i]);
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
+  if (threadIdx.x == 0) {
+    double total = 0.0;
+#pragma unroll
+    for (int w = 0; w < kFinishParts; ++w) total += parts[c * kFinishParts + w];
     int e2 = 0;
     const double m = frexp(total, &e2);
     out2[2 * c] = m;
-    out2[2 * c + 1] = (ex + (double)e2) * 0.69314718055994530942;
+    out2[2 * c + 1] = (s + (double)e2) * 0.69314718055994530942;
   }
 }
 
@@ -103,6 +108,7 @@ struct Launch {
   size_t tile_off[kGroupedCfgs];     // per grouped tile: index into the tile-start table
   int32_t tiles[kGroupedCfgs];       // per grouped tile: workgroups of the launch
   int heur;                          // the tile the work estimate picks
+  bool direct;                       // tile 2 (32 x 32, the direct kernel) takes every problem
   int variant;                       // gather variant shared by every problem of the launch
   int side;                          // 0: the caller's stream (right halves), 1: the side stream (left halves)
   bool has_left;                     // a caller's-stream launch that holds left halves too (small steps)
@@ -114,7 +120,7 @@ struct BatchPlan {
   std::vector<Gemm2D> probs;
   std::vector<int32_t> tstart;
   std::vector<Launch> launches;
-  size_t chain_bytes = 0, chain_tab = 0, prob_tab = 0, tile_tab = 0, total = 0;
+  size_t chain_bytes = 0, chain_tab = 0, prob_tab = 0, tile_tab = 0, parts = 0, total = 0;
 };
 
 bool is_contiguous(const tn_tensor& t) {
@@ -129,31 +135,35 @@ bool is_contiguous(const tn_tensor& t) {
 // Work estimate of the tile for one site step, shared by all of its problems
 // (one launch per step, product and half); used when tuning is off or the stream
 // is being captured.  With tuning on, the first launch of each step
-// signature and precision times the grouped tiles instead.  A step is usually too small to fill the chip with
-// 128 x 128 tiles, so its time is the latency of one tile rather than the
-// total work: the estimate is, in units of one wave's 32 x 32 block times one
-// k, the larger of the longest wave's work and the total padded work spread
-// over the 1024 SIMDs, divided by a per-wave efficiency of the tile shape.
-// The efficiencies follow per-launch measurement on a batch of 32 chains
-// with odd bond dimensions (run-time gathers; N up to 256, chi up to 512):
-// the 128 x 128 tile was 10-25 % faster on the full steps, the k-sliced
-// 64 x 64 tile about twice as fast on the last steps, where few tiles run.
+// signature and precision times the grouped tiles instead.
+//
+// Up to kDirectTiles 32 x 32 tiles a step lasts as long as one tile: the
+// direct kernel, which cuts a tile's K over eight waves (32 chains of up to
+// 128 sites and bonds up to 512, the last steps: 141 tiles of 64 x 64 20 us
+// against 14.6 direct, 74 tiles of twice the K 30 against 17; 646 direct tiles
+// as long as 174 of 64 x 64).  8 chains of bond 100 as a whole 0.52 -> 0.36 ms.
+// Above, in units of one wave's 32 x 32 block times one k, the larger of the
+// longest wave's work and the total padded work spread over the 1024 SIMDs,
+// divided by a per-wave efficiency of the tile shape.  64 x 64 with stages of
+// 32 k lets four workgroups share a compute unit: 1536 x 1664 x 400 in 31 us
+// (stages of 64 k 41, 128 x 128 42), 4096 x 4096 x 400 in 131 (177, 127).
 //   0: 128 x 128 (four 64 x 64 waves)   1: 64 x 64 (four 32 x 32 waves)
 //   3: 64 x 64 in two k-slices (eight waves, each over half of K)
-//   2: 32 x 32 when every problem of the step fits one such tile
+//   2: 32 x 32, the direct kernel
 // chains of at least this many sites are contracted from both ends
 constexpr int kTwoSided = 4;
 
-int step_cfg(const std::vector<Gemm2D>& v) {
-  bool tiny = true;
-  for (const Gemm2D& q : v) tiny = tiny && q.M <= 32 && q.N <= 32;
-  if (tiny) return 2;
+constexpr int64_t kDirectTiles = 1024;
+int step_cfg(const std::vector<Gemm2D>& v, bool direct) {
+  int64_t tiles32 = 0;
+  for (const Gemm2D& q : v) tiles32 += (int64_t)((q.M + 31) / 32) * ((q.N + 31) / 32);
+  if (direct && tiles32 <= kDirectTiles) return 2;
   struct Cand {
     int cfg, bm;
     double per_wave;  // blocks x k per wave, per k of the problem
     double eff;
   };
-  static const Cand cands[] = {{0, 128, 4.0, 1.2}, {1, 64, 1.0, 0.9}, {3, 64, 0.5, 1.0}};
+  static const Cand cands[] = {{0, 128, 4.0, 1.2}, {1, 64, 1.0, 1.5}, {3, 64, 0.5, 1.0}};
   int best = 0;
   double best_t = 1e300;
   for (const Cand& c : cands) {
@@ -370,7 +380,8 @@ int32_t build(int32_t n_chains, const int32_t* off, const tn_tensor* psi, const 
   P.chain_tab = align256b(P.chain_bytes);
   P.prob_tab = P.chain_tab + align256b(P.chains.size() * sizeof(ChainRec));
   P.tile_tab = P.prob_tab + align256b(P.probs.size() * sizeof(Gemm2D));
-  P.total = P.tile_tab + align256b(P.tstart.size() * sizeof(int32_t));
+  P.parts = P.tile_tab + align256b(P.tstart.size() * sizeof(int32_t));
+  P.total = P.parts + align256b(P.chains.size() * kFinishParts * sizeof(double));
   return TN_OK;
 }
 
@@ -382,7 +393,9 @@ static int32_t add_launch(BatchPlan& P, std::vector<std::pair<int64_t, Gemm2D>>&
   Launch L;
   L.prob_off = P.probs.size();
   L.n_probs = (int32_t)u.size();
-  L.heur = step_cfg(qs);
+  L.direct = true;
+  for (const Gemm2D& q : qs) L.direct = L.direct && direct_grouped_ok(q);
+  L.heur = step_cfg(qs, L.direct);
   L.variant = var;
   L.side = side;
   L.has_left = has_left;
@@ -498,6 +511,7 @@ int32_t tn_mps_inner_batched_launch(int32_t n_chains, const int32_t* site_offset
     const int ncfg = L.variant ? kGroupedCfgs : kGroupedCfgs - 1;
     int cfg = forced >= 0 ? (forced < ncfg ? forced : 0) : grouped_tune_get(L.sig, prec);
     if (cfg >= ncfg) cfg = 0;
+    if (cfg == 2 && !L.direct) cfg = 1;   // operands past 2^31 bytes
     if (cfg < 0) {
       bool timed = false;
       cfg = L.heur;
@@ -512,6 +526,7 @@ int32_t tn_mps_inner_batched_launch(int32_t n_chains, const int32_t* site_offset
         float best = 1e30f;
         const int reps = level >= 2 ? 10 : 3;
         for (int c = 0; c < ncfg; ++c) {
+          if (c == 2 && !L.direct) continue;
           TN_TRY(run(L, c, s));
           TN_TRY(hip_check(hipEventRecord(e0, s), "tuning event"));
           for (int r = 0; r < reps; ++r) TN_TRY(run(L, c, s));
@@ -552,7 +567,9 @@ int32_t tn_mps_inner_batched_launch(int32_t n_chains, const int32_t* site_offset
   }
   hipEventDestroy(hop);
   TN_TRY(rc);
-  hipLaunchKernelGGL(batched_finish_kernel, dim3(n_chains), dim3(kFinishThreads), 0, st, d_chains, n_chains, out2);
+  double* parts = reinterpret_cast<double*>(ws + Q.parts);
+  hipLaunchKernelGGL(batched_sum_kernel, dim3(n_chains, kFinishParts), dim3(kFinishThreads), 0, st, d_chains, parts);
+  hipLaunchKernelGGL(batched_finish_kernel, dim3(n_chains), dim3(64), 0, st, d_chains, parts, out2);
   return hip_check(hipGetLastError(), "batched finish");
 }
 

@@ -126,7 +126,7 @@ static GemmFn pick_fn(const GemmDesc& d, int prec, int cfg, bool lean) {
 }
 
 // grouped configurations: 0 -> 128x128, 1 -> 64x64, 2 -> 32x32, 3 -> 64x64 in two k-slices
-static const int kGroupedCfg[5] = {3, 15, 7, 14, 10};
+static const int kGroupedCfg[5] = {3, 6, 7, 14, 10};
 int grouped_tile_m(int cfg) { return kCfgs[kGroupedCfg[cfg]].bm; }
 int grouped_tile_n(int cfg) { return kCfgs[kGroupedCfg[cfg]].bn; }
 
@@ -618,6 +618,7 @@ int grouped_variant(const Gemm2D& p) {
 int32_t launch_gemm_grouped(const Gemm2D* dev_probs, const int32_t* dev_tile_start, int32_t n_probs,
                             int32_t total_tiles, int32_t prec, int cfg, int variant, hipStream_t st) {
   if (n_probs <= 0 || total_tiles <= 0) return TN_OK;
+  if (cfg == 2) return launch_direct_grouped(dev_probs, dev_tile_start, n_probs, total_tiles, prec, variant, st);
   const Cfg& g = kCfgs[kGroupedCfg[cfg]];
   hipLaunchKernelGGL(pick_grouped(prec, cfg, variant), dim3((unsigned)total_tiles), dim3(g.wm * g.wn * g.wk * 64), 0, st, dev_probs,
                      dev_tile_start, n_probs);

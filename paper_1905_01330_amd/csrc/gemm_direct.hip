@@ -116,6 +116,30 @@ int32_t launch_gemm_direct(const GemmDesc& d, int32_t prec, hipStream_t st) {
   return hip_check(hipGetLastError(), "direct gemm launch");
 }
 
+// ---- tiles of many problems a launch ------------------------------------------
+
+// offsets as in direct_ok
+bool direct_grouped_ok(const Gemm2D& p) {
+  const int64_t lim = (1ll << 29) - 8;
+  auto fits = [&](int64_t rows, int64_t sr, int64_t sk) {
+    return sr >= 0 && sk >= 0 && (rows - 1) * sr < lim && (p.K - 1) * sk < lim && (rows - 1) * sr + (p.K - 1) * sk < lim;
+  };
+  return fits(p.M, p.sam, p.sak) && fits(p.N, p.sbn, p.sbk);
+}
+
+int32_t launch_direct_grouped(const Gemm2D* dev_probs, const int32_t* dev_tile_start, int32_t n_probs,
+                              int32_t total_tiles, int32_t prec, int variant, hipStream_t st) {
+  const bool akv = variant == 1 || variant == 2, bkv = variant == 1 || variant == 3;
+  void (*f)(const Gemm2D*, const int32_t*, int32_t) = nullptr;
+  with_prec(prec, [&](auto pr) {
+    constexpr int P = pr.value;
+    f = akv ? (bkv ? gemm_direct_grouped_kernel<P, D_STAGED, D_STAGED> : gemm_direct_grouped_kernel<P, D_STAGED, D_ANY>)
+            : (bkv ? gemm_direct_grouped_kernel<P, D_ANY, D_STAGED> : gemm_direct_grouped_kernel<P, D_ANY, D_ANY>);
+  });
+  hipLaunchKernelGGL(f, dim3((unsigned)total_tiles), dim3(kDirectWaves * 64), 0, st, dev_probs, dev_tile_start, n_probs);
+  return hip_check(hipGetLastError(), "direct grouped launch");
+}
+
 // ---- two problems a launch ---------------------------------------------------
 
 typedef void (*PairFn)(const DirectPair);

@@ -22,6 +22,7 @@
 #pragma once
 
 #include "gemm_kernel.h"
+#include "internal.h"
 
 namespace tn {
 
@@ -408,6 +409,38 @@ __global__ void __launch_bounds__(kDirectWaves * 64) __attribute__((amdgpu_waves
     gemm_direct_kernel(const DirectDesc d) {
   __shared__ __attribute__((aligned(16))) float red[direct_lds(AM, BM)];
   direct_tile<P, AM, BM, MK>(d, blockIdx.x, blockIdx.z, red, red + direct_lds(AM, BM) - kDirectWaves);
+}
+
+// Tiles of many 2-D problems in one launch (the halves of an uneven batch of
+// chains), each problem a range of workgroups; D_STAGED where every problem's
+// operand has unit stride along k
+template <int P, int AM, int BM>
+__global__ void __launch_bounds__(kDirectWaves * 64) __attribute__((amdgpu_waves_per_eu(4)))
+    gemm_direct_grouped_kernel(const Gemm2D* probs, const int32_t* tile_start, int32_t n_probs) {
+  __shared__ __attribute__((aligned(16))) float red[direct_lds(AM, BM)];
+  const int prob = grouped_find(tile_start, n_probs, blockIdx.x);
+  const Gemm2D& p = probs[prob];
+  DirectDesc d;
+  d.a = p.a;
+  d.b = p.b;
+  d.c = p.c;
+  d.M = p.M;
+  d.N = p.N;
+  d.K = p.K;
+  d.tiles_m = (p.M + 31) / 32;
+  d.a_bs = d.b_bs = d.c_bs = 0;
+  d.a_scale_bits = p.a_scale_bits;
+  d.c_absmax = p.c_absmax;
+  d.gm.one = d.gn.one = 1;
+  d.gm.sx[2] = (int32_t)p.sam;
+  d.gm.sc[2] = p.scm;
+  d.gn.sx[2] = (int32_t)p.sbn;
+  d.gn.sc[2] = p.scn;
+  d.ska[1] = (int32_t)p.sak;
+  d.skb[1] = (int32_t)p.sbk;
+  const int tile = (int)blockIdx.x - tile_start[prob];
+  if (tile >= d.tiles_m * ((p.N + 31) / 32)) return;
+  direct_tile<P, AM, BM, 1>(d, tile, 0, red, red + direct_lds(AM, BM) - kDirectWaves);
 }
 
 // Two independent problems in one launch (the same step of a chain's two

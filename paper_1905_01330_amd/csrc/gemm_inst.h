@@ -35,9 +35,9 @@ __global__ void __launch_bounds__(WM* WN * WK * 64)
   GemmTile<P, BM, BN, BK, WM, WN, AMODE, BMODE, WK>::run(d, gk, blockIdx.x, blockIdx.z, smem);
 }
 
-// Grouped launch: the workgroup finds its problem by binary search over the
-// per-problem first-tile table, then expands the compact 2-D description
-// into a full descriptor held in LDS.
+// Grouped launch: the workgroup finds its problem in the per-problem
+// first-tile table, then expands the compact 2-D description into a full
+// descriptor held in LDS.
 // AMODE / BMODE as for gemm_kernel: the fast gathers when the host has
 // checked that every problem of the launch has those layouts, else -1.
 template <int P, int BM, int BN, int BK, int WM, int WN, int AMODE = -1, int BMODE = -1, int WK = 1>
@@ -45,19 +45,10 @@ __global__ void __launch_bounds__(WM* WN * WK * 64)
     gemm_grouped_kernel(const Gemm2D* probs, const int32_t* tile_start, int32_t n_probs) {
   __shared__ __attribute__((aligned(16))) char smem[GemmTile<P, BM, BN, BK, WM, WN, AMODE, BMODE, WK>::lds_bytes];
   __shared__ GemmDesc sd;
-  __shared__ int32_t s_prob;
   const int bid = blockIdx.x;
+  const int prob = grouped_find(tile_start, n_probs, bid);
   if (threadIdx.x == 0) {
-    int lo = 0, hi = n_probs - 1;
-    while (lo < hi) {
-      int mid = (lo + hi + 1) >> 1;
-      if (tile_start[mid] <= bid)
-        lo = mid;
-      else
-        hi = mid - 1;
-    }
-    s_prob = lo;
-    const Gemm2D& p = probs[lo];
+    const Gemm2D& p = probs[prob];
     GemmDesc& d = sd;
     d.a = p.a;
     d.b = p.b;
@@ -74,10 +65,8 @@ __global__ void __launch_bounds__(WM* WN * WK * 64)
     auto one = [](Group& g, int64_t dim, int64_t s0, int64_t s1) {
       g.n = 1;
       g.dim[0] = (uint32_t)dim;
-      uint32_t shr = 0;
-      while (shr < 32 && (1ull << shr) < (uint64_t)dim) ++shr;
-      g.mul[0] = (uint32_t)((((1ull << 32) * ((1ull << shr) - (uint64_t)dim)) / (uint64_t)dim) + 1);
-      g.shr[0] = shr;
+      g.mul[0] = 0;   // the one axis' digit is the index itself: a quotient of zero
+      g.shr[0] = 31;
       g.s[0][0] = s0;
       g.s[1][0] = s1;
       g.s[2][0] = 0;
@@ -94,7 +83,7 @@ __global__ void __launch_bounds__(WM* WN * WK * 64)
   }
   __syncthreads();
   // a tile table built for another tile size must not reach past the problem
-  const int tile = bid - tile_start[s_prob];
+  const int tile = bid - tile_start[prob];
   if (tile >= sd.tiles_m * sd.tiles_n) return;
   GemmTile<P, BM, BN, BK, WM, WN, AMODE, BMODE, WK>::run(sd, sd.gk, tile, 0, smem);
 }
@@ -139,14 +128,14 @@ template <int P, int AM, int BM_>
 GroupedFn grouped_fn_modes(int cfg) {
   switch (cfg) {
     case 0: return gemm_grouped_kernel<P, 128, 128, 32, 2, 2, AM, BM_>;
-    case 1: return gemm_grouped_kernel<P, 64, 64, 64, 2, 2, AM, BM_>;
+    case 1: return gemm_grouped_kernel<P, 64, 64, 32, 2, 2, AM, BM_>;
     case 3: return gemm_grouped_kernel<P, 64, 64, 64, 2, 2, AM, BM_, 2>;
     // eight waves side by side: fast gathers only (the run-time gathers
     // exceed its register budget; such launches never take this tile)
     case 4:
       if constexpr (AM >= 0 && BM_ >= 0) return gemm_grouped_kernel<P, 160, 256, 32, 1, 8, AM, BM_>;
       else return gemm_grouped_kernel<P, 128, 128, 32, 2, 2, AM, BM_>;
-    default: return gemm_grouped_kernel<P, 32, 32, 32, 1, 1, AM, BM_>;
+    default: return nullptr;   // 32 x 32: the direct kernel
   }
 }
 
