@@ -36,15 +36,16 @@ def contract_between(a, b, axes_a, axes_b, out=None, prec="fp32", conj_a=False, 
         return _contract_c64(a, b, axes_a, axes_b, out, prec, conj_a, conj_b)
     if conj_a or conj_b:
         raise ValueError("conjugation applies to complex operands")
-    axes_a = [int(x) % max(a.dim(), 1) for x in axes_a]
-    axes_b = [int(x) % max(b.dim(), 1) for x in axes_b]
+    na, nb = a.dim() or 1, b.dim() or 1
+    axes_a = [int(x) % na for x in axes_a]
+    axes_b = [int(x) % nb for x in axes_b]
     if out is None:
         shape = [a.shape[i] for i in range(a.dim()) if i not in axes_a] + \
                 [b.shape[j] for j in range(b.dim()) if j not in axes_b]
         out = torch.empty(shape, dtype=torch.float32, device=a.device)
     da, db, do = L.tensor_desc(a), L.tensor_desc(b), L.tensor_desc(out)
-    # few outputs may be long sums, which split over workgroups with a small scratch
-    ws = _workspace(L.REDUCE_WORKSPACE_BYTES, a.device) if out.numel() < 1024 else None
+    # few outputs may be sums over 16384 and more, which split over workgroups with a small scratch
+    ws = _workspace(L.REDUCE_WORKSPACE_BYTES, a.device) if out.numel() < 1024 and a.numel() >= 16384 else None
     L.check(L.lib().tn_contract_between(C.byref(da), C.byref(db), len(axes_a), L.int_array(axes_a),
                                         L.int_array(axes_b), C.byref(do),
                                         C.c_void_p(ws.data_ptr()) if ws is not None else None,
