@@ -18,7 +18,7 @@
 // Everything is FP64 matrix-core work on the whole chip, 64 columns at a
 // time; the Householder panels are a chain of one workgroup's reductions over
 // the rows, one a column.  The chain of 100 sites of bond 1024 of two states:
-// 58.1 ms by Householder panels, 10.2 ms here.
+// 58.1 ms by Householder panels, 9.4 ms here.
 #include "cholqr.h"
 
 namespace tn {
@@ -215,22 +215,26 @@ __device__ __forceinline__ void chol_each(const d64x4_t (&acc)[2], F&& f) {
 }
 
 __device__ __forceinline__ double chol_lane(double x, int l) {
-  const long long v = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_readlane((int)v, l), hi = __builtin_amdgcn_readlane((int)(v >> 32), l);
-  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned int)lo);
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l), __builtin_amdgcn_readlane(__double2loint(x), l));
 }
 
 // R and L = R^-T of the 64 x 64 matrix in tm (pitch kPn, upper triangle read):
-// R back into tm, L into ym (pitch kPn).  Blocks of 16: one wave eliminates
-// the diagonal block, a column a lane, with the identity's columns on the
-// next sixteen lanes (the elimination turns [G I] into [R L]); the rest of
-// the block row and of the trailing rows are 16 x 16 products, as many at a
-// time as there are waves.
+// R back into tm, L into ym (pitch kPn).  Blocks of 16: the first wave
+// eliminates the diagonal block and updates the next one, straight on to its
+// elimination, while the others take the rest of the trailing rows as 16 x 16
+// products; block rows by four waves.  The elimination has a column a lane,
+// with the identity's columns on the next sixteen lanes ([G I] turns into
+// [R L]); its chain from pivot to pivot is 1 / sqrt (the hardware's estimate
+// and one step of third order; NaN where a pivot is not positive and finite,
+// which fails the certificate), the row, and the next pivot from its own lane.
+// (All in turn, two steps of second order: 5700 of 8200 cycles a block of 16
+// in the elimination, 33000 in all; now 4500 and 24500.)
 __device__ __forceinline__ void chol_factor(double* tm, double* ym, double* dm) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l15 = lane & 15, lk = lane >> 4;
   for (int e = threadIdx.x; e < 64 * 64; e += kCholThreads) ym[(e >> 6) * kPn + (e & 63)] = (e >> 6) == (e & 63) ? 1.0 : 0.0;
-  // C (16 x 16) = sign * A^T-or-A B, A at a + k * ak + row * ar, B at b + k * kPn + col
-  auto block = [&](const double* a, int ar, int ak, const double* b, d64x4_t c) {
+  // C (16 x 16) = A^T-or-A B, A at a + k * ak + row * ar, B at b + k * kPn + col
+  auto block = [&](const double* a, int ar, int ak, const double* b) {
+    d64x4_t c = {};
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
       c = __builtin_amdgcn_mfma_f64_16x16x4f64(a[(4 * kk + lk) * ak + l15 * ar], b[(4 * kk + lk) * kPn + l15], c, 0, 0, 0);
@@ -238,24 +242,22 @@ __device__ __forceinline__ void chol_factor(double* tm, double* ym, double* dm) 
   };
   for (int b = 0; b < 4; ++b) {
     const int r0 = 16 * b;
-    __syncthreads();
     if (wave == 0) {
       double g[16];
 #pragma unroll
       for (int i = 0; i < 16; ++i)
-        g[i] = lane < 16 ? (i <= lane ? tm[(r0 + i) * kPn + r0 + lane] : 0.0) : (i == l15 ? 1.0 : 0.0);
+        g[i] = lane < 16 ? tm[(r0 + i) * kPn + r0 + lane] : (i == l15 ? 1.0 : 0.0);
+      double d = chol_lane(g[0], 0);
 #pragma unroll
       for (int k = 0; k < 16; ++k) {
-        const double d = chol_lane(g[k], k);
-        // 1 / sqrt(d): the hardware's estimate and two Newton steps
         double y = __builtin_amdgcn_rsq(d);
-        y = y * fma(-0.5 * d * y, y, 1.5);
-        y = y * fma(-0.5 * d * y, y, 1.5);
-        if (!(d > 0.0)) y = __builtin_nan("");   // not positive: the certificate fails
-        const double rk = g[k] * y;
-        g[k] = rk;
+        const double e = fma(-(d * y), y, 1.0);
+        y = fma(y * e, fma(0.375, e, 0.5), y);
+        const double r = g[k] * y;
+        g[k] = r;
+        if (k < 15) d = chol_lane(fma(-r, r, g[k + 1]), k + 1);
 #pragma unroll
-        for (int i = k + 1; i < 16; ++i) g[i] = fma(-chol_lane(rk, i), rk, g[i]);
+        for (int i = k + 1; i < 16; ++i) g[i] = fma(-chol_lane(r, i), r, g[i]);
       }
       if (lane < 16) {
 #pragma unroll
@@ -266,15 +268,10 @@ __device__ __forceinline__ void chol_factor(double* tm, double* ym, double* dm) 
       }
     }
     __syncthreads();
-    // block row b: R_b,cb = D T_b,cb (cb > b), L_b,cb = D Y_b,cb (cb <= b): four products
-    d64x4_t c = {};
-    double* row = nullptr;
+    // block row b: R_b,cb = D T_b,cb (cb > b), L_b,cb = D Y_b,cb (cb <= b), a wave its own block
     if (wave < 4) {
-      row = (wave > b ? tm : ym) + r0 * kPn + 16 * wave;
-      c = block(dm, 18, 1, row, d64x4_t{});
-    }
-    __syncthreads();
-    if (wave < 4) {
+      double* row = (wave > b ? tm : ym) + r0 * kPn + 16 * wave;
+      const d64x4_t c = block(dm, 18, 1, row);
 #pragma unroll
       for (int r = 0; r < 4; ++r) row[(4 * r + lk) * kPn + l15] = c[r];
     }
@@ -284,10 +281,11 @@ __device__ __forceinline__ void chol_factor(double* tm, double* ym, double* dm) 
     for (int ib = b + 1; ib < 4; ++ib)
       for (int cb = 0; cb < 4; ++cb) {
         if (cb > b && cb < ib) continue;
-        if ((job++ & 7) != wave) continue;
+        const int who = ib == b + 1 && cb == ib ? 0 : 1 + job++ % 7;
+        if (who != wave) continue;
         double* src = (cb > b ? tm : ym) + r0 * kPn + 16 * cb;
         double* dst = (cb > b ? tm : ym) + 16 * ib * kPn + 16 * cb;
-        const d64x4_t u = block(tm + r0 * kPn + 16 * ib, 1, kPn, src, d64x4_t{});
+        const d64x4_t u = block(tm + r0 * kPn + 16 * ib, 1, kPn, src);
 #pragma unroll
         for (int r = 0; r < 4; ++r) dst[(4 * r + lk) * kPn + l15] -= u[r];
       }

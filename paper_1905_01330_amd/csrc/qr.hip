@@ -262,31 +262,46 @@ __device__ __forceinline__ void qr_panel_step(double (&x)[NR][kQrNb], double (*r
     if (J < nb) {
       constexpr int NW = kQrNb - J;
       const int gj = j0 + J;
-      double s[NW];
+      // A column of values near 1e-150 (what is left of dependent columns)
+      // would lose its norm to underflow and the reflector its orthogonality:
+      // its products are then formed again with the column scaled by 2^700,
+      // which leaves v and tau as they are.
+      double s[NW], unit = 1.0, sigma, alpha;
+      int at;
+      for (;;) {
 #pragma unroll
-      for (int c = 0; c < NW; ++c) s[c] = 0.0;
+        for (int c = 0; c < NW; ++c) s[c] = 0.0;
 #pragma unroll
-      for (int q = 0; q < NR; ++q) {
-        const int row = r0 + threadIdx.x + kQrThreads * q;
-        const double xv = row > gj && row < m ? x[q][J] : 0.0;
+        for (int q = 0; q < NR; ++q) {
+          const int row = r0 + threadIdx.x + kQrThreads * q;
+          const double xv = row > gj && row < m ? unit * x[q][J] : 0.0;
+          s[0] += xv * xv;
 #pragma unroll
-        for (int c = 0; c < NW; ++c) s[c] += xv * x[q][J + c];
-        if (row == gj) {
+          for (int c = 1; c < NW; ++c) s[c] += xv * x[q][J + c];
+          if (row == gj) {
 #pragma unroll
-          for (int c = 0; c < NW; ++c) top[buf][c] = x[q][J + c];
+            for (int c = 0; c < NW; ++c) top[buf][c] = x[q][J + c];
+          }
         }
+        at = buf;
+        qr_block_sum<NW, (NW > 8 ? 16 : NW > 4 ? 8 : NW > 2 ? 4 : NW > 1 ? 2 : 1)>(s, red, buf);
+        sigma = s[0];
+        alpha = unit * top[at][0];
+        if (unit != 1.0 || !(alpha * alpha + sigma < 1e-240)) break;
+        unit = 0x1p700;
       }
-      const int at = buf;
-      qr_block_sum<NW, (NW > 8 ? 16 : NW > 4 ? 8 : NW > 2 ? 4 : NW > 1 ? 2 : 1)>(s, red, buf);
-      const double sigma = s[0], alpha = top[at][0];
       double t = 0.0;
       if (sigma != 0.0) {   // the same in every thread
-        const double beta = -copysign(sqrt(alpha * alpha + sigma), alpha);
-        const double scale = 1.0 / (alpha - beta);
+        double beta = -copysign(sqrt(alpha * alpha + sigma), alpha);
+        double scale = 1.0 / (alpha - beta);
         t = (beta - alpha) / beta;
         double w[NW];
 #pragma unroll
         for (int c = 1; c < NW; ++c) w[c] = t * (top[at][c] + scale * s[c]);
+        if (unit != 1.0) {
+          beta *= 0x1p-700;
+          scale *= unit;
+        }
 #pragma unroll
         for (int q = 0; q < NR; ++q) {
           const int row = r0 + threadIdx.x + kQrThreads * q;
