@@ -20,7 +20,9 @@ inline size_t jac_scratch_doubles(int64_t cp) { return (size_t)(3 * cp * cp + 2 
 int32_t jac_gram(const double* x, int rows, int cp, const double* sigma, const int* perm, double tol, double* scratch,
                  int* ctl, hipStream_t st);
 // One sweep over all pairs from that Gram matrix: x2 = x(:, perm) J, v2 = v(:, perm) J (v: cp x cp).
+// Its kernels leave at once where *ctl is zero, so that a sweep can be issued
+// before the count is known to the host; x2 and v2 are undefined then.
 int32_t jac_sweep(const double* x, const double* v, double* x2, double* v2, int rows, int cp, const int* perm,
-                  double tol, double* scratch, hipStream_t st);
+                  double tol, double* scratch, const int* ctl, hipStream_t st);
 
 }  // namespace tn

@@ -103,6 +103,7 @@ struct JacRound {
   double* jthis;
   double* js;           // cp x cp, row-major: the order's permutation and the sweep's rotations so far
   const int* perm;
+  const int* ctl;       // zero: nothing to rotate
   int cp, nb, round, rounds;
   double tol2;
 };
@@ -154,9 +155,11 @@ __global__ void __launch_bounds__(256) jac_round_kernel(const JacRound p) {
   __shared__ double A[2][kJacP][P], J[2][kJacP][P];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l15 = lane & 15, lk = lane >> 4;
   const int np = p.nb / 2, first = p.round < p.rounds ? np : 0;
+  const int gate = *p.ctl;   // looked at behind the loads
   if ((int)blockIdx.x >= first) {
     const int tiles = p.cp / kJacP;
     int w = ((int)blockIdx.x - first) * 4 + wave;
+    if (gate == 0) return;
     if (p.round == 0) {   // Js: the permutation
       if (w < p.cp)
         for (int c = lane; c < p.cp; c += 64) p.js[(int64_t)w * p.cp + c] = p.perm[c] == w ? 1.0 : 0.0;
@@ -225,6 +228,7 @@ __global__ void __launch_bounds__(256) jac_round_kernel(const JacRound p) {
       jac_tile(p.g, p.cp, pa, qa, pb, qb, l15, lk, t);
       jac_cols(p.jlast + tb * kJacJ, hb, l15, lk, b);
       jac_cols(p.jlast + ta * kJacJ, ha, l15, lk, a);
+      if (gate == 0) return;
       jac_right(t, b, s);
       o = jac_left(a, s);
     }
@@ -237,6 +241,7 @@ __global__ void __launch_bounds__(256) jac_round_kernel(const JacRound p) {
   } else {
     for (int e = lane; e < kJacJ; e += 64) J[0][e / kJacP][e % kJacP] = e / kJacP == e % kJacP ? 1.0 : 0.0;
   }
+  if (gate == 0) return;
   __syncthreads();
   // thread (i, j): the 2 x 2 block of row pair i and column pair j, and rows i
   // and 16 + i of J; one barrier a step, from one LDS copy into the other.
@@ -318,7 +323,7 @@ struct JacGemm {
   double* c2;          // JAC_APPLY: the new V
   const double* sigma;
   const int* perm;
-  int* ctl;
+  int* ctl;            // JAC_GRAM: the count, JAC_APPLY: read
   double tol;
   int rows, cp, xtiles;
 };
@@ -339,6 +344,7 @@ __global__ void __launch_bounds__(512) jac_gemm_kernel(const JacGemm p) {
   const bool second = OP == JAC_APPLY && (int)blockIdx.x >= p.xtiles;
   const int m0 = blockIdx.y * 32, n0 = ((int)blockIdx.x - (second ? p.xtiles : 0)) * 32;
   if (OP == JAC_GRAM && n0 < m0) return;
+  if (OP == JAC_APPLY && *p.ctl == 0) return;
   const int K = OP == JAC_GRAM ? p.rows : p.cp;
   const int N = OP == JAC_GRAM || second ? p.cp : p.rows;   // columns of the result
   constexpr int D = 4;
@@ -463,7 +469,7 @@ int32_t jac_gram(const double* x, int rows, int cp, const double* sigma, const i
 }
 
 int32_t jac_sweep(const double* x, const double* v, double* x2, double* v2, int rows, int cp, const int* perm,
-                  double tol, double* scratch, hipStream_t st) {
+                  double tol, double* scratch, const int* ctl, hipStream_t st) {
   const int64_t nn = (int64_t)cp * cp;
   const int np = cp / kJacP;
   double* g[2] = {scratch, scratch + nn};
@@ -471,6 +477,7 @@ int32_t jac_sweep(const double* x, const double* v, double* x2, double* v2, int 
   JacRound r{};
   r.js = scratch + 2 * nn;
   r.perm = perm;
+  r.ctl = ctl;
   r.cp = cp;
   r.nb = 2 * np;
   r.rounds = r.nb - 1;
@@ -492,6 +499,7 @@ int32_t jac_sweep(const double* x, const double* v, double* x2, double* v2, int 
   a.js = r.js;
   a.c = x2;
   a.c2 = v2;
+  a.ctl = const_cast<int*>(ctl);
   a.rows = rows;
   a.cp = cp;
   a.xtiles = (rows + 31) / 32;

@@ -922,8 +922,8 @@ int32_t tn_split_node_decompose(const tn_tensor* a, int32_t n_left, int32_t max_
     // pairs count as orthogonal when |g_ij| <= tol sqrt(g_ii g_jj): a few
     // roundings of a dot product of length `rows`
     const double tol = 8.0 * std::sqrt((double)rows) * 2.220446049250313e-16;
-    auto rank_columns = [&](const double* m) {
-      hipLaunchKernelGGL(column_norm_kernel, dim3((unsigned)g.Cp), dim3(kNT), 0, st, m, rows, sigma, ctl);
+    auto rank_columns = [&](const double* m, int* count) {
+      hipLaunchKernelGGL(column_norm_kernel, dim3((unsigned)g.Cp), dim3(kNT), 0, st, m, rows, sigma, count);
       hipLaunchKernelGGL(rank_kernel, dim3((unsigned)((g.Cp + 3) / 4)), dim3(256), 0, st, sigma, (int)g.Cp, perm);
     };
     if (g.gram) {
@@ -932,18 +932,33 @@ int32_t tn_split_node_decompose(const tn_tensor* a, int32_t n_left, int32_t max_
       double* scratch = reinterpret_cast<double*>(ws + g.g_off);
       int at = 0;
       bool done = false;
-      while (!done && done_sweeps < kGramSweeps) {
-        rank_columns(xs[at]);
-        TN_TRY(jac_gram(xs[at], (int)rows, (int)g.Cp, sigma, perm, tol, scratch, ctl, st));
+      // A sweep is issued together with the check that precedes it, and the
+      // host reads the check's count on a side stream meanwhile: the device
+      // does not wait for the host between sweeps (50 us each), and the last
+      // sweep's kernels find the count zero and leave.  Two counts in turn.
+      hipStream_t rs = st;
+      TN_TRY(side_stream(rs));
+      hipEvent_t counted = nullptr;
+      TN_TRY(hip_check(hipEventCreateWithFlags(&counted, hipEventDisableTiming), "create event"));
+      auto sweep = [&]() -> int32_t {
+        int* count = ctl + 2 + (done_sweeps & 1);
+        rank_columns(xs[at], count);
+        TN_TRY(jac_gram(xs[at], (int)rows, (int)g.Cp, sigma, perm, tol, scratch, count, st));
+        TN_TRY(hip_check(hipEventRecord(counted, st), "record event"));
+        TN_TRY(jac_sweep(xs[at], vs[at], xs[at ^ 1], vs[at ^ 1], (int)rows, (int)g.Cp, perm, tol, scratch, count, st));
+        TN_TRY(hip_check(hipStreamWaitEvent(rs, counted, 0), "wait for event"));
         int pairs = 0;
-        TN_TRY(hip_check(hipMemcpyAsync(&pairs, ctl, sizeof(int), hipMemcpyDeviceToHost, st), "read sweep counter"));
-        TN_TRY(hip_check(hipStreamSynchronize(st), "sweep sync"));
+        TN_TRY(hip_check(hipMemcpyAsync(&pairs, count, sizeof(int), hipMemcpyDeviceToHost, rs), "read sweep counter"));
+        TN_TRY(hip_check(hipStreamSynchronize(rs), "sweep sync"));
         ++done_sweeps;
         done = pairs == 0;
-        if (done) break;
-        TN_TRY(jac_sweep(xs[at], vs[at], xs[at ^ 1], vs[at ^ 1], (int)rows, (int)g.Cp, perm, tol, scratch, st));
-        at ^= 1;
-      }
+        if (!done) at ^= 1;
+        return TN_OK;
+      };
+      int32_t rc = TN_OK;
+      while (rc == TN_OK && !done && done_sweeps < kGramSweeps) rc = sweep();
+      hipEventDestroy(counted);
+      TN_TRY(rc);
       if (at) {
         const auto blocks = [](int64_t n) { return dim3((unsigned)std::min<int64_t>((n + 255) / 256, 16384)); };
         hipLaunchKernelGGL(svd_copy_kernel, blocks(rows * g.Cp), dim3(256), 0, st, xs[1], M, rows * g.Cp);
@@ -955,7 +970,7 @@ int32_t tn_split_node_decompose(const tn_tensor* a, int32_t n_left, int32_t max_
     for (int sw = 0; sw < kMaxSweeps; ++sw) {
       // columns in descending order of their norms: the blocks of a sweep then
       // pair columns of similar size first (fewer sweeps on graded spectra)
-      rank_columns(M);
+      rank_columns(M, ctl);
       for (int r = 0; r < g.nb - 1; ++r) {
         const dim3 grid(g.nb / 2), blk(kNT);
         if (!g.lds)
