@@ -18,7 +18,7 @@
 // Everything is FP64 matrix-core work on the whole chip, 64 columns at a
 // time; the Householder panels are a chain of one workgroup's reductions over
 // the rows, one a column.  The chain of 100 sites of bond 1024 of two states:
-// 58.1 ms by Householder panels, 9.4 ms here.
+// 58.1 ms by Householder panels, 8.4 ms here.
 #include "cholqr.h"
 
 namespace tn {
@@ -39,106 +39,136 @@ struct CholGemm {
   uint64_t* ebits;
 };
 
+// a raw buffer of 2^31 bytes
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t chol_rsrc(const double* p) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(p), (short)0, (int)0x80000000, 0x00020000);
 }
 
-// C (32 x 64 a workgroup, four waves of 16 x 32) with
+// C with
 //   C_ABSORB:   C = A B, A upper triangular (K from the row)
 //   C_GRAM:     C = A^T B, the upper triangle's tiles
 //   C_DEFECT:   U of A^T B - I, and max |E| into ebits
 //   C_TRIANGLE: C = base + A B, all triangles upper, zero below (where certified)
 //   C_Q:        C = base - A B, B upper triangular (where certified)
-// Stages of 16 k through two LDS buffers, k-major with a pitch of 16 mod 32
-// doubles so that the four k that a matrix-core operand reads fall into both
-// halves of the banks.  A stage's products take 0.2 us, a load a few times
-// that: four stages are in flight in registers (1024 x 1024 over 2048: one in
-// flight 131 us, four 70).
-template <int OP>
-__global__ void __launch_bounds__(256) chol_gemm_kernel(const CholGemm p) {
+// A workgroup of eight waves owns a tile of 16 NB squared and cuts K over its
+// waves, 16 k a wave and turn.  The operands go from memory straight into the
+// matrix cores' registers, up to two turns ahead: no barrier before the sums.
+// An instruction reads whole lines: four rows of 128 bytes where k is the
+// outer index, 16 rows of 32 bytes in two halves where it is the inner one (a
+// lane's four k are neighbours, the same four in both operands).  Bound by
+// what a compute unit reads, 17 to 20 KB a us (the matrix cores would take
+// twice that), so by the tile's side.  At 1024 columns, 2048 rows: the Gram
+// matrix's triangle 94 us in tiles of 48, A B 76 to 82 and base - A B beside
+// it in tiles of 64 (a site's absorb, Q and Gram 258 us staged through LDS in
+// 32 x 64 tiles, 198 here; the defect 105 and 83, the triangle 47 and 30).
+template <int OP, int NB>
+__global__ void __launch_bounds__(512) chol_gemm_kernel(const CholGemm p) {
   constexpr bool TN = OP == C_GRAM || OP == C_DEFECT;   // A stored k x m
-  constexpr int PA = 48, PB = 80;
-  __shared__ double sa[2][16][PA], sb[2][16][PB];
-  __shared__ uint64_t smax[4];
-  if constexpr (OP == C_TRIANGLE || OP == C_Q) {
+  constexpr bool TRI = OP == C_TRIANGLE || OP == C_Q;   // B's blocks below the diagonal are not written: read as zero
+  constexpr int T = 16 * NB, D = NB < 4 ? 2 : 1;   // turns in flight: 256 registers a wave
+  __shared__ double red[8][4 * NB][64];
+  __shared__ uint64_t smax[8];
+  if constexpr (TRI) {
     if (!chol_certified(p.ebits)) return;
   }
-  const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 64;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  if (TN && n0 + 63 < m0) return;
+  // the longest sums first
+  const int m0 = (int)blockIdx.y * T, n0 = (int)(TRI ? gridDim.x - 1 - blockIdx.x : blockIdx.x) * T;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l15 = lane & 15, lk = lane >> 4;
+  if (TN && n0 + T <= m0) return;
   int kb = 0, ke = p.K;
-  if (OP == C_ABSORB || OP == C_TRIANGLE) kb = m0 & ~15;
-  if (OP == C_TRIANGLE || OP == C_Q) ke = min(p.K, n0 + 64);
-  constexpr int D = 4;   // stages in flight
-  double ra[D][2], rb[D][4];
-  // Raw buffers of 2^31 bytes (the host keeps matrices below that): an offset
-  // past the end reads zero, so a guard is a select and not a branch, behind
-  // which the loads of a stage would wait for each other.
-  const __amdgpu_buffer_rsrc_t qa = chol_rsrc(p.a), qb = chol_rsrc(p.b);
-  auto get = [](__amdgpu_buffer_rsrc_t rs, bool ok, int at) {
-    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, ok ? (uint32_t)at * 8u : 0x80000000u, 0, 0));
+  if (OP == C_ABSORB || OP == C_TRIANGLE) kb = m0;
+  if (TRI) ke = min(p.K, n0 + T);
+  // Raw buffers of exactly a matrix (below 2^31 bytes): what lies past it reads
+  // zero, so no load has a guard, behind which the loads of a turn would wait
+  // for each other.  Columns past M or N read the next row's values and are
+  // not stored; A's k past K, where they run along a row, meet B's zeros.
+  auto rsrc = [](const double* q, int64_t count) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(q), (short)0, (int)(count * 8), 0x00020000);
   };
-  auto load = [&](double (&xa)[2], double (&xb)[4], int k0) {
+  const __amdgpu_buffer_rsrc_t qa = rsrc(p.a, (int64_t)(TN ? p.K : p.M) * p.lda), qb = rsrc(p.b, (int64_t)p.K * p.ldb);
+  typedef double d2_t __attribute__((ext_vector_type(2)));
+  constexpr int NA = TN ? 4 : NB;
+  uint32_t oa[NA], ob[4];   // byte offsets of the next turn
+  const int k0 = kb + wave * 16 + 4 * lk;
+  int kt = k0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) ob[j] = ((uint32_t)(k0 + j) * (uint32_t)p.ldb + (uint32_t)(n0 + l15)) * 8u;
+#pragma unroll
+  for (int j = 0; j < NA; ++j)
+    oa[j] = TN ? ((uint32_t)(k0 + j) * (uint32_t)p.lda + (uint32_t)(m0 + l15)) * 8u
+               : ((uint32_t)(m0 + 16 * j + l15) * (uint32_t)p.lda + (uint32_t)k0) * 8u;
+  const uint32_t ia = 128u * 8u * (TN ? (uint32_t)p.lda : 1u), ib = 128u * 8u * (uint32_t)p.ldb;
+  double a[D][NB][4], b[D][NB][4];
+  auto load = [&](double (&xa)[NB][4], double (&xb)[NB][4]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int t = 0; t < NB; ++t) {
+        uint32_t at = ob[j] + 128u * t;
+        if constexpr (TRI) at = kt + j <= n0 + 16 * t + l15 ? at : 0x80000000u;
+        xb[t][j] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(qb, at, 0, 0));
+      }
     if constexpr (TN) {
-      const int m = m0 + (t & 31);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int k = k0 + (t >> 5) + 8 * i;
-        xa[i] = get(qa, k < ke && m < p.M, k * p.lda + m);
-      }
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int t = 0; t < NB; ++t)
+          xa[t][j] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(qa, oa[j] + 128u * t, 0, 0));
     } else {
-      const int m = m0 + (t >> 3);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int k = k0 + (t & 7) + 8 * i;
-        xa[i] = get(qa, k < ke && m < p.M, m * p.lda + k);
-      }
-    }
-    const int n = n0 + (t & 63);
+      for (int t = 0; t < NB; ++t)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int k = k0 + (t >> 6) + 4 * i;
-      xb[i] = get(qb, k < ke && n < p.N, k * p.ldb + n);
+        for (int j = 0; j < 4; j += 2) {
+          const d2_t v = __builtin_bit_cast(d2_t, __builtin_amdgcn_raw_buffer_load_b128(qa, oa[t] + 8u * j, 0, 0));
+          xa[t][j] = v[0];
+          xa[t][j + 1] = v[1];
+        }
     }
+    kt += 128;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) ob[j] += ib;
+#pragma unroll
+    for (int j = 0; j < NA; ++j) oa[j] += ia;
   };
-  auto store = [&](const double (&xa)[2], const double (&xb)[4], int s) {
+  d64x4_t acc[NB][NB] = {};
+  const int turns = (ke - kb + 127) / 128;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      if constexpr (TN) sa[s][(t >> 5) + 8 * i][t & 31] = xa[i];
-      else sa[s][(t & 7) + 8 * i][t >> 3] = xa[i];
-    }
+  for (int d = 0; d < D; ++d) {
+    load(a[d], b[d]);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  for (int turn = 0; turn < turns; turn += D) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) sb[s][(t >> 6) + 4 * i][t & 63] = xb[i];
-  };
-  const int wm = (wave & 1) * 16, wn = (wave >> 1) * 32, l15 = lane & 15, lk = lane >> 4;
-  d64x4_t acc[2] = {};
-  // loads past the last k return zeros: no stage needs a condition
+    for (int d = 0; d < D; ++d) {
 #pragma unroll
-  for (int i = 0; i < D; ++i) load(ra[i], rb[i], kb + 16 * i);
-  for (int k0 = kb; k0 < ke; k0 += 16 * D) {
+      for (int j = 0; j < 4; ++j)
 #pragma unroll
-    for (int i = 0; i < D; ++i) {
-      store(ra[i], rb[i], i & 1);
-      load(ra[i], rb[i], k0 + 16 * (i + D));
-      __syncthreads();
+        for (int x = 0; x < NB; ++x)
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const double av = sa[i & 1][4 * kk + lk][wm + l15];
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-          acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, sb[i & 1][4 * kk + lk][wn + 16 * q + l15], acc[q], 0, 0, 0);
-      }
+          for (int y = 0; y < NB; ++y)
+            acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[d][x][j], b[d][y][j], acc[x][y], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);   // a set's loads in one place, a turn ahead of their use
+      load(a[d], b[d]);
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
+  // the waves' sums, a row of blocks at a time: wave w adds registers w and w + 8
   // FP64 16x16x4 result: lane (column l15) register r holds row 4 r + lk
   uint64_t emax = 0;
 #pragma unroll
-  for (int q = 0; q < 2; ++q)
+  for (int x = 0; x < NB; ++x) {
+    if (x > 0) __syncthreads();
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int m = m0 + wm + 4 * r + lk, n = n0 + wn + 16 * q + l15;
+    for (int y = 0; y < NB; ++y)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wave][4 * y + r][lane] = acc[x][y][r];
+    __syncthreads();
+    for (int e = wave; e < 4 * NB; e += 8) {
+      double v = 0.0;
+#pragma unroll
+      for (int w = 0; w < 8; ++w) v += red[w][e][lane];
+      const int m = m0 + 16 * x + 4 * (e & 3) + lk, n = n0 + 16 * (e >> 2) + l15;
       if (m >= p.M || n >= p.N) continue;
-      double v = acc[q][r];
       const int64_t at = (int64_t)m * p.ldc + n;
       if constexpr (OP == C_DEFECT) {
         if (m == n) v -= 1.0;
@@ -151,13 +181,17 @@ __global__ void __launch_bounds__(256) chol_gemm_kernel(const CholGemm p) {
       }
       p.c[at] = v;
     }
+  }
   if constexpr (OP == C_DEFECT) {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) emax = max(emax, (uint64_t)__shfl_xor((unsigned long long)emax, o, 64));
     if (lane == 0) smax[wave] = emax;
     __syncthreads();
-    if (t == 0)
-      atomicMax((unsigned long long*)p.ebits, (unsigned long long)max(max(smax[0], smax[1]), max(smax[2], smax[3])));
+    if (threadIdx.x == 0) {
+#pragma unroll
+      for (int w = 1; w < 8; ++w) emax = max(emax, smax[w]);
+      atomicMax((unsigned long long*)p.ebits, (unsigned long long)emax);
+    }
   }
 }
 
@@ -413,9 +447,20 @@ __global__ void __launch_bounds__(kCholThreads) chol_step_kernel(const CholStep 
 
 // ---------------------------------------------------------------------------
 
+// Tiles of 32, 48 or 64, whichever has the busiest compute unit read least:
+// a tile's bytes go with its side, and they bound it
 template <int OP>
 static void chol_gemm(const CholGemm& p, hipStream_t st) {
-  hipLaunchKernelGGL(chol_gemm_kernel<OP>, dim3((unsigned)((p.N + 63) / 64), (unsigned)((p.M + 31) / 32)), dim3(256), 0, st, p);
+  auto load = [&](int64_t t) {
+    const int64_t tm = (p.M + t - 1) / t, tn = (p.N + t - 1) / t;
+    const int64_t tiles = OP == C_GRAM || OP == C_DEFECT || OP == C_TRIANGLE ? tm * (tm + 1) / 2 : tm * tn;
+    return (tiles + 255) / 256 * t;
+  };
+  auto grid = [&](int t) { return dim3((unsigned)((p.N + t - 1) / t), (unsigned)((p.M + t - 1) / t)); };
+  const int64_t l2 = load(32), l3 = load(48), l4 = load(64);
+  if (l2 <= l3 && l2 <= l4) hipLaunchKernelGGL((chol_gemm_kernel<OP, 2>), grid(32), dim3(512), 0, st, p);
+  else if (l3 <= l4) hipLaunchKernelGGL((chol_gemm_kernel<OP, 3>), grid(48), dim3(512), 0, st, p);
+  else hipLaunchKernelGGL((chol_gemm_kernel<OP, 4>), grid(64), dim3(512), 0, st, p);
 }
 
 int32_t chol_absorb(const double* r, const double* a, double* x, int dk, int cols, hipStream_t st) {
