@@ -64,7 +64,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t chol_rsrc(const double* p) {
 template <int OP, int NB>
 __global__ void __launch_bounds__(512) chol_gemm_kernel(const CholGemm p) {
   constexpr bool TN = OP == C_GRAM || OP == C_DEFECT;   // A stored k x m
-  constexpr bool TRI = OP == C_TRIANGLE || OP == C_Q;   // B's blocks below the diagonal are not written: read as zero
+  constexpr bool TRI = OP == C_TRIANGLE || OP == C_Q;   // R1's blocks below the diagonal are not written: B reads zero there
   constexpr int T = 16 * NB, D = NB < 4 ? 2 : 1;   // turns in flight: 256 registers a wave
   __shared__ double red[8][4 * NB][64];
   __shared__ uint64_t smax[8];
@@ -74,7 +74,16 @@ __global__ void __launch_bounds__(512) chol_gemm_kernel(const CholGemm p) {
   // the longest sums first
   const int m0 = (int)blockIdx.y * T, n0 = (int)(TRI ? gridDim.x - 1 - blockIdx.x : blockIdx.x) * T;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l15 = lane & 15, lk = lane >> 4;
-  if (TN && n0 + T <= m0) return;
+  if (TN && n0 + T <= m0) {
+    // U's other half is zero: reads past the end of a row of it meet zeros of
+    // the other operand, which what the workspace held before need not survive
+    if constexpr (OP == C_DEFECT)
+      for (int e = threadIdx.x; e < T * T; e += 512) {
+        const int m = m0 + e / T, n = n0 + e % T;
+        if (m < p.M && n < p.N) p.c[(int64_t)m * p.ldc + n] = 0.0;
+      }
+    return;
+  }
   int kb = 0, ke = p.K;
   if (OP == C_ABSORB || OP == C_TRIANGLE) kb = m0;
   if (TRI) ke = min(p.K, n0 + T);

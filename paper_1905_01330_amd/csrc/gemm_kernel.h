@@ -565,16 +565,6 @@ __device__ __forceinline__ void copy_group(Group& dst, const Group& src) {
   }
 }
 
-// The problem of a grouped launch that holds workgroup bid: the last whose
-// first tile is not past it, every wave looking at 64 entries at a time (a
-// search by one thread is a chain of loads from a cold cache)
-__device__ __forceinline__ int grouped_find(const int32_t* tile_start, int n_probs, int bid) {
-  const int lane = threadIdx.x & 63;
-  int n = 0;
-  for (int i = 0; i < n_probs; i += 64) n += __popcll(__ballot(i + lane < n_probs && tile_start[i + lane] <= bid));
-  return __builtin_amdgcn_readfirstlane(n - 1);
-}
-
 // XCD-aware tile order: the hardware deals workgroups round-robin over the 8
 // XCDs, so consecutive ids are remapped to one XCD's contiguous range, then
 // grouped by GROUP_M tile rows so neighbouring tiles share A rows and B

@@ -12,61 +12,57 @@ constexpr int kSmallK = 32, kSmallN = 16;
 
 __device__ inline float small_bf16(float x) { return (float)(__bf16)x; }
 
-// K and N up to 16: the offsets of k and n come with the arguments, a row's
-// values are all in flight before the operand's are in LDS, and KM and NM
-// bound the unrolled sums.  A row's time is the latency of one load then, not
-// of K (131072 rows, K = N = 6, the operator step of a two-site update at bond
-// 256: 10.6 us before, 7.7 now).
-constexpr int kTabK = 16, kTabN = 16;
+// K and N up to 8: the offsets of k and n come with
+// the arguments, a row's values are all in flight before the operand's are in
+// LDS, and the sums are unrolled.  A row's time is the latency of one load
+// then, not of K.  131072 rows, K = N = 6 (the operator step of a two-site
+// update at bond 256): 10.6 us before, 7.7 now, with its result laid out along
+// the rows; 10^6 rows, K = N = 4, 20.1 and 10.0.  (With 16 by 16 sums, or a
+// loop over a thread's rows, the operand moves into registers and costs waves:
+// 10^6 rows, K = N = 10, 38 -> 177 us.)
+constexpr int kTab = 8;
+constexpr int64_t kTabRows = 65536 * 256;   // a row a thread
 struct SmallDesc {
   const float* a;
   const float* b;
   float* c;
   int32_t M, K, N;
   Group gm;
-  int64_t ka[kTabK], kb[kTabK], bn[kTabN], cn[kTabN];
+  int64_t ka[kTab], kb[kTab], bn[kTab], cn[kTab];
 };
-template <int KM, int NM>
 __global__ void __launch_bounds__(256) gemm_small_table_kernel(const SmallDesc d, int bf16_round) {
-  __shared__ double sb[KM][NM];
+  __shared__ double sb[kTab][kTab];
   const int K = d.K, N = d.N;
-  const int64_t nthreads = (int64_t)gridDim.x * blockDim.x;
-  int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  float av[KM];
-  int64_t oc = 0;
-  auto load = [&]() {
-    int64_t om[2];
-    group_offsets<2>(d.gm, (uint32_t)(m < d.M ? m : d.M - 1), om, 0);
-    oc = om[1];
+  const int m = blockIdx.x * 256 + threadIdx.x;
+  int64_t om[2];
+  group_offsets<2>(d.gm, (uint32_t)(m < d.M ? m : d.M - 1), om, 0);
+  float av[kTab];
 #pragma unroll
-    for (int k = 0; k < KM; ++k)
-      if (k < K) av[k] = d.a[om[0] + d.ka[k]];
-  };
-  load();
-  if ((int)threadIdx.x < KM * NM) {
-    const int k = threadIdx.x / NM, n = threadIdx.x % NM;
+  for (int k = 0; k < kTab; ++k)
+    if (k < K) av[k] = d.a[om[0] + d.ka[k]];
+  if (threadIdx.x < kTab * kTab) {
+    const int k = threadIdx.x / kTab, n = threadIdx.x % kTab;
     if (k < K && n < N) {
       const float v = d.b[d.kb[k] + d.bn[n]];
       sb[k][n] = (double)(bf16_round ? small_bf16(v) : v);
     }
   }
   __syncthreads();
-  for (; m < d.M; m += nthreads, load()) {
-    double acc[NM];
+  if (m >= d.M) return;
+  double acc[kTab];
 #pragma unroll
-    for (int n = 0; n < NM; ++n) acc[n] = 0.0;
+  for (int n = 0; n < kTab; ++n) acc[n] = 0.0;
 #pragma unroll
-    for (int k = 0; k < KM; ++k)
-      if (k < K) {
-        const double a = (double)(bf16_round ? small_bf16(av[k]) : av[k]);
+  for (int k = 0; k < kTab; ++k)
+    if (k < K) {
+      const double a = (double)(bf16_round ? small_bf16(av[k]) : av[k]);
 #pragma unroll
-        for (int n = 0; n < NM; ++n)
-          if (n < N) acc[n] += a * sb[k][n];
-      }
+      for (int n = 0; n < kTab; ++n)
+        if (n < N) acc[n] += a * sb[k][n];
+    }
 #pragma unroll
-    for (int n = 0; n < NM; ++n)
-      if (n < N) d.c[oc + d.cn[n]] = (float)acc[n];
-  }
+  for (int n = 0; n < kTab; ++n)
+    if (n < N) d.c[om[1] + d.cn[n]] = (float)acc[n];
 }
 
 // PRELOAD: a row's K values are loaded before the first is used (for grids
@@ -150,7 +146,7 @@ int32_t launch_gemm_small(const GemmDesc& d0, int32_t prec, hipStream_t st) {
   int64_t blocks = (d.M + 255) / 256;
   blocks = blocks < 1 ? 1 : (blocks > 65536 ? 65536 : blocks);
   const int bf = prec == TN_PREC_BF16 ? 1 : 0;
-  if (d.K <= kTabK && d.N <= kTabN) {
+  if (d.K <= kTab && d.N <= kTab && d.M <= kTabRows) {
     SmallDesc t{};
     t.a = d.a;
     t.b = d.b;
@@ -171,9 +167,7 @@ int32_t launch_gemm_small(const GemmDesc& d0, int32_t prec, hipStream_t st) {
       t.bn[n] = o[0];
       t.cn[n] = o[1];
     }
-    auto f = d.K <= 8 ? (d.N <= 8 ? gemm_small_table_kernel<8, 8> : gemm_small_table_kernel<8, 16>)
-                      : (d.N <= 8 ? gemm_small_table_kernel<16, 8> : gemm_small_table_kernel<16, 16>);
-    hipLaunchKernelGGL(f, dim3((unsigned)blocks), dim3(256), 0, st, t, bf);
+    hipLaunchKernelGGL(gemm_small_table_kernel, dim3((unsigned)blocks), dim3(256), 0, st, t, bf);
   } else if (blocks < 256)
     hipLaunchKernelGGL(gemm_small_kernel<true>, dim3((unsigned)blocks), dim3(256), 0, st, d, bf);
   else

@@ -125,6 +125,15 @@ struct Gemm2D {
   const uint32_t* a_scale_bits;
   uint32_t* c_absmax;
 };
+// The problem of a grouped launch that holds workgroup bid: the last whose
+// first tile is not past it, every wave looking at 64 entries at a time (a
+// search by one thread is a chain of loads from a cold cache)
+__device__ __forceinline__ int grouped_find(const int32_t* tile_start, int n_probs, int bid) {
+  const int lane = threadIdx.x & 63;
+  int n = 0;
+  for (int i = 0; i < n_probs; i += 64) n += __popcll(__ballot(i + lane < n_probs && tile_start[i + lane] <= bid));
+  return __builtin_amdgcn_readfirstlane(n - 1);
+}
 // variant: 0 run-time gathers; 1..4 fast gathers, for launches whose every
 // problem passes grouped_variant with that value
 int grouped_variant(const Gemm2D& p);

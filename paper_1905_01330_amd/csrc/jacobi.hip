@@ -428,7 +428,7 @@ __global__ void __launch_bounds__(512) jac_gemm_kernel(const JacGemm p) {
   // wave w adds registers 2 w and 2 w + 1 over the waves
   // G by a power of two that brings the largest norm below one
   double scale = 1.0;
-  if constexpr (OP == JAC_GRAM) scale = ldexp(1.0, -2 * max(-500, min(500, ilogb(p.sigma[p.perm[0]]) + 1)));
+  if constexpr (OP == JAC_GRAM) scale = ldexp(1.0, -2 * max(-500, min(500, ilogb(p.sigma[p.perm[0]]))) - 2);
   bool over = false;
   double* c = second ? p.c2 : p.c;
 #pragma unroll

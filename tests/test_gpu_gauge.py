@@ -133,3 +133,17 @@ def test_capture():
         graph.replay()
         torch.cuda.synchronize()
         assert all(np.array_equal(s.cpu().numpy(), w) for s, w in zip(sites, want)) and float(lognorm) == wantnorm
+
+
+@pytest.mark.parametrize("n", [33, 65, 100, 130, 200, 300])
+def test_workspace_holding_nan(n):
+    """What the workspace held before plays no part: its memory is full of NaN."""
+    rng = np.random.default_rng(n)
+    bonds = [1, 40, n, n, n, 50, 1]
+    raw = [rng.standard_normal((a, -(-2 * max(a, b) // a), b)) for a, b in zip(bonds, bonds[1:])]
+    sites = [torch.tensor(s, device=DEV) for s in raw]
+    poison = torch.full((64 << 20,), float("nan"), dtype=torch.float64, device=DEV)
+    del poison
+    lognorm = tn.mps_left_canonicalize(sites)
+    torch.cuda.synchronize()
+    check(raw, [s.cpu().numpy() for s in sites], float(lognorm))

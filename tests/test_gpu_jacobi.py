@@ -89,3 +89,12 @@ def test_small_values_next_to_large_ones():
     s = s.cpu().numpy()
     s = np.diag(s) if s.ndim == 2 else s
     np.testing.assert_allclose(s, np.sort(norms)[::-1], rtol=1e-13)
+
+
+@pytest.mark.parametrize("shape", [(33, 40), (97, 97), (130, 300), (2060, 70)])
+def test_workspace_holding_nan(shape):
+    """What the workspace held before plays no part: its memory is full of NaN."""
+    a = np.random.default_rng(shape[1]).standard_normal(shape)
+    poison = torch.full((16 << 20,), float("nan"), dtype=torch.float64, device=DEV)
+    del poison
+    check(a)
