@@ -48,7 +48,7 @@ static const Cfg kCfgs[] = {
 static constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
 // 32 x 32 tiles: the direct kernel (gemm_direct.hip) where it takes the
 // problem, else one wave a tile with run-time gathers
-static constexpr int kCfg32 = 7;
+static constexpr int kCfg32 = 7, kCfg64 = 6;
 
 int gemm_num_cfgs() { return kNumCfgs; }
 
@@ -259,23 +259,38 @@ static int64_t cfg_tiles(const GemmDesc& d, int c) {
   return (int64_t)((d.M + g.bm - 1) / g.bm) * ((d.N + g.bn - 1) / g.bn) * d.batch;
 }
 
+// Few tiles: a call lasts as long as one tile's chain of loads and products,
+// which the direct kernel cuts over eight waves.  Measured against the best
+// staged tile (M x N x K, graph replay): 256 x 512 x 256 FP32 11.6 -> 4.5 us,
+// 512 x 512 x 1024 30.8 -> 8.6.  Up to 800 tiles it is faster in every
+// precision and layout (1.1 to 3.4 times), past that where the staged tiles
+// leave a round of the compute units partly empty: below 0.85 of a round's 64
+// x 64 tiles FP32 1.2 to 1.7 times up to 2560 tiles, the split terms 1.1 to
+// 1.5 up to K = 1024 (1500^3 1.01 to 0.91); 1300 x 1300 (0.86) 0.9 to 1.2,
+// 2048 x 1024 (full) 0.84 to 1.1.  Up to 1024 tiles the split terms 1.02 to
+// 1.33, FP32 1.0 to 1.6 except with both operands along k (0.92 to 1.09).
+// Single BF16 products are too quick for it past 800: 900 x 900 x 500 0.75 to
+// 0.94.  With K below 128 the sums and stores weigh more: 1024 x 1024 x 64 6.4
+// either way, 2048 x 1024 x 32 8.1 -> 10.3.  Two problems at once (a shared
+// chip, or both in one launch) count on less than half: 1024 tiles each.
+static bool direct_few(const GemmDesc& d, int prec) {
+  const int64_t tiles = cfg_tiles(d, kCfg32);
+  if (d.K < 128) return tiles <= (g_shared ? 320 : 640);
+  if (g_shared) return tiles <= 1024;
+  if (tiles <= 800) return true;
+  if (prec == TN_PREC_BF16 || tiles > 2560) return false;
+  if (tiles <= 1024) return prec != TN_PREC_FP32 || d.a_mode != LOAD_KVEC || d.b_mode != LOAD_KVEC;
+  const int64_t t64 = cfg_tiles(d, kCfg64);
+  return (prec == TN_PREC_FP32 || d.K <= 1024) && t64 * 100 < (t64 + 255) / 256 * 256 * 85;
+}
+
 static int heuristic_cfg(const GemmDesc& d, int prec) {
   const int forced = g_forced_cfg.load();
   if (forced >= 0) return forced;
   // one workgroup per compute unit for the large tiles; a GEMM that shares
   // the chip with a concurrent stream counts on half of them
   const int kSlots = g_shared ? 128 : 256;
-  // Few tiles: a call lasts as long as one tile's chain of loads and
-  // products, which the direct kernel cuts over eight waves.  Measured
-  // against the best staged tile (M x N x K, graph replay): 256 x 512 x 256
-  // FP32 11.6 -> 4.5 us, 512 x 512 x 1024 30.8 -> 8.6; at 2560 tiles (2560 x
-  // 1024 x 512) FP32 54.4 -> 35.1, split-BF16 37.7 -> 30.9, past which the
-  // larger tiles fill the chip.  With K below 128 the sums and stores weigh
-  // more: 1024 x 1024 x 64 6.4 either way, 2048 x 1024 x 32 8.1 -> 10.3.  Two
-  // problems at once (a shared chip, or both in one launch) count on less
-  // than half: 1024 tiles each.
-  const int64_t most = d.K >= 128 ? (g_shared ? 1024 : 2560) : (g_shared ? 320 : 640);
-  if (direct_ok(d) && cfg_tiles(d, kCfg32) <= most) return kCfg32;
+  if (direct_ok(d) && direct_few(d, prec)) return kCfg32;
   double best = 1e300;
   int best_c = kCfg32;   // 32 x 32 tiles fit every problem
   for (int c = 0; c < kNumCfgs; ++c) {
