@@ -16,7 +16,8 @@
 // registers (one workgroup reduction per column, row conditions as selects so
 // the unrolled panel stays short) and forms the panel's triangular factor T
 // from the Gram matrix of its reflectors; I - V T^T V^T is applied to all
-// trailing columns (one reduction per workgroup); Q is accumulated panel by
+// trailing columns (one reduction per workgroup), to the next panel's by the
+// next panel's workgroup on the matrix cores; Q is accumulated panel by
 // panel in reverse with I - V T V^T.  All panels and updates of a matrix are
 // tasks of one launch.  Taller matrices take one reflector launch and one
 // update launch per column.
@@ -326,13 +327,109 @@ struct QrPanelSmem {
   double top[2][kQrNb];
   double gram[kQrNb * kQrNb];
   double tl[kQrNb * kQrNb];
+  double stage[kQrWaves][64][kQrNb + 1];   // a wave's 64 rows, between a row a lane and the matrix cores' layouts
+  double part[kQrWaves][kQrNb * kQrNb];    // the waves' shares of a 16 x 16 sum
 };
+typedef double qr_d4_t __attribute__((ext_vector_type(4)));
+// a wave's LDS accesses are served in order; the compiler must keep them so
+__device__ __forceinline__ void qr_wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+__device__ __forceinline__ void qr_stage(double (*st)[kQrNb + 1], const double (&v)[kQrNb]) {
+  qr_wave_order();
+#pragma unroll
+  for (int c = 0; c < kQrNb; ++c) st[threadIdx.x & 63][c] = v[c];
+  qr_wave_order();
+}
+// the staged rows as a right operand (or, transposed, a left one) of a sum
+// over the rows: k = 4 kk + lane / 16, column lane % 16
+__device__ __forceinline__ void qr_rows(const double (*st)[kQrNb + 1], double (&o)[16]) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int kk = 0; kk < 16; ++kk) o[kk] = st[4 * kk + (lane >> 4)][lane & 15];
+}
+
+// Panel j0 (whole, reflectors in X, factor T) applied to the next panel's
+// columns x, rows r0 = j0 on: x -= V T^T (V^T x) on the matrix cores.  The
+// next panel's own workgroup does it: by column groups in other workgroups it
+// was 7 us and a second exchange of data of a panel's 60 us (512 x 512, one
+// factorisation 1.91 ms, now 1.40 with the panels in one workgroup).
 template <int NR>
-__device__ inline void qr_panel(double* xc, double* tau, double* tf, int m, int j0, int nb, QrPanelSmem& sm) {
+__device__ inline void qr_ahead(double (&x)[NR][kQrNb], const double* __restrict__ xc, const double* __restrict__ tf,
+                                int m, int j0, QrPanelSmem& sm) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l15 = lane & 15, lk = lane >> 4;
+  auto st = sm.stage[wave];
+  double t[4];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) t[kk] = tf[(j0 / kQrNb) * kQrNb * kQrNb + (4 * kk + lk) * kQrNb + l15];
+  auto reflectors = [&](int q, double (&v)[kQrNb]) {
+    const int row = j0 + threadIdx.x + kQrThreads * q;
+#pragma unroll
+    for (int c = 0; c < kQrNb; ++c) {
+      const int gc = j0 + c;
+      const double u = xc[(int64_t)gc * m + (row < m ? row : m - 1)];
+      v[c] = row == gc ? 1.0 : row > gc && row < m ? u : 0.0;
+    }
+  };
+  double v[kQrNb];
+  qr_d4_t w = {};
+#pragma unroll
+  for (int q = 0; q < NR; ++q) {
+    double a[16], b[16];
+    reflectors(q, v);
+    qr_stage(st, v);
+    qr_rows(st, a);
+    qr_stage(st, x[q]);
+    qr_rows(st, b);
+#pragma unroll
+    for (int kk = 0; kk < 16; ++kk) w = __builtin_amdgcn_mfma_f64_16x16x4f64(a[kk], b[kk], w, 0, 0, 0);
+  }
+  // FP64 16x16x4 result: lane (column l15) register r holds row 4 r + lk,
+  // which is the next product's right operand as it stands
+#pragma unroll
+  for (int r = 0; r < 4; ++r) sm.part[wave][r * 64 + lane] = w[r];
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    w[r] = 0.0;
+#pragma unroll
+    for (int wv = 0; wv < kQrWaves; ++wv) w[r] += sm.part[wv][r * 64 + lane];
+  }
+  qr_d4_t w2 = {};
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) w2 = __builtin_amdgcn_mfma_f64_16x16x4f64(t[kk], w[kk], w2, 0, 0, 0);
+#pragma unroll
+  for (int q = 0; q < NR; ++q) {
+    if (NR > 1) reflectors(q, v);
+    qr_stage(st, v);
+    double a[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) a[i][kk] = st[16 * i + l15][4 * kk + lk];
+    qr_wave_order();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      qr_d4_t o = {};
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) o = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i][kk], w2[kk], o, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) st[16 * i + 4 * r + lk][l15] = o[r];
+    }
+    qr_wave_order();
+#pragma unroll
+    for (int c = 0; c < kQrNb; ++c) x[q][c] -= st[lane][c];
+  }
+}
+
+// (ahead: the panel before it is applied first, and its rows are held too)
+template <int NR>
+__device__ inline void qr_panel(double* xc, double* tau, double* tf, int m, int j0, int nb, bool ahead, QrPanelSmem& sm) {
   auto& red = sm.red;
   auto& gram = sm.gram;
   auto& tl = sm.tl;
-  const int r0 = j0;   // rows above the panel's first are done
+  const int r0 = ahead ? j0 - kQrNb : j0;   // rows above are done
   int buf = 0;
   double x[NR][kQrNb];
 #pragma unroll
@@ -341,6 +438,7 @@ __device__ inline void qr_panel(double* xc, double* tau, double* tf, int m, int 
 #pragma unroll
     for (int c = 0; c < kQrNb; ++c) x[q][c] = (row < m && c < nb) ? xc[(int64_t)(j0 + c) * m + row] : 0.0;
   }
+  if (ahead) qr_ahead<NR>(x, xc, tf, m, r0, sm);
   qr_panel_step<0, NR>(x, red, sm.top, buf, tau, m, r0, j0, nb);
 #pragma unroll
   for (int q = 0; q < NR; ++q) {
@@ -362,42 +460,29 @@ __device__ inline void qr_panel(double* xc, double* tau, double* tf, int m, int 
       x[q][c] = (c >= nb || row >= m) ? 0.0 : (row == gc ? 1.0 : (row > gc ? x[q][c] : 0.0));
     }
   }
-  // Gram entries v_i . v_j (i < j), enumerated column by column: 120 pairs in
-  // batches of 16 (registers: the panel holds 128)
-  constexpr int kPairs = kQrNb * (kQrNb - 1) / 2;
-#pragma unroll
-  for (int b0 = 0; b0 < kPairs; b0 += 16) {
-    double g[16];
-#pragma unroll
-    for (int p = 0; p < 16; ++p) {
-      g[p] = 0.0;
-      const int pp = b0 + p;
-      if (pp < kPairs) {
-        int j = 1, base = 0;
-#pragma unroll
-        for (int jj = 1; jj < kQrNb; ++jj)
-          if (pp >= jj * (jj - 1) / 2) {
-            j = jj;
-            base = jj * (jj - 1) / 2;
-          }
-        const int i = pp - base;
-#pragma unroll
-        for (int q = 0; q < NR; ++q) g[p] += x[q][i] * x[q][j];
-      }
-    }
-    const double v = qr_reduce_scatter<16>(g);
+  // Gram matrix of the reflectors, on the matrix cores
+  {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (lane < 16) red[buf][wave * 16 + lane] = v;
+    qr_d4_t g = {};
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      double o[16];
+      qr_stage(sm.stage[wave], x[q]);
+      qr_rows(sm.stage[wave], o);
+#pragma unroll
+      for (int kk = 0; kk < 16; ++kk) g = __builtin_amdgcn_mfma_f64_16x16x4f64(o[kk], o[kk], g, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sm.part[wave][r * 64 + lane] = g[r];
     __syncthreads();
-    if (threadIdx.x < 16 && b0 + (int)threadIdx.x < kPairs) {
+    if (threadIdx.x < kQrNb * kQrNb) {
       double t = 0.0;
 #pragma unroll
-      for (int wv = 0; wv < kQrWaves; ++wv) t += red[buf][wv * 16 + threadIdx.x];
-      gram[b0 + threadIdx.x] = t;   // packed pair order
+      for (int wv = 0; wv < kQrWaves; ++wv) t += sm.part[wv][threadIdx.x];
+      gram[threadIdx.x] = t;
     }
-    buf ^= 1;
+    __syncthreads();
   }
-  __syncthreads();
   // lane i builds row i of T: T[i][j] needs only T[i][i..j-1] (its own row)
   if (threadIdx.x < kQrNb) {
     const int i = threadIdx.x;
@@ -405,16 +490,10 @@ __device__ inline void qr_panel(double* xc, double* tau, double* tf, int m, int 
 #pragma unroll
     for (int j = 0; j < kQrNb; ++j) {
       const double tj = j < nb ? tau[j0 + j] : 0.0;
-      double v = 0.0;
-      if (i < j) {
+      double v = 0.0;   // row[l] is zero for l < i
 #pragma unroll
-        for (int l = 0; l < j; ++l)
-          if (l >= i) v += row[l] * gram[j * (j - 1) / 2 + l];
-        v *= -tj;
-      } else if (i == j) {
-        v = tj;
-      }
-      row[j] = v;
+      for (int l = 0; l < j; ++l) v += row[l] * gram[l * kQrNb + j];
+      row[j] = i < j ? -tj * v : i == j ? tj : 0.0;
     }
 #pragma unroll
     for (int j = 0; j < kQrNb; ++j) tl[i * kQrNb + j] = row[j];
@@ -524,17 +603,20 @@ __device__ inline void qr_update(double* xc, const double* tf, int m, int j0, in
   qr_store_y<NR>(xc, m, j0, cb0, n, yv);
 }
 
-// The whole factorisation in one launch.  Its tasks are the panels and the
-// applications of a panel to a group of kQrCb columns; workgroups take them
-// from a counter in an order in which every task comes after those it needs:
-//   panel 0; then for p = 0, 1, ...: apply p to the columns of panel p + 1,
-//   panel p + 1, apply p to the other columns
-// so that the next panel runs while the last one is still being applied.  A
-// workgroup that waits does so for tasks with smaller numbers, which running
-// workgroups have taken; the one with the smallest number never waits, so
-// every wait ends whatever share of the grid is resident.
-// ctr: the task counter, the number of finished panels, and per column group
-// the number of panels applied to it (zero at the start).
+// The whole factorisation in one launch.  The workgroup that is first does the
+// panels, one after the other (its code and its own panel stay close; dealt to
+// any workgroup they took 49 us each, and now 44), each with the panel before it
+// applied to its own columns.  The tasks of the others are the applications of
+// panel p to a group of kQrCb columns past panel p + 1, in the order of p,
+// taken from a counter.  An application waits for its panel and
+// for the last application to its columns, which has a smaller number and so
+// has been taken by a running workgroup.  A panel waits for the applications
+// of all but the last panel to its columns; while these have not been taken
+// the panels' workgroup takes tasks itself, so every wait ends whatever share
+// of the grid is resident.
+// ctr: the task counter, the number of finished panels, the number of
+// workgroups begun, and per column group the number of panels applied to it
+// (zero at the start).
 __host__ __device__ inline int qr_groups(int n) { return (n + kQrCb - 1) / kQrCb; }
 
 __device__ inline void qr_wait(const uint32_t* flag, uint32_t want) {
@@ -562,42 +644,63 @@ __global__ void __launch_bounds__(kQrThreads) qr_factor_kernel(double* xc, doubl
   const int groups = qr_groups(n), panels = (n + kQrNb - 1) / kQrNb;
   constexpr int GP = kQrNb / kQrCb;   // column groups a panel
   uint32_t* done = ctr + 1;
-  uint32_t* applied = ctr + 2;
-  // tasks base .. base + size - 1: panel p's applications and panel p + 1
-  int p = -1, base = 0, size = 1;
+  uint32_t* applied = ctr + 3;
+  // panel p's applications: groups GP (p + 2) and on
+  auto count = [&](int p) { return groups > GP * (p + 2) ? groups - GP * (p + 2) : 0; };
+  auto apply = [&](int p, int g) {
+    const int j0 = p * kQrNb;
+    qr_wait(done, (uint32_t)(p + 1));
+    qr_wait(applied + g, (uint32_t)p);
+    qr_acquire();
+    if (m - j0 <= kQrThreads) qr_update<1>(xc, tf, m, j0, kQrNb, g * kQrCb, n, sm.apply);
+    else if (m - j0 <= 2 * kQrThreads) qr_update<2>(xc, tf, m, j0, kQrNb, g * kQrCb, n, sm.apply);
+    else qr_update<kQrRows>(xc, tf, m, j0, kQrNb, g * kQrCb, n, sm.apply);
+    qr_signal(applied + g, (uint32_t)(p + 1));
+  };
+  if (threadIdx.x == 0) s_task = (int)atomicAdd(ctr + 2, 1u);
+  __syncthreads();
+  const bool first = s_task == 0;
+  // tasks base .. base + count(p) - 1 are panel p's
+  int p = 0, base = 0, q = first ? 0 : panels;
   for (;;) {
     __syncthreads();
-    if (threadIdx.x == 0) s_task = (int)atomicAdd(ctr, 1u);
-    __syncthreads();
-    const int task = s_task;
-    while (p < panels && task >= base + size) {
-      base += size;
-      ++p;
-      const int ng = groups - GP * (p + 1);
-      size = p >= panels ? 0 : (ng > 0 ? ng : 0) + (p + 1 < panels ? 1 : 0);
-    }
-    if (p >= panels) return;
-    const int local = task - base, ng = p < 0 ? 0 : groups - GP * (p + 1), first = ng < GP ? ng : GP;
-    if (local == first) {   // panel p + 1
-      const int q = p + 1, j0 = q * kQrNb;
-      for (int g = GP * q; q > 0 && g < GP * (q + 1) && g < groups; ++g) qr_wait(applied + g, (uint32_t)q);
-      qr_acquire();
-      const int nb = n - j0 < kQrNb ? n - j0 : kQrNb;
-      if (m - j0 <= kQrThreads) qr_panel<1>(xc, tau, tf, m, j0, nb, sm.panel);
-      else if (m - j0 <= 2 * kQrThreads) qr_panel<2>(xc, tau, tf, m, j0, nb, sm.panel);
-      else qr_panel<kQrRows>(xc, tau, tf, m, j0, nb, sm.panel);
-      qr_signal(done, (uint32_t)(q + 1));
+    if (q < panels) {
+      // the next panel, as soon as all tasks that it needs have been taken
+      int need = 0;   // tasks up to panel q - 2's last for its columns
+      for (int i = 0; i < q - 2; ++i) need += count(i);
+      if (q >= 2) need += min(GP * (q + 1), groups) - GP * q;
+      if (threadIdx.x == 0) {
+        uint32_t t = __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_task = -1;
+        while ((int)t < need) {
+          if (__hip_atomic_compare_exchange_strong(ctr, &t, t + 1, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT)) {
+            s_task = (int)t;
+            break;
+          }
+        }
+      }
+      __syncthreads();
+      if (s_task < 0) {
+        const int j0 = q * kQrNb;
+        for (int g = GP * q; q > 1 && g < GP * (q + 1) && g < groups; ++g) qr_wait(applied + g, (uint32_t)(q - 1));
+        qr_acquire();
+        const int nb = n - j0 < kQrNb ? n - j0 : kQrNb, rows = m - (q > 0 ? j0 - kQrNb : 0);
+        if (rows <= kQrThreads) qr_panel<1>(xc, tau, tf, m, j0, nb, q > 0, sm.panel);
+        else if (rows <= 2 * kQrThreads) qr_panel<2>(xc, tau, tf, m, j0, nb, q > 0, sm.panel);
+        else qr_panel<kQrRows>(xc, tau, tf, m, j0, nb, q > 0, sm.panel);
+        ++q;
+        qr_signal(done, (uint32_t)q);
+        continue;
+      }
     } else {
-      const int g = GP * (p + 1) + local - (local > first ? 1 : 0), j0 = p * kQrNb;
-      qr_wait(done, (uint32_t)(p + 1));
-      qr_wait(applied + g, (uint32_t)p);
-      qr_acquire();
-      const int nb = n - j0 < kQrNb ? n - j0 : kQrNb;
-      if (m - j0 <= kQrThreads) qr_update<1>(xc, tf, m, j0, nb, g * kQrCb, n, sm.apply);
-      else if (m - j0 <= 2 * kQrThreads) qr_update<2>(xc, tf, m, j0, nb, g * kQrCb, n, sm.apply);
-      else qr_update<kQrRows>(xc, tf, m, j0, nb, g * kQrCb, n, sm.apply);
-      qr_signal(applied + g, (uint32_t)(p + 1));
+      if (threadIdx.x == 0) s_task = (int)atomicAdd(ctr, 1u);
+      __syncthreads();
     }
+    const int task = s_task;
+    while (p < panels && task >= base + count(p)) base += count(p++);
+    if (p >= panels) return;
+    apply(p, GP * (p + 2) + task - base);
   }
 }
 
@@ -686,7 +789,7 @@ bool householder_qr_fits(int64_t m) { return m <= (int64_t)kQrThreads * kQrRows;
 
 // the panels' T factors, then the task counters of the factorisation
 static size_t qr_tf_doubles(int64_t n) { return (size_t)((n + kQrNb - 1) / kQrNb) * kQrNb * kQrNb; }
-static size_t qr_ctr_words(int64_t n) { return 2 + (size_t)qr_groups((int)n); }
+static size_t qr_ctr_words(int64_t n) { return 3 + (size_t)qr_groups((int)n); }
 size_t householder_tf_doubles(int64_t n) { return qr_tf_doubles(n) + (qr_ctr_words(n) + 1) / 2; }
 
 // as many workgroups as the widest application has column groups, one a compute unit
@@ -694,7 +797,7 @@ static int qr_grid(int n) { return std::max(1, std::min(256, qr_groups(n))); }
 
 // Y := Q Y or Q [I; 0], the rows 1, 2 or 4 a thread as in the factorisation (a
 // panel's rows start at its first; with 4 a thread throughout, 512 x 512 took
-// 2.49 ms to factorise and 0.38 ms here, now 1.91 and 0.21)
+// 2.49 ms to factorise and 0.38 ms here, with 2 then 1 1.91 and 0.21)
 static void launch_form(const double* xc, const double* tf, double* y, int m, int n, int ncols, bool eye,
                         const uint64_t* cert, hipStream_t st) {
   const dim3 grid((unsigned)qr_groups(ncols)), blk(kQrThreads);
