@@ -39,6 +39,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <mutex>
 #include <vector>
 
 #include "jacobi.h"
@@ -861,6 +862,72 @@ int32_t write_outputs(const tn_tensor* a, int32_t n_left, int32_t k, const tn_te
   return hip_check(hipGetLastError(), "split node outputs");
 }
 
+// The stream on which a split reads its counts.  It is the call's alone: on
+// one shared with other calls (the side streams) it would wait for their work,
+// and would be drawn into a capture that one of them has under way.  Idle ones
+// are kept for later calls, at most kIdle.  On a stream that is being captured
+// the reads stay on it (and fail there: a split waits for its counts).
+class CountStream {
+ public:
+  hipStream_t s = nullptr;
+  int32_t take(hipStream_t st) {
+    s = st;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+      (void)hipGetLastError();
+      return TN_OK;
+    }
+    if (cap != hipStreamCaptureStatusNone) return TN_OK;
+    TN_TRY(hip_check(hipGetDevice(&dev_), "get device"));
+    {
+      std::lock_guard<std::mutex> lk(mu());
+      for (Idle& i : idle())
+        if (i.s && i.dev == dev_) {
+          s = i.s;
+          i.s = nullptr;
+          own_ = true;
+          return TN_OK;
+        }
+    }
+    TN_TRY(hip_check(hipStreamCreateWithFlags(&s, hipStreamNonBlocking), "create stream"));
+    own_ = true;
+    return TN_OK;
+  }
+  ~CountStream() {
+    if (!own_) return;
+    {
+      std::lock_guard<std::mutex> lk(mu());
+      for (Idle& i : idle())
+        if (!i.s) {
+          i.s = s;
+          i.dev = dev_;
+          return;
+        }
+    }
+    (void)hipStreamDestroy(s);
+  }
+  CountStream() = default;
+  CountStream(const CountStream&) = delete;
+  CountStream& operator=(const CountStream&) = delete;
+
+ private:
+  static constexpr int kIdle = 8;
+  struct Idle {
+    hipStream_t s = nullptr;
+    int dev = 0;
+  };
+  static std::mutex& mu() {
+    static std::mutex m;
+    return m;
+  }
+  static Idle (&idle())[kIdle] {
+    static Idle x[kIdle];
+    return x;
+  }
+  int dev_ = 0;
+  bool own_ = false;
+};
+
 }  // namespace
 
 }  // namespace tn
@@ -933,11 +1000,12 @@ int32_t tn_split_node_decompose(const tn_tensor* a, int32_t n_left, int32_t max_
       int at = 0;
       bool done = false;
       // A sweep is issued together with the check that precedes it, and the
-      // host reads the check's count on a side stream meanwhile: the device
+      // host reads the check's count on another stream meanwhile: the device
       // does not wait for the host between sweeps (50 us each), and the last
       // sweep's kernels find the count zero and leave.  Two counts in turn.
-      hipStream_t rs = st;
-      TN_TRY(side_stream(rs));
+      CountStream reader;
+      TN_TRY(reader.take(st));
+      const hipStream_t rs = reader.s;
       hipEvent_t counted = nullptr;
       TN_TRY(hip_check(hipEventCreateWithFlags(&counted, hipEventDisableTiming), "create event"));
       auto sweep = [&]() -> int32_t {

@@ -6,6 +6,8 @@ degenerate, of low rank or zero, scales near the ends of FP64's range.
 Gates: the columns count as orthogonal at |x_i . x_j| <= 8 sqrt(rows) eps |x_i|
 |x_j|, twice that for the vectors; values and the product to 1e-13 of the
 largest value (a thousand roundings of the up to 600 terms a value sums)."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -98,3 +100,44 @@ def test_workspace_holding_nan(shape):
     poison = torch.full((16 << 20,), float("nan"), dtype=torch.float64, device=DEV)
     del poison
     check(a)
+
+
+def test_beside_a_capture_on_other_streams():
+    """A split leaves a capture that another thread has under way alone, on
+    whichever streams either works: its reads share no stream with it."""
+    rng = np.random.default_rng(8)
+    a = rng.standard_normal((70, 40))
+    ga = torch.tensor(a, device=DEV)
+    dims = [1, 2, 4, 8, 16, 32, 33, 32, 16, 8, 4, 2, 1]
+    raw = [rng.standard_normal((dims[k], 2, dims[k + 1])) for k in range(len(dims) - 1)]
+    sites = [torch.tensor(x, device=DEV) for x in raw]
+    wantnorm = float(tn.mps_left_canonicalize(sites))
+    want = [x.cpu().numpy() for x in sites]
+    for x, r in zip(sites, raw):
+        x.copy_(torch.tensor(r, device=DEV))
+    streams = [torch.cuda.Stream() for _ in range(5)]
+    torch.cuda.synchronize()
+    got, failed = [], []
+
+    def splits():
+        try:
+            for st in streams:
+                with torch.cuda.stream(st):
+                    got.append(tn.split_node_full_svd(ga, [0], [1])[1].cpu().numpy())
+        except Exception as e:   # noqa: BLE001 (re-raised on the main thread)
+            failed.append(e)
+
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, capture_error_mode="thread_local"):
+        lognorm = tn.mps_left_canonicalize(sites)
+        worker = threading.Thread(target=splits)
+        worker.start()
+        worker.join(60)
+    assert not failed, failed
+    s0 = np.linalg.svd(a)[1]
+    assert len(got) == len(streams)
+    for s in got:
+        np.testing.assert_allclose(np.diag(s) if s.ndim == 2 else s, s0, rtol=0, atol=1e-13 * s0[0])
+    graph.replay()
+    torch.cuda.synchronize()
+    assert float(lognorm) == wantnorm and all(np.array_equal(x.cpu().numpy(), w) for x, w in zip(sites, want))
