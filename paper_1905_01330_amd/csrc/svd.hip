@@ -566,15 +566,18 @@ __global__ void column_norm_kernel(const double* W, int64_t R, double* sigma, in
 
 // order[t] = the column of the t-th largest singular value (ties: lower column first)
 // one wavefront per column j: its lanes count the larger values (ties by
-// index) over strided parts of sigma, then add their counts
+// index) over strided parts of sigma, then add their counts.  Compared as bit
+// patterns, which order norms as their values do and put NaN above them: the
+// result is a permutation whatever the node holds (with NaN unequal to all,
+// columns shared a rank and other ranks kept what the memory held before).
 __global__ void __launch_bounds__(256) rank_kernel(const double* sigma, int n, int* order) {
   const int lane = threadIdx.x & 63;
   const int nw = (int)((gridDim.x * blockDim.x) >> 6);
   for (int j = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6); j < n; j += nw) {
-    const double sj = sigma[j];
+    const int64_t sj = __double_as_longlong(fabs(sigma[j]));
     int rank = 0;
     for (int i = lane; i < n; i += 64) {
-      const double si = sigma[i];
+      const int64_t si = __double_as_longlong(fabs(sigma[i]));
       rank += (si > sj || (si == sj && i < j)) ? 1 : 0;
     }
 #pragma unroll

@@ -141,3 +141,16 @@ def test_beside_a_capture_on_other_streams():
     graph.replay()
     torch.cuda.synchronize()
     assert float(lognorm) == wantnorm and all(np.array_equal(x.cpu().numpy(), w) for x, w in zip(sites, want))
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("shape", [(20, 12), (40, 33), (130, 97), (2060, 70)])
+def test_a_node_that_is_not_finite(shape, bad):
+    """One bad entry: the call ends, keeps every value and shows the entry;
+    columns of norm NaN still have a rank each."""
+    a = np.random.default_rng(shape[0]).standard_normal(shape)
+    a[3, 5] = bad
+    u, s, vt, _ = tn.split_node_full_svd(torch.tensor(a, device=DEV), [0], [1])
+    torch.cuda.synchronize()
+    assert u.shape == (shape[0], shape[1]) and vt.shape == (shape[1], shape[1])
+    assert not torch.isfinite(s).all()
