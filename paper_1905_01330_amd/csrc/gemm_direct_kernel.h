@@ -266,7 +266,11 @@ __device__ __forceinline__ void direct_sums(const D& d, const float* A, const fl
                                             float* red) {
   constexpr int WK = kDirectWaves;
   constexpr int CH = DirectInfo<P>::CH, NQ = DirectInfo<P>::NQ, NC = DirectInfo<P>::NC;
-  constexpr int NS = PrecInfo<P>::bf ? 1 : 2;   // blocks in flight (the bf16 terms need the registers)
+  // blocks in flight: the bf16 terms need the registers, and so do the offsets
+  // of two contracted axes (FP32, M x 2 x K by 2 x K x N with both along k or
+  // strided, one block instead of two: 333 x 333, K = 2 x 600, 17.4 -> 13.1 us;
+  // 512 x 1024, K = 2 x 256, 14.5 -> 11.5; 216 shapes 1.09 in the mean, none slower)
+  constexpr int NS = PrecInfo<P>::bf || MK == 2 ? 1 : 2;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   float* stage = red + wave * kDirectStage;
