@@ -266,11 +266,14 @@ __device__ __forceinline__ void direct_sums(const D& d, const float* A, const fl
                                             float* red) {
   constexpr int WK = kDirectWaves;
   constexpr int CH = DirectInfo<P>::CH, NQ = DirectInfo<P>::NQ, NC = DirectInfo<P>::NC;
-  // blocks in flight: the bf16 terms need the registers, and so do the offsets
-  // of two contracted axes (FP32, M x 2 x K by 2 x K x N with both along k or
-  // strided, one block instead of two: 333 x 333, K = 2 x 600, 17.4 -> 13.1 us;
-  // 512 x 1024, K = 2 x 256, 14.5 -> 11.5; 216 shapes 1.09 in the mean, none slower)
-  constexpr int NS = PrecInfo<P>::bf || MK == 2 ? 1 : 2;
+  // Blocks in flight.  One where the bf16 terms need the registers, or the
+  // offsets of two contracted axes do (FP32, 333 x 333, K = 2 x 600 17.4 -> 13.1
+  // us; 512 x 1024, K = 2 x 256 14.5 -> 11.5; 216 shapes 1.08 in the mean, none
+  // slower), or where A is read in 4-byte loads, 16 a block: the shorter code
+  // starts sooner than a second block helps (both operands so, 333 x 1000 x 666
+  // 11.5 -> 10.0 us, 100 x 200 x 100 4.3 -> 3.9; 140 shapes 1.05 in the mean, the
+  // worst 2 % slower).  A along k alone gains 2 % in the mean and loses up to 4.
+  constexpr int NS = PrecInfo<P>::bf || MK == 2 || AM == D_ANY ? 1 : 2;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   float* stage = red + wave * kDirectStage;
