@@ -15,9 +15,9 @@
 // Loan 5.2.3): one workgroup factorises a panel of 16 columns held in
 // registers (one workgroup reduction per column, row conditions as selects so
 // the unrolled panel stays short) and forms the panel's triangular factor T
-// from the Gram matrix of its reflectors; I - V T^T V^T is applied to all
-// trailing columns (one reduction per workgroup), to the next panel's by the
-// next panel's workgroup on the matrix cores; Q is accumulated panel by
+// from the Gram matrix of its reflectors; I - V T^T V^T is applied to the
+// columns of the panels after it on the matrix cores, a panel's columns a
+// workgroup (the next panel's by that panel's own); Q is accumulated panel by
 // panel in reverse with I - V T V^T.  All panels and updates of a matrix are
 // tasks of one launch.  Taller matrices take one reflector launch and one
 // update launch per column.
@@ -138,7 +138,7 @@ __global__ void __launch_bounds__(256) reflect_cols_kernel(const double* __restr
 constexpr int kQrThreads = 512;   // threads per workgroup; thread t owns rows t + 512 q
 constexpr int kQrRows = 4;        // rows per thread
 constexpr int kQrNb = 16;         // panel width
-constexpr int kQrCb = 4;          // trailing columns per workgroup
+constexpr int kQrCb = 4;          // columns of a product with Q per workgroup
 constexpr int kQrWaves = kQrThreads / 64;
 
 // x from lane (this lane xor M) of the wavefront.  Within a 16-lane row (M <
@@ -350,40 +350,86 @@ __device__ __forceinline__ void qr_rows(const double (*st)[kQrNb + 1], double (&
   for (int kk = 0; kk < 16; ++kk) o[kk] = st[4 * kk + (lane >> 4)][lane & 15];
 }
 
-// Panel j0 (whole, reflectors in X, factor T) applied to the next panel's
-// columns x, rows r0 = j0 on: x -= V T^T (V^T x) on the matrix cores.  The
-// next panel's own workgroup does it: by column groups in other workgroups it
-// was 7 us and a second exchange of data of a panel's 60 us (512 x 512, one
-// factorisation 1.91 ms, now 1.40 with the panels in one workgroup).
-template <int NR>
-__device__ inline void qr_ahead(double (&x)[NR][kQrNb], const double* __restrict__ xc, const double* __restrict__ tf,
-                                int m, int j0, QrPanelSmem& sm) {
+// A matrix (below 2^31 bytes) as a raw buffer: a thread's row is a vector
+// offset, a column a scalar one, and a row past the matrix an offset past the
+// buffer, which reads zero and is not written.  (Addresses of 16 columns each
+// would take the registers that a panel of four rows a thread needs.)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t qr_rsrc(const double* xc) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(xc), (short)0, (int)0x80000000, 0x00020000);
+}
+__device__ __forceinline__ uint32_t qr_row(int m, int r0, int q) {
+  const int row = r0 + threadIdx.x + kQrThreads * q;
+  return row < m ? (uint32_t)row * 8u : 0x80000000u;
+}
+// columns c0 .. c0 + nb - 1 at this thread's row q (rows from r0 on), zero past the matrix
+__device__ __forceinline__ void qr_columns(double (&x)[kQrNb], __amdgpu_buffer_rsrc_t rs, int m, int r0, int c0, int nb, int q) {
+  const uint32_t row = qr_row(m, r0, q);
+#pragma unroll
+  for (int c = 0; c < kQrNb; ++c)
+    x[c] = __builtin_bit_cast(
+        double, __builtin_amdgcn_raw_buffer_load_b64(rs, c < nb ? row : 0x80000000u, c < nb ? (c0 + c) * m * 8 : 0, 0));
+}
+__device__ __forceinline__ void qr_store(const double (&x)[kQrNb], __amdgpu_buffer_rsrc_t rs, int m, int r0, int c0, int nb,
+                                         int q) {
+  typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+  const uint32_t row = qr_row(m, r0, q);
+#pragma unroll
+  for (int c = 0; c < kQrNb; ++c)
+    if (c < nb) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, x[c]), rs, row, (c0 + c) * m * 8, 0);
+}
+
+// Panel j0 (whole, reflectors in X, factor T) applied to the columns c0 .. c0 +
+// nb - 1, rows from j0 on: x -= V T^T (V^T x) on the matrix cores; f(q, x) with
+// the result at this thread's row q.  The next panel's own workgroup does it
+// for that panel's columns (by other workgroups it was 7 us and a second
+// exchange of data of a panel's 60 us at 512 x 512).  Bound by the latency of a
+// workgroup's loads; each application also costs a release and an acquire of
+// the caches, so a task takes a panel's 16 columns.  With four columns a task,
+// summed by vector instructions, the applications were longer than the panels
+// from 1024 rows on: 2048 x 1024 7.1 -> 4.3 ms (4.9 with a launch a panel and a
+// launch an application), 1024 x 1024 4.5 -> 2.7, 512 x 512 1.38 -> 1.13.  Up
+// to two rows a thread x is read once and held between the two products, and
+// the reflectors are read ahead of them; with four the registers hold neither.
+template <int NR, class F>
+__device__ __forceinline__ void qr_block(__amdgpu_buffer_rsrc_t rs, const double* __restrict__ tf, int m, int j0, int c0,
+                                         int nb, QrPanelSmem& sm, F&& f) {
+  constexpr bool HOLD = NR <= 2;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l15 = lane & 15, lk = lane >> 4;
   auto st = sm.stage[wave];
   double t[4];
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) t[kk] = tf[(j0 / kQrNb) * kQrNb * kQrNb + (4 * kk + lk) * kQrNb + l15];
   auto reflectors = [&](int q, double (&v)[kQrNb]) {
-    const int row = j0 + threadIdx.x + kQrThreads * q;
+    qr_columns(v, rs, m, j0, j0, kQrNb, q);
+    const int at = threadIdx.x + kQrThreads * q;   // row j0 + at: column c is 1 at c, X below it, 0 above
 #pragma unroll
-    for (int c = 0; c < kQrNb; ++c) {
-      const int gc = j0 + c;
-      const double u = xc[(int64_t)gc * m + (row < m ? row : m - 1)];
-      v[c] = row == gc ? 1.0 : row > gc && row < m ? u : 0.0;
-    }
+    for (int c = 0; c < kQrNb; ++c) v[c] = at > c ? v[c] : at == c ? 1.0 : 0.0;
   };
-  double v[kQrNb];
+  double v[kQrNb], x[HOLD ? NR : 1][kQrNb];
   qr_d4_t w = {};
-#pragma unroll
-  for (int q = 0; q < NR; ++q) {
+  auto sum = [&](const double (&y)[kQrNb]) {
     double a[16], b[16];
-    reflectors(q, v);
     qr_stage(st, v);
     qr_rows(st, a);
-    qr_stage(st, x[q]);
+    qr_stage(st, y);
     qr_rows(st, b);
 #pragma unroll
     for (int kk = 0; kk < 16; ++kk) w = __builtin_amdgcn_mfma_f64_16x16x4f64(a[kk], b[kk], w, 0, 0, 0);
+  };
+  if constexpr (HOLD) {
+#pragma unroll
+    for (int q = 0; q < NR; ++q) {
+      qr_columns(x[q], rs, m, j0, c0, nb, q);
+      reflectors(q, v);
+      sum(x[q]);
+    }
+  } else {
+#pragma unroll 1
+    for (int q = 0; q < NR; ++q) {
+      reflectors(q, v);
+      qr_columns(x[0], rs, m, j0, c0, nb, q);
+      sum(x[0]);
+    }
   }
   // FP64 16x16x4 result: lane (column l15) register r holds row 4 r + lk,
   // which is the next product's right operand as it stands
@@ -401,25 +447,32 @@ __device__ inline void qr_ahead(double (&x)[NR][kQrNb], const double* __restrict
   for (int kk = 0; kk < 4; ++kk) w2 = __builtin_amdgcn_mfma_f64_16x16x4f64(t[kk], w[kk], w2, 0, 0, 0);
 #pragma unroll
   for (int q = 0; q < NR; ++q) {
+    double(&y)[kQrNb] = x[HOLD ? q : 0];
     if (NR > 1) reflectors(q, v);
+    if (!HOLD) qr_columns(y, rs, m, j0, c0, nb, q);
     qr_stage(st, v);
-    double a[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) a[i][kk] = st[16 * i + l15][4 * kk + lk];
-    qr_wave_order();
+    constexpr int AHEAD = HOLD ? 4 : 1;   // 16-row blocks read at a time
+    double a[AHEAD][4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
+      if (i % AHEAD == 0) {
+#pragma unroll
+        for (int h = 0; h < AHEAD; ++h)
+#pragma unroll
+          for (int kk = 0; kk < 4; ++kk) a[h][kk] = st[16 * (i + h) + l15][4 * kk + lk];
+        qr_wave_order();
+      }
       qr_d4_t o = {};
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) o = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i][kk], w2[kk], o, 0, 0, 0);
+      for (int kk = 0; kk < 4; ++kk) o = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i % AHEAD][kk], w2[kk], o, 0, 0, 0);
 #pragma unroll
       for (int r = 0; r < 4; ++r) st[16 * i + 4 * r + lk][l15] = o[r];
     }
     qr_wave_order();
 #pragma unroll
-    for (int c = 0; c < kQrNb; ++c) x[q][c] -= st[lane][c];
+    for (int c = 0; c < kQrNb; ++c) y[c] -= st[lane][c];
+    f(q, y);
+    if (!HOLD) __builtin_amdgcn_sched_barrier(0);   // one row's loads at a time: the registers hold no more
   }
 }
 
@@ -432,23 +485,19 @@ __device__ inline void qr_panel(double* xc, double* tau, double* tf, int m, int 
   const int r0 = ahead ? j0 - kQrNb : j0;   // rows above are done
   int buf = 0;
   double x[NR][kQrNb];
+  const __amdgpu_buffer_rsrc_t rs = qr_rsrc(xc);
+  if (ahead) {
+    qr_block<NR>(rs, tf, m, r0, j0, nb, sm, [&](int q, const double (&y)[kQrNb]) {
 #pragma unroll
-  for (int q = 0; q < NR; ++q) {
-    const int row = r0 + threadIdx.x + kQrThreads * q;
+      for (int c = 0; c < kQrNb; ++c) x[q][c] = y[c];
+    });
+  } else {
 #pragma unroll
-    for (int c = 0; c < kQrNb; ++c) x[q][c] = (row < m && c < nb) ? xc[(int64_t)(j0 + c) * m + row] : 0.0;
+    for (int q = 0; q < NR; ++q) qr_columns(x[q], rs, m, r0, j0, nb, q);
   }
-  if (ahead) qr_ahead<NR>(x, xc, tf, m, r0, sm);
   qr_panel_step<0, NR>(x, red, sm.top, buf, tau, m, r0, j0, nb);
 #pragma unroll
-  for (int q = 0; q < NR; ++q) {
-    const int row = r0 + threadIdx.x + kQrThreads * q;
-    if (row < m) {
-#pragma unroll
-      for (int c = 0; c < kQrNb; ++c)
-        if (c < nb) xc[(int64_t)(j0 + c) * m + row] = x[q][c];
-    }
-  }
+  for (int q = 0; q < NR; ++q) qr_store(x[q], rs, m, r0, j0, nb, q);
   // the reflectors in place of the panel: v_c is 1 at row j0 + c, X below it,
   // 0 above (and 0 in the columns past nb)
 #pragma unroll
@@ -514,16 +563,15 @@ __device__ inline void qr_load_v(const double* __restrict__ xc, int m, int r0, i
 }
 
 // Y (this workgroup's kQrCb columns, thread t's rows r0 + t + 512 q in yv) times
-// the panel j0 .. j0+nb-1 (reflectors in X, triangular factor T):
-// Y -= V T^T (V^T Y) in the factorisation (transpose: H_{nb-1} ... H_0 Y),
-// Y -= V T (V^T Y) for products with Q (H_0 ... H_{nb-1} Y)
+// the panel j0 .. j0+nb-1 (reflectors in X, triangular factor T) for products
+// with Q: Y -= V T (V^T Y) (H_0 ... H_{nb-1} Y)
 struct QrApplySmem {
   double red[kQrWaves * kQrNb * kQrCb];
   double sw[kQrNb * kQrCb], sw2[kQrNb * kQrCb], st[kQrNb * kQrNb];
 };
 template <int NR>
 __device__ inline void qr_apply(const double* __restrict__ xc, const double* __restrict__ tf, int m, int r0, int j0, int nb,
-                                bool transpose, double (&yv)[NR][kQrCb], QrApplySmem& sm) {
+                                double (&yv)[NR][kQrCb], QrApplySmem& sm) {
   constexpr int NW = kQrNb * kQrCb;   // 64 entries of W = V^T Y
   for (int e = threadIdx.x; e < kQrNb * kQrNb; e += kQrThreads) sm.st[e] = tf[(j0 / kQrNb) * kQrNb * kQrNb + e];
   double w[NW];
@@ -554,8 +602,7 @@ __device__ inline void qr_apply(const double* __restrict__ xc, const double* __r
     const int j = threadIdx.x / kQrCb, c = threadIdx.x % kQrCb;
     double t = 0.0;
 #pragma unroll
-    for (int l = 0; l < kQrNb; ++l)
-      t += (transpose ? sm.st[l * kQrNb + j] : sm.st[j * kQrNb + l]) * sm.sw[l * kQrCb + c];
+    for (int l = 0; l < kQrNb; ++l) t += sm.st[j * kQrNb + l] * sm.sw[l * kQrCb + c];
     sm.sw2[threadIdx.x] = t;
   }
   __syncthreads();
@@ -594,30 +641,21 @@ __device__ inline void qr_store_y(double* y, int m, int r0, int cb0, int ncols, 
   }
 }
 
-// panel j0 of X applied to X's columns cb0 .. of its group
-template <int NR>
-__device__ inline void qr_update(double* xc, const double* tf, int m, int j0, int nb, int cb0, int n, QrApplySmem& sm) {
-  double yv[NR][kQrCb];
-  qr_load_y<NR>(xc, m, j0, cb0, n, yv);
-  qr_apply<NR>(xc, tf, m, j0, j0, nb, true, yv, sm);
-  qr_store_y<NR>(xc, m, j0, cb0, n, yv);
-}
-
 // The whole factorisation in one launch.  The workgroup that is first does the
 // panels, one after the other (its code and its own panel stay close; dealt to
-// any workgroup they took 49 us each, and now 44), each with the panel before it
-// applied to its own columns.  The tasks of the others are the applications of
-// panel p to a group of kQrCb columns past panel p + 1, in the order of p,
-// taken from a counter.  An application waits for its panel and
-// for the last application to its columns, which has a smaller number and so
-// has been taken by a running workgroup.  A panel waits for the applications
-// of all but the last panel to its columns; while these have not been taken
-// the panels' workgroup takes tasks itself, so every wait ends whatever share
-// of the grid is resident.
+// any workgroup they took 49 us each at 512 x 512, so 44, and now 35), each with the
+// panel before it applied to its own columns.  The tasks of the others are the
+// applications of panel p to the columns of a panel past p + 1, in the order of
+// p, taken from a counter.  An application waits for its panel and for the last
+// application to its columns, which has a smaller number and so has been taken
+// by a running workgroup.  A panel waits for the applications of all but the
+// last panel to its columns; while these have not been taken the panels'
+// workgroup takes tasks itself, so every wait ends whatever share of the grid
+// is resident.
 // ctr: the task counter, the number of finished panels, the number of
-// workgroups begun, and per column group the number of panels applied to it
+// workgroups begun, and per panel the number of panels applied to its columns
 // (zero at the start).
-__host__ __device__ inline int qr_groups(int n) { return (n + kQrCb - 1) / kQrCb; }
+__host__ __device__ inline int qr_panels(int n) { return (n + kQrNb - 1) / kQrNb; }
 
 __device__ inline void qr_wait(const uint32_t* flag, uint32_t want) {
   if (threadIdx.x == 0)
@@ -636,25 +674,23 @@ __device__ inline void qr_signal(uint32_t* flag, uint32_t value) {
 __global__ void __launch_bounds__(kQrThreads) qr_factor_kernel(double* xc, double* tau, double* tf, int m, int n,
                                                                uint32_t* ctr, const uint64_t* cert) {
   if (chol_certified(cert)) return;
-  __shared__ union {
-    QrPanelSmem panel;
-    QrApplySmem apply;
-  } sm;
+  __shared__ QrPanelSmem sm;
   __shared__ int s_task;
-  const int groups = qr_groups(n), panels = (n + kQrNb - 1) / kQrNb;
-  constexpr int GP = kQrNb / kQrCb;   // column groups a panel
+  const int panels = qr_panels(n);
   uint32_t* done = ctr + 1;
   uint32_t* applied = ctr + 3;
-  // panel p's applications: groups GP (p + 2) and on
-  auto count = [&](int p) { return groups > GP * (p + 2) ? groups - GP * (p + 2) : 0; };
+  // panel p's applications: panels p + 2 and on
+  auto count = [&](int p) { return max(panels - p - 2, 0); };
   auto apply = [&](int p, int g) {
-    const int j0 = p * kQrNb;
+    const int j0 = p * kQrNb, c0 = g * kQrNb, nb = min(n - c0, kQrNb);
     qr_wait(done, (uint32_t)(p + 1));
     qr_wait(applied + g, (uint32_t)p);
     qr_acquire();
-    if (m - j0 <= kQrThreads) qr_update<1>(xc, tf, m, j0, kQrNb, g * kQrCb, n, sm.apply);
-    else if (m - j0 <= 2 * kQrThreads) qr_update<2>(xc, tf, m, j0, kQrNb, g * kQrCb, n, sm.apply);
-    else qr_update<kQrRows>(xc, tf, m, j0, kQrNb, g * kQrCb, n, sm.apply);
+    const __amdgpu_buffer_rsrc_t rs = qr_rsrc(xc);
+    auto store = [&](int q, const double (&y)[kQrNb]) { qr_store(y, rs, m, j0, c0, nb, q); };
+    if (m - j0 <= kQrThreads) qr_block<1>(rs, tf, m, j0, c0, nb, sm, store);
+    else if (m - j0 <= 2 * kQrThreads) qr_block<2>(rs, tf, m, j0, c0, nb, sm, store);
+    else qr_block<kQrRows>(rs, tf, m, j0, c0, nb, sm, store);
     qr_signal(applied + g, (uint32_t)(p + 1));
   };
   if (threadIdx.x == 0) s_task = (int)atomicAdd(ctr + 2, 1u);
@@ -666,9 +702,9 @@ __global__ void __launch_bounds__(kQrThreads) qr_factor_kernel(double* xc, doubl
     __syncthreads();
     if (q < panels) {
       // the next panel, as soon as all tasks that it needs have been taken
-      int need = 0;   // tasks up to panel q - 2's last for its columns
+      int need = 0;   // tasks up to panel q - 2's for its columns
       for (int i = 0; i < q - 2; ++i) need += count(i);
-      if (q >= 2) need += min(GP * (q + 1), groups) - GP * q;
+      if (q >= 2) ++need;
       if (threadIdx.x == 0) {
         uint32_t t = __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         s_task = -1;
@@ -683,12 +719,12 @@ __global__ void __launch_bounds__(kQrThreads) qr_factor_kernel(double* xc, doubl
       __syncthreads();
       if (s_task < 0) {
         const int j0 = q * kQrNb;
-        for (int g = GP * q; q > 1 && g < GP * (q + 1) && g < groups; ++g) qr_wait(applied + g, (uint32_t)(q - 1));
+        if (q > 1) qr_wait(applied + q, (uint32_t)(q - 1));
         qr_acquire();
         const int nb = n - j0 < kQrNb ? n - j0 : kQrNb, rows = m - (q > 0 ? j0 - kQrNb : 0);
-        if (rows <= kQrThreads) qr_panel<1>(xc, tau, tf, m, j0, nb, q > 0, sm.panel);
-        else if (rows <= 2 * kQrThreads) qr_panel<2>(xc, tau, tf, m, j0, nb, q > 0, sm.panel);
-        else qr_panel<kQrRows>(xc, tau, tf, m, j0, nb, q > 0, sm.panel);
+        if (rows <= kQrThreads) qr_panel<1>(xc, tau, tf, m, j0, nb, q > 0, sm);
+        else if (rows <= 2 * kQrThreads) qr_panel<2>(xc, tau, tf, m, j0, nb, q > 0, sm);
+        else qr_panel<kQrRows>(xc, tau, tf, m, j0, nb, q > 0, sm);
         ++q;
         qr_signal(done, (uint32_t)q);
         continue;
@@ -700,7 +736,7 @@ __global__ void __launch_bounds__(kQrThreads) qr_factor_kernel(double* xc, doubl
     const int task = s_task;
     while (p < panels && task >= base + count(p)) base += count(p++);
     if (p >= panels) return;
-    apply(p, GP * (p + 2) + task - base);
+    apply(p, p + 2 + task - base);
   }
 }
 
@@ -725,7 +761,7 @@ __global__ void __launch_bounds__(kQrThreads) qr_form_kernel(const double* __res
   const int last = (n - 1) / kQrNb;
   for (int p = eye ? min(last, cb0 / kQrNb) : last; p >= 0; --p) {
     __syncthreads();
-    qr_apply<NR>(xc, tf, m, 0, p * kQrNb, min(kQrNb, n - p * kQrNb), false, yv, sm);
+    qr_apply<NR>(xc, tf, m, 0, p * kQrNb, min(kQrNb, n - p * kQrNb), yv, sm);
   }
   qr_store_y<NR>(y, m, 0, cb0, ncols, yv);
 }
@@ -780,8 +816,6 @@ static unsigned blocks_for(int64_t n) {
   return (unsigned)std::max<int64_t>(1, std::min<int64_t>(b, 16384));
 }
 
-// X, Q and T come in two sets, used by alternate sites: a site's Q is formed
-// on the side stream while the next site is factorised
 // Householder QR of a column-major m x n matrix (m >= n) for other callers:
 // the blocked path only (m <= 2048), factorised in place (R in the upper
 // triangle, the reflectors below), T factors in tf; and the product Q y.
@@ -789,18 +823,18 @@ bool householder_qr_fits(int64_t m) { return m <= (int64_t)kQrThreads * kQrRows;
 
 // the panels' T factors, then the task counters of the factorisation
 static size_t qr_tf_doubles(int64_t n) { return (size_t)((n + kQrNb - 1) / kQrNb) * kQrNb * kQrNb; }
-static size_t qr_ctr_words(int64_t n) { return 3 + (size_t)qr_groups((int)n); }
+static size_t qr_ctr_words(int64_t n) { return 3 + (size_t)qr_panels((int)n); }
 size_t householder_tf_doubles(int64_t n) { return qr_tf_doubles(n) + (qr_ctr_words(n) + 1) / 2; }
 
-// as many workgroups as the widest application has column groups, one a compute unit
-static int qr_grid(int n) { return std::max(1, std::min(256, qr_groups(n))); }
+// a workgroup for the panels and one for every task of the widest application
+static int qr_grid(int n) { return std::min(256, qr_panels(n)); }
 
 // Y := Q Y or Q [I; 0], the rows 1, 2 or 4 a thread as in the factorisation (a
 // panel's rows start at its first; with 4 a thread throughout, 512 x 512 took
-// 2.49 ms to factorise and 0.38 ms here, with 2 then 1 1.91 and 0.21)
+// 2.49 ms to factorise and 0.38 ms here, with 2 then 1 1.91, now 1.13, and 0.21)
 static void launch_form(const double* xc, const double* tf, double* y, int m, int n, int ncols, bool eye,
                         const uint64_t* cert, hipStream_t st) {
-  const dim3 grid((unsigned)qr_groups(ncols)), blk(kQrThreads);
+  const dim3 grid((unsigned)((ncols + kQrCb - 1) / kQrCb)), blk(kQrThreads);
   if (m <= kQrThreads) hipLaunchKernelGGL(qr_form_kernel<1>, grid, blk, 0, st, xc, tf, y, m, n, ncols, eye, cert);
   else if (m <= 2 * kQrThreads) hipLaunchKernelGGL(qr_form_kernel<2>, grid, blk, 0, st, xc, tf, y, m, n, ncols, eye, cert);
   else hipLaunchKernelGGL(qr_form_kernel<kQrRows>, grid, blk, 0, st, xc, tf, y, m, n, ncols, eye, cert);
@@ -825,6 +859,8 @@ int32_t householder_apply_q(const double* xc, int m, int n, const double* tf, do
 // launches.
 constexpr int kCholMin = 32;
 
+// X, Q and T come in two sets, used by alternate sites: a site's Q is formed
+// on the side stream while the next site is factorised
 struct QrLayout {
   size_t x[2], q[2], r, tau, tf[2], g, r1, u[2], linv, ebits, total;
 };

@@ -93,6 +93,18 @@ def test_sites_without_a_certificate(kind, n):
     check(raw, *gauge(raw), agree=False)
 
 
+@pytest.mark.parametrize("rows,n", [(511, 33), (512, 64), (513, 47), (529, 96), (1024, 100), (1025, 49), (1040, 80),
+                                    (1500, 131), (2047, 50), (2048, 257)])
+def test_panels_of_one_two_and_four_rows_a_thread(rows, n):
+    """The Householder path alone (equal columns): rows that a thread of the
+    panels' workgroup holds, panels that shrink past a step of them, last
+    panels of 1 to 16 columns."""
+    rng = np.random.default_rng(rows)
+    raw = [rng.standard_normal((1, rows, n)), rng.standard_normal((n, 3, 1))]
+    raw[0][:, :, n // 2] = raw[0][:, :, 3]
+    check(raw, *gauge(raw), agree=False)
+
+
 @pytest.mark.parametrize("scale", [1e-140, 1e-30, 1e30, 1e140])
 def test_scales(scale):
     raw = chain(70, 66, 2, 5)
