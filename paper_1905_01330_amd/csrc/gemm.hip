@@ -489,7 +489,8 @@ bool direct_chosen(const GemmDesc& d, int32_t prec) {
     if (g_tune_level > 0 || !g_tune_path.empty()) return false;
   }
   SharedChipScope shared;
-  return g_forced_cfg.load() < 0 && direct_ok(d) && heuristic_choice(d, prec) == kCfg32;
+  // the small-extent path comes first, as in launch_gemm: its sums are FP64
+  return g_forced_cfg.load() < 0 && !gemm_small_fits(d) && direct_ok(d) && heuristic_choice(d, prec) == kCfg32;
 }
 
 // the stream on which the tuner runs the second copy of a GEMM that shares

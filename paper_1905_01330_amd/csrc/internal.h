@@ -92,8 +92,8 @@ int32_t launch_gemm_small(const GemmDesc& d, int32_t prec, hipStream_t st);
 bool direct_ok(const GemmDesc& d);
 int32_t launch_gemm_direct(const GemmDesc& d, int32_t prec, hipStream_t st);
 // whether a GEMM issued now beside another of its size runs whole on the
-// direct kernel: few tiles, no tile forced, no tuning and no tile cache file
-// that could say otherwise
+// direct kernel: few tiles, not a problem of the small-extent path, no tile
+// forced, no tuning and no tile cache file that could say otherwise
 bool direct_chosen(const GemmDesc& d, int32_t prec);
 // two independent GEMMs (either may be null) in one launch of the direct
 // kernel, where direct_pair_ok

@@ -149,3 +149,50 @@ def test_inner_product_in_shared_launches(prec, dims):
     norms = [v[0] * np.exp(v[1]) for v in (oracle.mps_inner(psi, psi), oracle.mps_inner(phi, phi))]
     # relative to the Cauchy-Schwarz scale: the overlap of two random chains cancels
     assert abs(m * np.exp(s) - value) <= TOL[prec] * np.sqrt(norms[0] * norms[1])
+
+
+def short_sums(side):
+    """A chain whose site 1 contracts few terms that cancel (left: 11 with bond
+    187 beside it, right: 2 beside 190), on one end of a long free extent."""
+    rng = np.random.default_rng(12)
+    if side == "left":
+        a0 = np.zeros((1, 2, 11))
+        a0[0, 0, 10] = 1
+        a0[0, 1, :3] = 1   # L_1[a', a] = a0[0, a'] a0[1, a]
+        a1 = rng.uniform(1, 2, (11, 2, 187))
+        a1[0] = 2.0**24 * (2 * rng.integers(0, 4, (2, 187)) + 1)
+        a1[2] = -a1[0]
+        psi = [a0, a1, rng.standard_normal((187, 2, 1))]
+        bonds = (1, 1)
+    else:
+        e = 2.0**-12
+        k = rng.integers(1, 100, (190, 2))
+        a1 = np.stack([1 + k * e, -(1 + (k + 1) * e)], axis=2)   # times (1 + e, 1): k e^2
+        a2 = np.zeros((2, 2, 1))
+        a2[0, 0] = 1
+        a2[:, 1, 0] = 1 + e, 1
+        psi = [rng.standard_normal((1, 2, 190)), a1, a2]
+        bonds = (1, 8)
+    psi = [x.astype(np.float32).astype(np.float64) for x in psi]
+    up = np.array([[0.0, 1.0], [0.0, 0.0]])
+    mpo = [np.zeros((1, bonds[0], 2, 2)), np.zeros((bonds[0], bonds[1], 2, 2)), np.zeros((bonds[1], 1, 2, 2))]
+    mpo[0][0, 0], mpo[1][0, 0], mpo[2][0, 0] = (up, np.eye(2), np.eye(2)) if side == "left" else (np.eye(2), np.eye(2), up)
+    return psi, mpo
+
+
+@pytest.mark.parametrize("prec,gate", [("fp32", 2.0**-21), ("split_bf16_3p", 2.0**-14)])
+@pytest.mark.parametrize("side", ["left", "right"])
+def test_short_sums_of_a_sweep_are_exact(side, prec, gate):
+    """A contraction of at most 32 terms with a free extent of at most 16 sums
+    in FP64 from whole operands, in a sweep as anywhere else: what is left are
+    the roundings of its result, the operator step and the second contraction
+    (four of FP32; three terms of 2^-16 in two BF16 parts)."""
+    psi, mpo = short_sums(side)
+    left = side == "left"
+    ls, rs, _, _ = oracle.env_sweep(psi, mpo)
+    gl, gr, _ = tn.mps_env_sweep([torch.tensor(x, dtype=torch.float32, device=DEV) for x in psi],
+                                 [torch.tensor(x, dtype=torch.float32, device=DEV) for x in mpo],
+                                 left=left, right=not left, prec=prec)
+    torch.cuda.synchronize()
+    got, want = (gl[2], ls[2]) if left else (gr[1], rs[1])
+    np.testing.assert_allclose(got.cpu().double().numpy(), want, rtol=gate)
