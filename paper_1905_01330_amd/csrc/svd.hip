@@ -60,6 +60,13 @@ constexpr int kInnerSweeps = 14;
 constexpr int kGramMinCols = 32;
 constexpr int kGramSweeps = 30;       // sweeps on the Gram matrix before the columns' own take over
 
+// tan of the smaller angle with cot(2 angle) = z.  Past 2^500 (columns whose
+// norms differ by as much) the square would overflow and the root is |z|.
+__device__ __forceinline__ double jacobi_tan(double z) {
+  const double a = fabs(z);
+  return (z >= 0.0 ? 1.0 : -1.0) / (a + (a < 0x1p500 ? sqrt(1.0 + a * a) : a));
+}
+
 // Strided matrix view of the node: element (i, j) at p + off(i over rows) + off(j over cols)
 struct MatView {
   const void* p;
@@ -228,7 +235,7 @@ __global__ void __launch_bounds__(kNT) jacobi_pair_kernel(double* W, double* V, 
         double c = 1.0, s = 0.0;
         if (apq != 0.0 && fabs(apq) > 1e-300) {
           const double tau = (aqq - app) / (2.0 * apq);
-          const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
+          const double t = jacobi_tan(tau);
           c = 1.0 / sqrt(1.0 + t * t);
           s = t * c;
         }
@@ -436,7 +443,7 @@ __global__ void __launch_bounds__(kNT) jacobi_lds_kernel(double* W, double* V, i
       const bool rot = ga != 0.0 && ga * ga > (tol * tol) * (al * be);
       if (rot) {
         const double zeta = (be - al) / (2.0 * ga);
-        const double t = (zeta >= 0.0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
+        const double t = jacobi_tan(zeta);
         c = rsqrt(1.0 + t * t);
         sn = t * c;
         rot_sweep = true;

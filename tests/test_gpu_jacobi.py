@@ -13,6 +13,7 @@ import pytest
 import torch
 
 import paper_1905_01330_amd as tn
+from test_gpu_split import decompose_sweeps
 
 pytestmark = pytest.mark.gpu
 DEV = torch.device("cuda:0")
@@ -91,6 +92,36 @@ def test_small_values_next_to_large_ones():
     s = s.cpu().numpy()
     s = np.diag(s) if s.ndim == 2 else s
     np.testing.assert_allclose(s, np.sort(norms)[::-1], rtol=1e-13)
+
+
+def blocks(rows, sizes, scales, seed):
+    """A node of column blocks of independent normal entries, each far below the
+    one before it, and its values: a block's are those of what it leaves beside
+    the earlier blocks, to the square of the blocks' ratio."""
+    rng = np.random.default_rng(seed)
+    a = rng.standard_normal((rows, sum(sizes)))
+    r = np.linalg.qr(a)[1]
+    ends = np.cumsum(sizes)
+    s = [np.linalg.svd(r[e - n:e, e - n:e], compute_uv=False) * f for n, e, f in zip(sizes, ends, scales)]
+    return a * np.repeat(scales, sizes), np.concatenate(s)
+
+
+# block pairs are at most ten in condition: a value's error is ten times the
+# gate of the columns' orthogonality (sqrt(rows) 2e-15 there), 1e-12 in all
+@pytest.mark.parametrize("rows", [90, 2060])
+@pytest.mark.parametrize("n", [50, 64])
+def test_columns_sweeps_take_over(n, rows):
+    """Squares of the small columns vanish in a Gram matrix scaled by the large
+    one: its sweeps do not end, and those on the columns finish the node."""
+    a, want = blocks(rows, [1, n - 1], [1e89, 1e-72], n)
+    ga = torch.tensor(a, device=DEV)
+    k, sweeps = decompose_sweeps(ga, 1)
+    assert k == n and sweeps > 30
+    u, s, vt, _ = (x.cpu().numpy() for x in tn.split_node_full_svd(ga, [0], [1]))
+    np.testing.assert_allclose(np.diag(s), want, rtol=1e-12)
+    # the small columns' part of the node from the small values alone
+    np.testing.assert_allclose(u[:, 1:] @ s[1:, 1:] @ vt[1:, 1:], (a - np.outer(u[:, 0], u[:, 0] @ a))[:, 1:],
+                               rtol=0, atol=1e-12 * want[1])
 
 
 @pytest.mark.parametrize("shape", [(33, 40), (97, 97), (130, 300), (2060, 70)])
