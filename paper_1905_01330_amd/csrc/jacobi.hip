@@ -56,22 +56,26 @@ __device__ __forceinline__ void jac_where(int nb, int round, int x, int& pair, i
 // Rotation by the angle that annihilates a_pq: s = sin(angle) and
 // u = tan(angle / 2).  With cos(2 angle) = |d| / r, r^2 = d^2 + b^2, the angle
 // is taken in single precision from values scaled to one (1e-7 of a_pq stays,
-// where convergence is quadratic anyway); s = 2 u / (1 + u^2) belongs to u to
-// double precision, one step from (1 + cos(angle)) / 2 = 1 / (1 + u^2).
+// where convergence is quadratic anyway), but for its factor b: between columns
+// of very different norms the angle is far below the smallest float.
+// s = 2 u / (1 + u^2) belongs to u to double precision, one step from
+// (1 + cos(angle)) / 2 = 1 / (1 + u^2).  Whether to rotate is asked of the
+// scaled values too: the products of entries of small columns would vanish.
 __device__ __forceinline__ void jac_angle(double app, double aqq, double apq, double tol2, double& s, double& u) {
-  const bool rot = apq * apq > tol2 * fabs(app * aqq);
   const double d = aqq - app, b = 2.0 * apq;
   // 2^-(exponent of the larger); entries of G are at most 1
   const int e = max(__double2hiint(d) & 0x7ff00000, __double2hiint(b) & 0x7ff00000);
   const double scale = __hiloint2double(0x7fe00000 - e, 0);
-  const float fd = fabsf((float)(d * scale));
-  const float fb = __int_as_float(__float_as_int((float)(b * scale)) ^ (__double2hiint(d) & 0x80000000));
+  const double bs = b * scale;
+  // (where d and b are far below the entries their scaled product is infinite, and that is orthogonal)
+  const bool rot = bs * bs > 4.0 * tol2 * fabs((app * scale) * (aqq * scale));
+  const float fd = fabsf((float)(d * scale)), fb = (float)bs;
   const float y = __builtin_amdgcn_rsqf(fd * fd + fb * fb);
   const float half = 0.5f + 0.5f * (fd * y);
   const float z = __builtin_amdgcn_rsqf(half);
   const float c1 = 1.0f + half * z;   // 1 + cos(angle)
-  const float h = 0.5f * fb * y * z * __builtin_amdgcn_rcpf(c1);
-  u = rot ? (double)h : 0.0;
+  const float h = 0.5f * y * z * __builtin_amdgcn_rcpf(c1);
+  u = rot ? __hiloint2double(__double2hiint(bs) ^ (__double2hiint(d) & 0x80000000), __double2loint(bs)) * (double)h : 0.0;
   const double w = 1.0 + u * u;
   double r = rot ? (double)(0.5f * c1) : 1.0;
   const double f = 1.0 - w * r;

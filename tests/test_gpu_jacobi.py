@@ -109,6 +109,21 @@ def blocks(rows, sizes, scales, seed):
 # block pairs are at most ten in condition: a value's error is ten times the
 # gate of the columns' orthogonality (sqrt(rows) 2e-15 there), 1e-12 in all
 @pytest.mark.parametrize("rows", [90, 2060])
+@pytest.mark.parametrize("scales", [[1, 1e-20, 1e-40, 1e-60], [1, 1e-50, 1e-75, 1e-100], [1e60, 1, 1e-30, 1e-60]])
+def test_spread_columns_that_are_not_orthogonal(scales, rows):
+    """Columns up to 1e-120 of the largest, not orthogonal to each other nor to
+    it: their angles are below single precision's range and the squares of
+    their products below double's, and the sweeps on the Gram matrix end all
+    the same."""
+    a, want = blocks(rows, [16, 20, 10, 4], scales, rows)
+    ga = torch.tensor(a, device=DEV)
+    k, sweeps = decompose_sweeps(ga, 1)
+    assert k == 50 and sweeps <= 20
+    s = np.diag(tn.split_node_full_svd(ga, [0], [1])[1].cpu().numpy())
+    np.testing.assert_allclose(s, want, rtol=1e-12)
+
+
+@pytest.mark.parametrize("rows", [90, 2060])
 @pytest.mark.parametrize("n", [50, 64])
 def test_columns_sweeps_take_over(n, rows):
     """Squares of the small columns vanish in a Gram matrix scaled by the large
