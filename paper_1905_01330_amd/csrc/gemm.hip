@@ -47,7 +47,7 @@ static const Cfg kCfgs[] = {
 };
 static constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
 // 32 x 32 tiles: the direct kernel (gemm_direct.hip) where it takes the
-// problem, else one wave a tile with run-time gathers
+// problem, else one wave a tile
 static constexpr int kCfg32 = 7, kCfg64 = 6;
 
 int gemm_num_cfgs() { return kNumCfgs; }
@@ -122,7 +122,7 @@ static GemmFn pick_fn(const GemmDesc& d, int prec, int cfg, bool lean) {
     if (lean) return split_fn(g.split, d.b_mode == LOAD_KVEC ? LOAD_KVEC : LOAD_MNVEC);
     cfg = g.fallback;
   }
-  return gemm_fn_prec(prec, cfg, cfg == kCfg32 ? 0 : gemm_variant(d));
+  return gemm_fn_prec(prec, cfg, gemm_variant(d));
 }
 
 // grouped configurations: 0 -> 128x128, 1 -> 64x64, 2 -> 32x32, 3 -> 64x64 in two k-slices

@@ -88,6 +88,29 @@ def test_groups_of_several_axes(prec, inner):
     check(tn.contract_between(ga, gpu(b), [5], [1], prec=prec), a, b, [5], [1], TOL[prec], "five free axes")
 
 
+@pytest.mark.parametrize("prec", ["fp32", "split_bf16"])
+@pytest.mark.parametrize("layout", ["kk", "km", "mk", "mm"])
+@pytest.mark.parametrize("last,n,k", [(4, 36, 40), (4, 33, 37), (3, 5, 64), (8, 64, 33)])
+def test_tiles_of_one_wave(last, n, k, layout, prec):
+    """Four row axes that do not merge: the 32 x 32 tile then runs on one wave,
+    with the gathers of the operands' layouts (k or the rows contiguous, whole
+    and partial runs of four)."""
+    rng = np.random.default_rng(last + n + k)
+    a = rng.standard_normal((3, 2, 2, last, k)).astype(np.float32)
+    b = rng.standard_normal((n, k)).astype(np.float32)
+    if layout[0] == "k":     # memory (2, last, 3, 2, k)
+        ga = gpu(a.transpose(1, 3, 0, 2, 4).copy()).permute(2, 0, 3, 1, 4)
+    else:                    # memory (k, 2, 3, 2, last)
+        ga = gpu(a.transpose(4, 2, 0, 1, 3).copy()).permute(2, 3, 1, 4, 0)
+    gb = gpu(b) if layout[1] == "k" else gpu(b.T.copy()).t()
+    tn.tune_force_config(TILE)
+    try:
+        got = tn.contract_between(ga, gb, [4], [1], prec=prec)
+    finally:
+        tn.tune_force_config(-1)
+    check(got, a, b, [4], [1], TOL[prec], layout)
+
+
 @pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
 def test_infinities_stay_in_their_rows(bad):
     """A row past the end of a tile repeats the last one, and k past the end
