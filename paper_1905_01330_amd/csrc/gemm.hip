@@ -565,6 +565,21 @@ static int tune_cfg(GemmDesc& d, int32_t prec, int level, hipStream_t st) {
   return best;
 }
 
+static void log_gemm(const GemmDesc& d, int32_t prec, int cfg, int lg, const char* how) {
+  const Cfg& g = kCfgs[cfg];
+  std::fprintf(stderr,
+               "[tn] gemm M=%d N=%d K=%d batch=%d groups(m,n,k)=(%d,%d,%d) modes(a,b,c)=(%d,%d,%d) prec=%d%s -> "
+               "tile %d (%dx%dx%d, %dx%dx%d waves) x%d k-slices %s\n",
+               d.M, d.N, d.K, d.batch, d.gm.n, d.gn.n, d.gk.n, d.a_mode, d.b_mode, d.c_mode, (int)prec,
+               g_shared ? " shared" : "", cfg, g.bm, g.bn, g.bk, g.wm, g.wn, g.wk, 1 << lg, how);
+}
+
+void note_direct(const GemmDesc& d, int32_t prec) {
+  SharedChipScope shared;
+  if (log_enabled()) log_gemm(d, prec, kCfg32, 0, "in a shared launch");
+  g_last_choice = kCfg32;
+}
+
 int32_t launch_gemm(GemmDesc& d, int32_t prec, hipStream_t st) {
   const bool log = log_enabled();
   const int forced = g_forced_cfg.load();
@@ -608,14 +623,7 @@ int32_t launch_gemm(GemmDesc& d, int32_t prec, hipStream_t st) {
     if (timed) append_cache_file_locked(key, cfg);
   }
   const int lg = slices_ok(d, choice_lg(cfg)) ? choice_lg(cfg) : 0;
-  if (log) {
-    const Cfg& g = kCfgs[choice_cfg(cfg)];
-    std::fprintf(stderr,
-                 "[tn] gemm M=%d N=%d K=%d batch=%d groups(m,n,k)=(%d,%d,%d) modes(a,b,c)=(%d,%d,%d) prec=%d%s -> "
-                 "tile %d (%dx%dx%d, %dx%dx%d waves) x%d k-slices %s\n",
-                 d.M, d.N, d.K, d.batch, d.gm.n, d.gn.n, d.gk.n, d.a_mode, d.b_mode, d.c_mode, (int)prec,
-                 g_shared ? " shared" : "", choice_cfg(cfg), g.bm, g.bn, g.bk, g.wm, g.wn, g.wk, 1 << lg, how);
-  }
+  if (log) log_gemm(d, prec, choice_cfg(cfg), lg, how);
   g_last_choice = choice_cfg(cfg);
   return launch_choice(d, prec, choice_cfg(cfg) + 100 * lg, st);
 }

@@ -863,15 +863,15 @@ int32_t tn_mps_env_sweep(int32_t n_sites, const tn_tensor* psi, const tn_tensor*
     WstepSite sl{&lc, kl >= 0 ? &psi[kl] : nullptr, kl >= 0 ? &mpo[kl] : nullptr, t2};
     WstepSite sr{&rc_, kr >= 0 ? &psi[kr] : nullptr, kr >= 0 ? &mpo[kr] : nullptr, t2r};
     tn_tensor nl{}, nr{};
-    GemmDesc g;
+    GemmDesc fl, fr;   // the first contractions
     const int32_t one2[1] = {2}, zero[1] = {0};
     if (kl >= 0) {
       const int64_t da = dims[kl], db = dims[kl + 1], wl = w[kl], wr = w[kl + 1];
       tn_tensor T1 = make_view(t1, TN_F32, {da, wl, d, db});
       tn_tensor T2 = make_view(t2, TN_F32, {da, d, wr, db});
       nl = L_out ? L_out[kl + 1] : make_view(buf[(kl + 1) & 1], TN_F32, {db, wr, db});
-      TN_TRY(plan_gemm(lc, psi[kl], 1, one2, zero, T1, g));
-      if (!direct_chosen(g, prec)) return TN_OK;
+      TN_TRY(plan_gemm(lc, psi[kl], 1, one2, zero, T1, fl));
+      if (!direct_chosen(fl, prec)) return TN_OK;
       const int32_t a3[2] = {0, 1}, b3[2] = {0, 1};
       TN_TRY(plan_gemm(psi[kl], T2, 2, a3, b3, nl, gl));
       if (!direct_chosen(gl, prec)) return TN_OK;
@@ -881,8 +881,8 @@ int32_t tn_mps_env_sweep(int32_t n_sites, const tn_tensor* psi, const tn_tensor*
       tn_tensor T1 = make_view(t1r, TN_F32, {da, d, db, wr});
       tn_tensor T2 = make_view(t2r, TN_F32, {wl, da, d, db});
       nr = R_out ? R_out[kr] : make_view(rbuf[kr & 1], TN_F32, {da, wl, da});
-      TN_TRY(plan_gemm(psi[kr], rc_, 1, one2, one2, T1, g));
-      if (!direct_chosen(g, prec)) return TN_OK;
+      TN_TRY(plan_gemm(psi[kr], rc_, 1, one2, one2, T1, fr));
+      if (!direct_chosen(fr, prec)) return TN_OK;
       const int32_t a3[2] = {1, 2}, b3[2] = {2, 3};
       TN_TRY(plan_gemm(psi[kr], T2, 2, a3, b3, nr, gr));
       if (!direct_chosen(gr, prec)) return TN_OK;
@@ -891,6 +891,8 @@ int32_t tn_mps_env_sweep(int32_t n_sites, const tn_tensor* psi, const tn_tensor*
     const GemmDesc *ql = kl >= 0 ? &gl : nullptr, *qr = kr >= 0 ? &gr : nullptr;
     if (!direct_wstep_ok(pl, pr) || !direct_pair_ok(ql, qr)) return TN_OK;
     TN_TRY(two.join());
+    if (kl >= 0) note_direct(fl, prec);
+    if (kr >= 0) note_direct(fr, prec);
     TN_TRY(launch_direct_wstep(pl, pr, prec, s));
     TN_TRY(launch_direct_pair(ql, qr, prec, s));
     if (kl >= 0) lc = nl;

@@ -219,3 +219,20 @@ def test_short_sums_of_a_sweep_are_exact(side, prec, gate):
     torch.cuda.synchronize()
     got, want = (gl[2], ls[2]) if left else (gr[1], rs[1])
     np.testing.assert_allclose(got.cpu().double().numpy(), want, rtol=gate)
+
+
+@pytest.mark.parametrize("call", ["inner", "sweep"])
+def test_last_choice_of_a_shared_launch(call):
+    """Products that share a launch are seen by tune_last_choice as others are."""
+    rng = np.random.default_rng(13)
+    dims = [1, 40, 50, 60, 40, 1]
+    psi = [gpu(rng.standard_normal((dims[k], 2, dims[k + 1])) / 10) for k in range(5)]
+    mpo = [gpu(rng.standard_normal((1 if k == 0 else 3, 1 if k == 4 else 3, 2, 2))) for k in range(5)]
+    big = gpu(rng.standard_normal((2048, 2048)))
+    tn.contract_between(big, big, [1], [1])
+    assert tn.tune_last_choice() != TILE
+    if call == "inner":
+        tn.mps_inner(psi, psi)
+    else:
+        tn.mps_env_sweep(psi, mpo, store=False)
+    assert tn.tune_last_choice() == TILE
