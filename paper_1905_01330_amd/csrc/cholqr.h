@@ -14,7 +14,9 @@ constexpr uint64_t kMaxE = (uint64_t)(1023 - 35) << 52;
 // where the site is certified
 __device__ __forceinline__ bool chol_certified(const uint64_t* ebits) { return ebits && *ebits <= kMaxE; }
 
-constexpr size_t kCholLinv = 2 * 64 * 64;   // doubles
+// the factor L of two diagonal blocks in turn, each with the sums of squares of
+// its 64 x 64 entries and of R's, eight parts each
+constexpr size_t kCholLinv = 2 * (64 * 64 + 16);   // doubles
 
 // x (dk x cols, row-major) = r (dk x dk upper triangular, zero below) a
 int32_t chol_absorb(const double* r, const double* a, double* x, int dk, int cols, hipStream_t st);

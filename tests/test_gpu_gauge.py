@@ -119,6 +119,44 @@ def test_more_rows_than_the_panels_take(kind):
     check(raw, *gauge(raw), agree=not kind)
 
 
+def conditioned(kind, n, cond, seed):
+    """2 n x n: one small value, values spread evenly, half of them small, or
+    independent columns of sizes spread evenly."""
+    rng = np.random.default_rng(seed)
+    if kind == "columns":
+        return rng.standard_normal((2 * n, n)) * np.exp(-np.log(cond) * rng.uniform(0, 1, n))
+    u = np.linalg.qr(rng.standard_normal((2 * n, n)))[0]
+    v = np.linalg.qr(rng.standard_normal((n, n)))[0]
+    s = np.ones(n)
+    if kind == "one":
+        s[-1] = 1 / cond
+    elif kind == "spread":
+        s = np.exp(-np.log(cond) * np.arange(n) / (n - 1))
+    else:
+        s[n // 2:] = 1 / cond
+    return (u * s) @ v.T
+
+
+@pytest.mark.parametrize("cond", [3, 30, 100, 300, 1000, 3000])
+@pytest.mark.parametrize("n", [33, 64, 65, 130])
+@pytest.mark.parametrize("kind", ["one", "spread", "half", "columns"])
+def test_conditions_across_the_certificate(kind, n, cond):
+    """Sites that the certificate takes easily, at its edge (conditions of some
+    hundreds) and not at all.  The chain's second site is the identity behind a
+    column e_0, so the factors come out: Q, and R over a norm (the site's first
+    entry, R_00 of the e_0, is left out: its reflector rounds it to the norm's
+    eps, not its own).  |Q^T Q - I| as above; a column of
+    Q R - X holds four sums of up to n roundings, 4 sqrt(n) eps of the column."""
+    x = conditioned(kind, n, cond, n + cond)
+    got, lognorm = gauge([x.reshape(1, 2 * n, n), np.c_[np.eye(n)[:, :1], np.eye(n)].reshape(n, n + 1, 1)])
+    q = got[0][0]
+    assert np.abs(q.T @ q - np.eye(n)).max() <= 4 * 2 * n * EPS
+    r = got[1][:, 1:, 0].astype(np.longdouble) * np.exp(np.longdouble(lognorm))
+    assert np.all(np.diag(r) > 0) and not np.tril(r, -1).any()
+    res = (q.astype(np.longdouble) @ r - x).astype(np.float64)
+    assert (np.linalg.norm(res, axis=0) <= 4 * np.sqrt(n) * EPS * np.linalg.norm(x, axis=0)).all()
+
+
 def test_mixed_chain_alternates_the_buffers():
     """Neighbouring sites with and without a certificate share the two sets of buffers."""
     rng = np.random.default_rng(3)
