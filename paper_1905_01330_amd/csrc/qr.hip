@@ -342,6 +342,15 @@ __device__ __forceinline__ void qr_stage(double (*st)[kQrNb + 1], const double (
   for (int c = 0; c < kQrNb; ++c) st[threadIdx.x & 63][c] = v[c];
   qr_wave_order();
 }
+// A^T B of a wave's 64 rows, operands as qr_rows reads them.  Sixteen rows a
+// chain: summed in a tree as far as the matrix cores' own order allows
+// (64 in one chain: |Q R - X| of a factorisation 1.2 times as large).
+__device__ __forceinline__ qr_d4_t qr_products(const double (&a)[16], const double (&b)[16]) {
+  qr_d4_t w[4] = {};
+#pragma unroll
+  for (int kk = 0; kk < 16; ++kk) w[kk & 3] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[kk], b[kk], w[kk & 3], 0, 0, 0);
+  return (w[0] + w[1]) + (w[2] + w[3]);
+}
 // the staged rows as a right operand (or, transposed, a left one) of a sum
 // over the rows: k = 4 kk + lane / 16, column lane % 16
 __device__ __forceinline__ void qr_rows(const double (*st)[kQrNb + 1], double (&o)[16]) {
@@ -386,8 +395,8 @@ __device__ __forceinline__ void qr_store(const double (&x)[kQrNb], __amdgpu_buff
 // workgroup's loads; each application also costs a release and an acquire of
 // the caches, so a task takes a panel's 16 columns.  With four columns a task,
 // summed by vector instructions, the applications were longer than the panels
-// from 1024 rows on: 2048 x 1024 7.1 -> 4.3 ms (4.9 with a launch a panel and a
-// launch an application), 1024 x 1024 4.5 -> 2.7, 512 x 512 1.38 -> 1.13.  Up
+// from 1024 rows on: 2048 x 1024 7.1 -> 4.2 ms (4.9 with a launch a panel and a
+// launch an application), 1024 x 1024 4.5 -> 2.7, 512 x 512 1.38 -> 1.09.  Up
 // to two rows a thread x is read once and held between the two products, and
 // the reflectors are read ahead of them; with four the registers hold neither.
 template <int NR, class F>
@@ -413,8 +422,7 @@ __device__ __forceinline__ void qr_block(__amdgpu_buffer_rsrc_t rs, const double
     qr_rows(st, a);
     qr_stage(st, y);
     qr_rows(st, b);
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) w = __builtin_amdgcn_mfma_f64_16x16x4f64(a[kk], b[kk], w, 0, 0, 0);
+    w += qr_products(a, b);
   };
   if constexpr (HOLD) {
 #pragma unroll
@@ -518,8 +526,7 @@ __device__ inline void qr_panel(double* xc, double* tau, double* tf, int m, int 
       double o[16];
       qr_stage(sm.stage[wave], x[q]);
       qr_rows(sm.stage[wave], o);
-#pragma unroll
-      for (int kk = 0; kk < 16; ++kk) g = __builtin_amdgcn_mfma_f64_16x16x4f64(o[kk], o[kk], g, 0, 0, 0);
+      g += qr_products(o, o);
     }
 #pragma unroll
     for (int r = 0; r < 4; ++r) sm.part[wave][r * 64 + lane] = g[r];
@@ -643,7 +650,7 @@ __device__ inline void qr_store_y(double* y, int m, int r0, int cb0, int ncols, 
 
 // The whole factorisation in one launch.  The workgroup that is first does the
 // panels, one after the other (its code and its own panel stay close; dealt to
-// any workgroup they took 49 us each at 512 x 512, so 44, and now 35), each with the
+// any workgroup they took 49 us each at 512 x 512, so 44, and now 34), each with the
 // panel before it applied to its own columns.  The tasks of the others are the
 // applications of panel p to the columns of a panel past p + 1, in the order of
 // p, taken from a counter.  An application waits for its panel and for the last
@@ -831,7 +838,7 @@ static int qr_grid(int n) { return std::min(256, qr_panels(n)); }
 
 // Y := Q Y or Q [I; 0], the rows 1, 2 or 4 a thread as in the factorisation (a
 // panel's rows start at its first; with 4 a thread throughout, 512 x 512 took
-// 2.49 ms to factorise and 0.38 ms here, with 2 then 1 1.91, now 1.13, and 0.21)
+// 2.49 ms to factorise and 0.38 ms here, with 2 then 1 1.91, now 1.09, and 0.21)
 static void launch_form(const double* xc, const double* tf, double* y, int m, int n, int ncols, bool eye,
                         const uint64_t* cert, hipStream_t st) {
   const dim3 grid((unsigned)((ncols + kQrCb - 1) / kQrCb)), blk(kQrThreads);
