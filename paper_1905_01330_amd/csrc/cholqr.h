@@ -5,11 +5,14 @@
 
 namespace tn {
 
-// The largest |E| that certifies a site, 2^-35, as bits: 1024 columns bound
-// |E|_2^2 by (1024 2^-35)^2 < 2^-49 at the very worst, and by about 2^-60 for
-// errors of random signs
+// The largest |E| that certifies a site of up to kMaxEn columns, 2^-35, as
+// bits; beyond, it falls as 1 / n.  The neglected terms are |E|_2^2 <= (n max
+// |E|)^2 <= 2^-52 from kMaxEn columns on, an FP64 rounding at the very worst,
+// and below that width less (2^-61 or so for errors of random signs).
 constexpr uint64_t kMaxE = (uint64_t)(1023 - 35) << 52;
-// ebits: the bits of max |E| (a NaN's are larger than any number's); kernels
+constexpr int kMaxEn = 512;
+// ebits: the bits of max |E| max(1, n / kMaxEn) (a NaN's are larger than any
+// number's); kernels
 // of the Householder path take it as `cert` (null: run) and leave at once
 // where the site is certified
 __device__ __forceinline__ bool chol_certified(const uint64_t* ebits) { return ebits && *ebits <= kMaxE; }

@@ -9,15 +9,16 @@
 // Fukaya, ETNA 44, 2015, for the two passes; the second one's factor is
 // I + U + O(E^2)).
 //
-// Certificate: max |E| is taken over the computed Q1^T Q1.  Up to kMaxE the
-// neglected terms stay below an FP64 rounding; above it, or with a NaN (a
-// pivot that is not positive, an overflow), the site is left to the
-// Householder kernels.  Both sets of kernels are always launched and look at
-// the certificate on the device: no host synchronisation, capturable.
+// Certificate: max |E| is taken over the computed Q1^T Q1.  Up to kMaxE (less
+// for more than kMaxEn columns) the neglected terms stay below an FP64
+// rounding; above it, or with a NaN (a pivot that is not positive, an
+// overflow), the site is left to the Householder kernels.  Both sets of kernels
+// are always launched and look at the certificate on the device: no host
+// synchronisation, capturable.
 //
 // Everything is FP64 matrix-core work on the whole chip, 64 columns at a
 // time; the Householder panels are a chain of one workgroup's reductions over
-// the rows, one a column.  The chain of 100 sites of bond 1024 of two states:
+// the rows, one a column.  A chain of 28 sites of two states and bond 1024:
 // 58.1 ms by Householder panels, 8.4 ms here.
 #include "cholqr.h"
 
@@ -199,6 +200,8 @@ __global__ void __launch_bounds__(512) chol_gemm_kernel(const CholGemm p) {
     if (threadIdx.x == 0) {
 #pragma unroll
       for (int w = 1; w < 8; ++w) emax = max(emax, smax[w]);
+      // by the width, towards the limit of kMaxEn columns (a NaN stays one)
+      emax = __double_as_longlong(fabs(__longlong_as_double(emax) * max(1.0, p.N * (1.0 / kMaxEn))));
       atomicMax((unsigned long long*)p.ebits, (unsigned long long)emax);
     }
   }

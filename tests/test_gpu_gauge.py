@@ -137,9 +137,9 @@ def conditioned(kind, n, cond, seed):
     return (u * s) @ v.T
 
 
-@pytest.mark.parametrize("cond", [3, 30, 100, 300, 1000, 3000])
-@pytest.mark.parametrize("n", [33, 64, 65, 130])
-@pytest.mark.parametrize("kind", ["one", "spread", "half", "columns"])
+@pytest.mark.parametrize("kind,n,cond", [(kind, n, cond) for kind in ("one", "spread", "half", "columns")
+                                         for n in (33, 64, 65, 130) for cond in (3, 30, 100, 300, 1000, 3000)]
+                         + [("half", 600, 30), ("half", 600, 100), ("half", 600, 300), ("one", 513, 300)])
 def test_conditions_across_the_certificate(kind, n, cond):
     """Sites that the certificate takes easily, at its edge (conditions of some
     hundreds) and not at all.  The chain's second site is the identity behind a
