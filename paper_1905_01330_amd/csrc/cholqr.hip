@@ -413,10 +413,12 @@ __global__ void __launch_bounds__(kCholThreads) chol_step_kernel(const CholStep 
 #pragma unroll
     for (int e = 0; e < 8; ++e) vl[e] = p.linv[threadIdx.x + kCholThreads * e];
     double fl = 0.0, fr = 0.0;   // |L|_F^2, |R_kk|_F^2
+    if (!in_g) {
 #pragma unroll
-    for (int w = 0; w < 8; ++w) {
-      fl += p.linv[kCb * kCb + w];
-      fr += p.linv[kCb * kCb + 8 + w];
+      for (int w = 0; w < 8; ++w) {
+        fl += p.linv[kCb * kCb + w];
+        fr += p.linv[kCb * kCb + 8 + w];
+      }
     }
     if (!solve_only) fetch(p.g, n, k0, j0, v1);
     if (!in_g) fetch(p.x, p.m, i0, k0, v2);
