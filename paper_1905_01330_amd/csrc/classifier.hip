@@ -390,9 +390,8 @@ __global__ void __launch_bounds__(CHI / 16 * 64) chain_kernel(const ChainRuns ru
   else chain_run<CHI, 1>(a, sm);
 }
 
-// X[b, a, s] = v[b, a] * Phi_s(x_{b, site}) * (with_scale ? 2^(e_v[b] + e_w[b]) : 1)
-__global__ void expand_kernel(const float* vblk, const float* wblk_exp, const float* pixels, int n_pix, int site, int B,
-                              int chi, int d, float* x) {
+// X[b, a, s] = v[b, a] * Phi_s(x_{b, site})
+__global__ void expand_kernel(const float* vblk, const float* pixels, int n_pix, int site, int B, int chi, int d, float* x) {
   const int64_t total = (int64_t)B * d * 2;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
     const int s = (int)(e & 1);
@@ -400,12 +399,7 @@ __global__ void expand_kernel(const float* vblk, const float* wblk_exp, const fl
     const int b = (int)(ba / d), aa = (int)(ba % d);
     float sv, cv;
     sincospif(0.5f * pixels[(int64_t)b * n_pix + site], &sv, &cv);
-    float val = vblk[(int64_t)b * chi + aa] * (s == 0 ? cv : sv);
-    if (wblk_exp) {
-      const int ex = (int)vblk[(int64_t)B * chi + b] + (int)wblk_exp[b];
-      val = ldexpf(val, ex);
-    }
-    x[e] = val;
+    x[e] = vblk[(int64_t)b * chi + aa] * (s == 0 ? cv : sv);
   }
 }
 
@@ -909,12 +903,6 @@ int32_t forward_core(const Geometry& g, const tn_tensor* sites, const float* pix
   return TN_OK;
 }
 
-__global__ void unit_block_kernel(float* blk, int B, int chi) {
-  const int64_t total = vblock_floats(B, chi);
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x)
-    blk[e] = (e < (int64_t)B * chi && e % chi == 0) ? 1.f : 0.f;
-}
-
 }  // namespace
 
 }  // namespace tn
@@ -999,8 +987,8 @@ int32_t tn_mps_classifier_forward(int32_t n_sites, int32_t label_site, int32_t n
   // label site
   float* xbuf = reinterpret_cast<float*>(ws + w.xbuf);
   float* tbuf = reinterpret_cast<float*>(ws + w.tbuf);
-  hipLaunchKernelGGL(expand_kernel, dim3(blocks_of((int64_t)B * chi * 2)), dim3(256), 0, st, vc, (const float*)nullptr,
-                     px, n_sites, label_site, B, g.pad_chi, chi, xbuf);
+  hipLaunchKernelGGL(expand_kernel, dim3(blocks_of((int64_t)B * chi * 2)), dim3(256), 0, st, vc, px, n_sites, label_site,
+                     B, g.pad_chi, chi, xbuf);
   TN_TRY(hip_check(hipGetLastError(), "expand"));
   TN_TRY(label_t(g, sites[label_site], xbuf, tbuf, prec, st));
   hipLaunchKernelGGL(logits_kernel, dim3(blocks_of((int64_t)B * n_labels)), dim3(256), 0, st, tbuf, uc, vc, B, n_labels,
@@ -1056,8 +1044,8 @@ int32_t tn_mps_classifier_backward(int32_t n_sites, int32_t label_site, int32_t 
   const tn_tensor& ac = sites[label_site];
 
   // ---- label site
-  hipLaunchKernelGGL(expand_kernel, dim3(blocks_of((int64_t)B * chi * 2)), dim3(256), 0, st, vc, (const float*)nullptr,
-                     px, n_sites, label_site, B, pc, chi, xbuf);
+  hipLaunchKernelGGL(expand_kernel, dim3(blocks_of((int64_t)B * chi * 2)), dim3(256), 0, st, vc, px, n_sites, label_site,
+                     B, pc, chi, xbuf);
   TN_TRY(label_t(g, ac, xbuf, tbuf, prec, st));
   // dA_c[a, s, l, z] = sum_b Xc[b, a, s] (g[b, l] u[b, z] 2^(e_v + e_u))
   hipLaunchKernelGGL(gu_kernel, dim3(blocks_of((int64_t)B * n_labels * chi)), dim3(256), 0, st, gl, gs0, gs1, uc, vc, B,
