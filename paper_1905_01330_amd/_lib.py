@@ -155,10 +155,16 @@ def int_array(xs):
     return (C.c_int32 * max(1, len(xs)))(*xs)
 
 
+# The current stream's handle alone (a Stream object costs several times the
+# call), where this torch has the function
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def stream_ptr(stream=None):
     if stream is None:
-        # the handle alone: a Stream object costs several times the call
-        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+        if _raw_stream is not None:
+            return C.c_void_p(_raw_stream(torch.cuda.current_device()))
+        stream = torch.cuda.current_stream()
     return C.c_void_p(stream.cuda_stream)
 
 

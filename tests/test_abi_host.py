@@ -314,3 +314,14 @@ def test_complex_validation_before_launch():
                                        C.byref(out), FAKE + (5 << 30), 16, 0, None) == -4
     big = desc([2] * 7, B0, dtype=L.C64)                                 # b of rank 7: above 6
     assert lib.tn_contract_between_c64_workspace(C.byref(big), C.byref(nbytes)) == -3
+
+
+def test_stream_without_the_raw_handle(monkeypatch):
+    """A torch without the function for the handle alone: through a Stream."""
+    import types
+
+    stream = types.SimpleNamespace(cuda_stream=0x1230)
+    monkeypatch.setattr(L.torch.cuda, "current_stream", lambda: stream)
+    monkeypatch.setattr(L, "_raw_stream", None)
+    assert L.stream_ptr().value == 0x1230
+    assert L.stream_ptr(types.SimpleNamespace(cuda_stream=0x4560)).value == 0x4560
