@@ -497,8 +497,7 @@ int32_t tn_mps_inner_batched_launch(int32_t n_chains, const int32_t* site_offset
   // (capturable)
   hipStream_t ls = st;
   TN_TRY(side_stream(ls));
-  hipEvent_t hop = nullptr;
-  TN_TRY(hip_check(hipEventCreateWithFlags(&hop, hipEventDisableTiming), "create event"));
+  StreamMark hop;
   bool left_on_side = false;
   auto run = [&](const Launch& L, int cfg, hipStream_t s) {
     return launch_gemm_grouped(d_probs + L.prob_off, d_tiles + L.tile_off[cfg], L.n_probs, L.tiles[cfg], prec, cfg,
@@ -548,25 +547,26 @@ int32_t tn_mps_inner_batched_launch(int32_t n_chains, const int32_t* site_offset
   int32_t rc = TN_OK;
   for (const Launch& L : Q.launches) {
     if (L.side == 1 && !left_on_side) {
-      hipEventRecord(hop, st);
-      hipStreamWaitEvent(ls, hop, 0);
+      rc = hop.set(st);
+      if (rc == TN_OK) rc = hop.wait(ls);
       left_on_side = true;
     } else if (L.side == 0 && L.has_left && left_on_side) {
-      hipEventRecord(hop, ls);
-      hipStreamWaitEvent(st, hop, 0);
+      rc = hop.set(ls);
+      if (rc == TN_OK) rc = hop.wait(st);
       left_on_side = false;
     }
-    rc = issue(L);
+    if (rc == TN_OK) rc = issue(L);
     if (rc != TN_OK) break;
   }
   if (e0) hipEventDestroy(e0);
   if (e1) hipEventDestroy(e1);
+  int32_t joined = TN_OK;
   if (left_on_side) {
-    hipEventRecord(hop, ls);
-    hipStreamWaitEvent(st, hop, 0);
+    joined = hop.set(ls);
+    if (joined == TN_OK) joined = hop.wait(st);
   }
-  hipEventDestroy(hop);
   TN_TRY(rc);
+  TN_TRY(joined);
   double* parts = reinterpret_cast<double*>(ws + Q.parts);
   hipLaunchKernelGGL(batched_sum_kernel, dim3(n_chains, kFinishParts), dim3(kFinishThreads), 0, st, d_chains, parts);
   hipLaunchKernelGGL(batched_finish_kernel, dim3(n_chains), dim3(64), 0, st, d_chains, parts, out2);

@@ -154,6 +154,42 @@ int grouped_tile_m(int cfg);
 // behind each other's side work.  Work is forked from and joined back into
 // the caller's stream by events.
 int32_t side_stream(hipStream_t& s);
+
+// A place in one or two streams' work that another stream waits for.  It has
+// an event for each stream that it is set on: a capture keeps the events
+// recorded on each of its streams until it ends, and destroying an event takes
+// it from the stream it was last recorded on alone, so one event for both
+// would be looked at by the capture's end after it is gone.
+class StreamMark {
+ public:
+  StreamMark() = default;
+  StreamMark(const StreamMark&) = delete;
+  StreamMark& operator=(const StreamMark&) = delete;
+  ~StreamMark() {
+    for (int i = 0; i < n_; ++i) (void)hipEventDestroy(ev_[i]);
+  }
+  int32_t set(hipStream_t s) {
+    int i = 0;
+    while (i < n_ && on_[i] != s) ++i;
+    if (i == 2) return fail(TN_ERR_DEVICE, "a mark is set on two streams at most");
+    if (i == n_) {
+      TN_TRY(hip_check(hipEventCreateWithFlags(&ev_[i], hipEventDisableTiming), "create event"));
+      on_[i] = s;
+      ++n_;
+    }
+    last_ = i;
+    return hip_check(hipEventRecord(ev_[i], s), "record event");
+  }
+  // s's later work waits for where the mark was last set, if it was
+  int32_t wait(hipStream_t s) const {
+    return last_ < 0 ? TN_OK : hip_check(hipStreamWaitEvent(s, ev_[last_], 0), "wait event");
+  }
+
+ private:
+  hipStream_t on_[2] = {};
+  hipEvent_t ev_[2] = {};
+  int n_ = 0, last_ = -1;
+};
 // grouped tile configuration pinned by tn_tune_force_grouped_config, or -1
 int forced_grouped_cfg();
 // the tuning level when timing is allowed on st now (not disabled on this

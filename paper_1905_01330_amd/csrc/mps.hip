@@ -178,18 +178,11 @@ static int32_t inner_launch(GemmDesc& g1, GemmDesc& g2, int32_t prec, hipStream_
 struct TwoStreams {
   hipStream_t st, side;
   bool forked = false;
-  hipEvent_t ev = nullptr;
+  StreamMark mark;
   explicit TwoStreams(hipStream_t s) : st(s), side(s) {}
-  ~TwoStreams() {
-    if (ev) hipEventDestroy(ev);
-  }
   int32_t order(hipStream_t before, hipStream_t after) {
-    if (!ev && hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
-      ev = nullptr;
-      return fail(TN_ERR_DEVICE, "create event failed");
-    }
-    TN_TRY(hip_check(hipEventRecord(ev, before), "record event"));
-    return hip_check(hipStreamWaitEvent(after, ev, 0), "wait event");
+    TN_TRY(mark.set(before));
+    return mark.wait(after);
   }
   int32_t fork() {
     if (forked) return TN_OK;

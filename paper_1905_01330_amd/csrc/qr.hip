@@ -952,18 +952,7 @@ int32_t tn_mps_left_canonicalize(int32_t n_sites, tn_tensor* sites, double* logn
   // that Q is done (event per set); the call ends joined on the caller's stream.
   hipStream_t side = st;
   TN_TRY(side_stream(side));
-  hipEvent_t ev_fact = nullptr, ev_q[2] = {nullptr, nullptr};
-  struct EventGuard {
-    hipEvent_t* e[3];
-    ~EventGuard() {
-      for (hipEvent_t* p : e)
-        if (*p) hipEventDestroy(*p);
-    }
-  } guard{{&ev_fact, &ev_q[0], &ev_q[1]}};
-  for (hipEvent_t* e : guard.e)
-    if (hipEventCreateWithFlags(e, hipEventDisableTiming) != hipSuccess) return fail(TN_ERR_DEVICE, "create event failed");
-  hipEventRecord(ev_q[0], st);
-  hipEventRecord(ev_q[1], st);
+  StreamMark factored, formed[2];
   hipLaunchKernelGGL(one_kernel, dim3(1), dim3(64), 0, st, r);
   int32_t rc = TN_OK;
   for (int k = 0; k < n_sites && rc == TN_OK; ++k) {
@@ -974,7 +963,8 @@ int32_t tn_mps_left_canonicalize(int32_t n_sites, tn_tensor* sites, double* logn
     const int dk = (int)sites[k].shape[0], d = (int)sites[k].shape[1], dn = (int)sites[k].shape[2];
     const int m = dk * d, n = dn;
     double* a = static_cast<double*>(sites[k].data);
-    hipStreamWaitEvent(st, ev_q[h], 0);   // site k-2's Q no longer reads this set
+    rc = formed[h].wait(st);   // site k-2's Q no longer reads this set
+    if (rc != TN_OK) break;
     // Cholesky first: the site's X and Q1 take the places of the Householder
     // path's, which then forms its own X again, or leaves at once where the
     // certificate holds
@@ -1006,10 +996,10 @@ int32_t tn_mps_left_canonicalize(int32_t n_sites, tn_tensor* sites, double* logn
     // tau, which the next site overwrites, so it stays on the caller's stream
     hipStream_t qs = blocked ? side : st;
     if (blocked) {
-      hipEventRecord(ev_fact, st);
-      hipStreamWaitEvent(side, ev_fact, 0);
+      rc = factored.set(st);
+      if (rc == TN_OK) rc = factored.wait(side);
     }
-    if (cert) rc = chol_q(qc, u, a, m, n, cert, qs);
+    if (rc == TN_OK && cert) rc = chol_q(qc, u, a, m, n, cert, qs);
     if (rc != TN_OK) break;
     if (blocked) {
       launch_form(xc, tf, qc, m, n, n, true, cert, qs);
@@ -1019,12 +1009,15 @@ int32_t tn_mps_left_canonicalize(int32_t n_sites, tn_tensor* sites, double* logn
         hipLaunchKernelGGL(reflect_cols_kernel, dim3(n - j), dim3(256), 0, qs, xc, tau, qc, m, j, j, cert);
     }
     hipLaunchKernelGGL(finalize_q_kernel, dim3(blocks_for((int64_t)m * n)), dim3(256), 0, qs, xc, qc, a, m, n, cert);
-    hipEventRecord(ev_q[h], qs);
     rc = hip_check(hipGetLastError(), "canonicalize");
+    const int32_t set = formed[h].set(qs);
+    if (rc == TN_OK) rc = set;
   }
   // join: every Q written back before the call's later work on the caller's stream
-  hipStreamWaitEvent(st, ev_q[0], 0);
-  hipStreamWaitEvent(st, ev_q[1], 0);
+  for (const StreamMark& q : formed) {
+    const int32_t joined = q.wait(st);
+    if (rc == TN_OK) rc = joined;
+  }
   TN_TRY(rc);
   hipLaunchKernelGGL(lognorm_kernel, dim3(1), dim3(64), 0, st, r, lognorm);
   return hip_check(hipGetLastError(), "lognorm");
