@@ -13,8 +13,8 @@
 //      on the whole chip (jac_gemm_kernel).
 // The chain is one LDS step a rotation (0.45 us) and a launch a round (5.5 us
 // beside its steps): 31 rounds of 13 and 20 us at 512 columns, 0.48 ms a sweep
-// with the products and the check; 512 x 512 as a whole 24.9 -> 7.1 ms, 1000 x 1000
-// 77 -> 20 ms.
+// with the products and the check; 512 x 512 as a whole 24.9 -> 6.6 ms, 1000 x 1000
+// 77 -> 17.8 ms.
 //
 // Accuracy.  G is formed anew from the columns before each sweep, and the
 // columns' orthogonality is judged on it with the same bound as the

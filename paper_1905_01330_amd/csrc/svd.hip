@@ -56,7 +56,8 @@ constexpr int kMaxSweeps = 100;
 constexpr int kPrecondMinCols = 32;   // narrower nodes converge in a few sweeps anyway
 constexpr int kInnerSweeps = 14;
 // fewer columns are one or two block pairs of the kernels above: 24 x 24 takes
-// 0.56 ms with them; 32 x 32 0.68 against 0.77, 64 x 64 1.1 against 1.6
+// 0.60 ms with them and 0.62 to 0.65 on the Gram matrix; 32 x 32 0.74 and 0.59
+// to 0.67, 64 x 64 1.53 and 0.88
 constexpr int kGramMinCols = 32;
 constexpr int kGramSweeps = 30;       // sweeps on the Gram matrix before the columns' own take over
 
