@@ -574,9 +574,12 @@ static void log_gemm(const GemmDesc& d, int32_t prec, int cfg, int lg, const cha
                g_shared ? " shared" : "", cfg, g.bm, g.bn, g.bk, g.wm, g.wn, g.wk, 1 << lg, how);
 }
 
-void note_direct(const GemmDesc& d, int32_t prec) {
-  SharedChipScope shared;
-  if (log_enabled()) log_gemm(d, prec, kCfg32, 0, "in a shared launch");
+void note_direct(const GemmDesc* l, const GemmDesc* r, int32_t prec) {
+  if (log_enabled()) {
+    SharedChipScope shared;
+    for (const GemmDesc* d : {l, r})
+      if (d) log_gemm(*d, prec, kCfg32, 0, "in a shared launch");
+  }
   g_last_choice = kCfg32;
 }
 

@@ -181,8 +181,7 @@ int32_t launch_direct_pair(const GemmDesc* l, const GemmDesc* r, int32_t prec, h
   int64_t t0 = 0, t1 = 0;
   if (l) TN_TRY(direct_desc(*l, p.d0, t0));
   if (r) TN_TRY(direct_desc(*r, p.d1, t1));
-  for (const GemmDesc* d : {l, r})
-    if (d) note_direct(*d, prec);
+  note_direct(l, r, prec);
   if (!l) p.d0 = p.d1;
   if (!r) p.d1 = p.d0;
   if (t0 + t1 >= (1ll << 31)) return fail(TN_ERR_UNSUPPORTED, "grid too large");

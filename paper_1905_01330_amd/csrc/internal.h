@@ -95,8 +95,9 @@ int32_t launch_gemm_direct(const GemmDesc& d, int32_t prec, hipStream_t st);
 // direct kernel: few tiles, not a problem of the small-extent path, no tile
 // forced, no tuning and no tile cache file that could say otherwise
 bool direct_chosen(const GemmDesc& d, int32_t prec);
-// its line in the log and the thread's last choice, as launch_gemm has them
-void note_direct(const GemmDesc& d, int32_t prec);
+// the products of such a launch (either may be null): their lines in the log
+// and the thread's last choice, as launch_gemm has them
+void note_direct(const GemmDesc* l, const GemmDesc* r, int32_t prec);
 // two independent GEMMs (either may be null) in one launch of the direct
 // kernel, where direct_pair_ok
 bool direct_pair_ok(const GemmDesc* l, const GemmDesc* r);

@@ -884,8 +884,7 @@ int32_t tn_mps_env_sweep(int32_t n_sites, const tn_tensor* psi, const tn_tensor*
     const GemmDesc *ql = kl >= 0 ? &gl : nullptr, *qr = kr >= 0 ? &gr : nullptr;
     if (!direct_wstep_ok(pl, pr) || !direct_pair_ok(ql, qr)) return TN_OK;
     TN_TRY(two.join());
-    if (kl >= 0) note_direct(fl, prec);
-    if (kr >= 0) note_direct(fr, prec);
+    note_direct(kl >= 0 ? &fl : nullptr, kr >= 0 ? &fr : nullptr, prec);
     TN_TRY(launch_direct_wstep(pl, pr, prec, s));
     TN_TRY(launch_direct_pair(ql, qr, prec, s));
     if (kl >= 0) lc = nl;
