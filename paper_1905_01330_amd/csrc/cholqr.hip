@@ -220,10 +220,11 @@ __global__ void __launch_bounds__(512) chol_gemm_kernel(const CholGemm p) {
 // Q_t = X_tk L^T leaves a residual X_tk - Q_t R_kk of the rounding of L times
 // the condition of the block R_kk, which no correction by E takes back.  Where
 // |R_kk|_F |L|_F, 64 for an orthogonal block, is above kRefine, X's tiles
-// therefore solve for it once more, Q_t += (X_tk - Q_t R_kk) L^T.  On sites of
-// 40 to 192 columns and conditions to 800, against a Householder factorisation:
-// |Q R - X| up to 23 times without, 0.8 at most with it; |Q| off by up to 10
-// times, 1.5 at most.  Sites near an isometry take none.
+// therefore solve for it once more, Q_t += (X_tk - Q_t R_kk) L^T.  Sites of 33
+// to 100 columns and conditions to 300: |Q R - X| up to 11 sqrt(n) eps of a
+// column without it, 0.8 with it, 0.6 by Householder; Q up to five times as far
+// from the exact one as Householder's, and as near with it.  Sites near an
+// isometry take none.
 constexpr double kRefine = 128.0;
 
 constexpr int kCb = 64;                  // block
